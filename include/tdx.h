@@ -341,7 +341,8 @@ int tdx_chi0_batched(tdx_ctx *ctx, const tdx_chi0_item *items, int n_items, int 
  * workgroup x chunk, and for split-BF16 buffering and waves per workgroup). */
 int tdx_chi0_variants(int prec, int *count);
 /* Tile variant (-1 = default: for split-BF16 the 8-wave 2 x 9 tile with three
- * LDS buffers, for FP32 and FP64 variant 0) and slice length 2^slice_log2
+ * LDS buffers, for FP32 variant 0, for FP64 variant 0 or 3 by the number of
+ * pairs of basis vectors) and slice length 2^slice_log2
  * (default 2^20; split-BF16 only, the FP32 and FP64 kernels choose their
  * slices to fill the chip) used for bases of n_g vectors (size classes of
  * 16), per precision. */

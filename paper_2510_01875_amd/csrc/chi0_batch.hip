@@ -14,7 +14,9 @@
 
 namespace tdx {
 
-int chi0_fp_variant_count(bool f64);  // chi0_fp.hip
+int chi0_fp32_variant_count();  // chi0_fp.hip
+int chi0_fp64_variant_count();  // chi0_fp64.hip
+int chi0_fp64_default_variant(int n_g);
 
 namespace {
 
@@ -86,10 +88,11 @@ void pick(const tdx_ctx *ctx, int ld, int *variant, int *slice_log2) {
   *slice_log2 = t.slice_log2;
 }
 
-// Tile variants of a precision (the FP32 and FP64 ones in chi0_fp.hip).
+// Tile variants of a precision.
 int variant_count(int prec) {
   return prec == TDX_PREC_BF16X3 ? bf16x3_variant_count()
-                                 : chi0_fp_variant_count(prec == TDX_PREC_FP64);
+         : prec == TDX_PREC_FP64 ? chi0_fp64_variant_count()
+                                 : chi0_fp32_variant_count();
 }
 
 const char *prec_name(int prec) {
@@ -356,7 +359,9 @@ int tdx_chi0_get_config(tdx_ctx *ctx, int prec, int n_g, int *variant, int *slic
     pick(ctx, (n_g + 15) / 16 * 16, variant, slice_log2);
   } else {
     const tdx_chi0_tune &t = ctx->tune[prec][bucket_of((n_g + 15) / 16 * 16)];
-    *variant = t.variant >= 0 ? t.variant : 0;
+    *variant = t.variant >= 0          ? t.variant
+               : prec == TDX_PREC_FP64 ? chi0_fp64_default_variant(n_g)
+                                       : 0;
     *slice_log2 = t.slice_log2;
   }
   return TDX_OK;
