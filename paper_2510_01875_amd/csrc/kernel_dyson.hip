@@ -15,6 +15,8 @@
 #include <climits>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 #include "internal.h"
 
@@ -224,30 +226,132 @@ __global__ void k_assemble_k(const int *gb, int n_g, double3 q, double3 b0, doub
 }
 
 // ------------------------------------------------------------------ Dyson
-constexpr int kT = 16;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// A_w = I - chi0_w K (row-major), batched over w.
-__global__ void k_one_minus(const double2 *chi0, const double2 *K, int n, double2 *A) {
-  __shared__ double2 sa[kT][kT + 1], sb[kT][kT + 1];
-  const int w = blockIdx.z;
-  const int i = blockIdx.y * kT + threadIdx.y, j = blockIdx.x * kT + threadIdx.x;
-  const double2 *C = chi0 + (size_t)w * n * n;
-  double re = 0.0, im = 0.0;
-  for (int l0 = 0; l0 < n; l0 += kT) {
-    const int la = l0 + threadIdx.x, lb = l0 + threadIdx.y;
-    sa[threadIdx.y][threadIdx.x] = (i < n && la < n) ? C[(size_t)i * n + la] : make_double2(0, 0);
-    sb[threadIdx.y][threadIdx.x] = (lb < n && j < n) ? K[(size_t)lb * n + j] : make_double2(0, 0);
-    __syncthreads();
+__device__ inline f64x4 mfma64(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// A_w = I - chi0_w K (row-major) for every w at once: the chi0 matrices form
+// one [n_w n][n] left operand, so the product is a single tall one on the
+// FP64 MFMA.  A wave owns 16 rows against CB blocks of 16 columns of K; its
+// rows come straight from global memory (one 16-byte value per lane and
+// K-step, a chunk ahead), chunks of 16 rows of K pass through LDS, double
+// buffered, for the four waves of the workgroup.  Rows and columns past the
+// end are clamped or zero and not stored.
+// At most three column blocks per workgroup: with nine (the rows read once)
+// the 1040 workgroups of the crystal's 500 matrices of 133 are two rounds and
+// a bit of the chip, 264 us against 210 (484 us on the vector units).
+constexpr int kOmCols = 3;
+
+template <int CB>
+__device__ __attribute__((always_inline)) void one_minus_tile(double2 *lds, const double2 *chi0,
+                                                              const double2 *K, int n,
+                                                              long long rows, long long r0, int c0,
+                                                              double2 *A) {
+  constexpr int kC = 16 * CB, kPer = CB;  // 16 kC values of K over 256 threads
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c16 = lane & 15, kq = lane >> 4;
+  const long long r = std::min(r0 + 16 * wave + c16, rows - 1);
+  const double2 *arow = chi0 + (size_t)r * n;
+  double2 a[4], kv[kPer];
+  auto load_a = [&](int k0) {
 #pragma unroll
-    for (int l = 0; l < kT; ++l) {
-      const double2 a = sa[threadIdx.y][l], b = sb[l][threadIdx.x];
-      re = fma(a.x, b.x, fma(-a.y, b.y, re));
-      im = fma(a.x, b.y, fma(a.y, b.x, im));
+    for (int s = 0; s < 4; ++s) a[s] = arow[std::min(k0 + 4 * s + kq, n - 1)];
+  };
+  auto load_k = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = tid + 256 * i, k = k0 + e / kC, c = c0 + e % kC;
+      const double2 v = K[(size_t)std::min(k, n - 1) * n + std::min(c, n - 1)];
+      kv[i] = k < n && c < n ? v : make_double2(0.0, 0.0);
     }
+  };
+  auto store_k = [&](double2 *buf) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) buf[tid + 256 * i] = kv[i];
+  };
+  f64x4 cr[CB], ci[CB];
+#pragma unroll
+  for (int b = 0; b < CB; ++b) cr[b] = ci[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  load_a(0);
+  load_k(0);
+  store_k(lds);
+  __syncthreads();
+  int cur = 0;
+  for (int k0 = 0; k0 < n; k0 += 16) {
+    const bool more = k0 + 16 < n;
+    double2 x[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = a[s];
+    if (more) {
+      load_a(k0 + 16);
+      load_k(k0 + 16);
+    }
+    const double2 *buf = lds + cur * 16 * kC;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (k0 + 4 * s >= n) break;
+#pragma unroll
+      for (int b = 0; b < CB; ++b) {
+        const double2 y = buf[(4 * s + kq) * kC + 16 * b + c16];
+        cr[b] = mfma64(x[s].x, y.x, cr[b]);
+        ci[b] = mfma64(x[s].x, y.y, ci[b]);
+        cr[b] = mfma64(-x[s].y, y.y, cr[b]);
+        ci[b] = mfma64(x[s].y, y.x, ci[b]);
+      }
+    }
+    if (more) store_k(lds + (cur ^ 1) * 16 * kC);
     __syncthreads();
+    cur ^= 1;
   }
-  if (i < n && j < n)
-    A[(size_t)w * n * n + (size_t)i * n + j] = make_double2((i == j ? 1.0 : 0.0) - re, -im);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const long long ro = r0 + 16 * wave + kq + 4 * j;  // row l/16 + 4 j of the FP64 MFMA's output
+    if (ro >= rows) continue;
+    const int i = (int)(ro % n);
+#pragma unroll
+    for (int b = 0; b < CB; ++b) {
+      const int c = c0 + 16 * b + c16;
+      if (c < n)
+        A[(size_t)ro * n + c] = make_double2((i == c ? 1.0 : 0.0) - cr[b][j], -ci[b][j]);
+    }
+  }
+}
+
+template <int CB>
+__device__ __attribute__((always_inline)) void one_minus_n(int cb, double2 *lds,
+                                                           const double2 *chi0, const double2 *K,
+                                                           int n, long long rows, long long r0,
+                                                           int c0, double2 *A) {
+  if constexpr (CB > 1) {
+    if (cb < CB) {
+      one_minus_n<CB - 1>(cb, lds, chi0, K, n, rows, r0, c0, A);
+      return;
+    }
+  }
+  one_minus_tile<CB>(lds, chi0, K, n, rows, r0, c0, A);
+}
+
+// Workgroup: 64 rows and one of the gridDim.y nearly equal column groups.
+__global__ void __launch_bounds__(256, 2)
+    k_one_minus(const double2 *chi0, const double2 *K, int n, long long rows, double2 *A) {
+  extern __shared__ double2 om_lds[];
+  const int nb = (n + 15) / 16, g = gridDim.y;
+  const int b0 = nb * (int)blockIdx.y / g, b1 = nb * ((int)blockIdx.y + 1) / g;
+  one_minus_n<kOmCols>(b1 - b0, om_lds, chi0, K, n, rows, 64LL * blockIdx.x, 16 * b0, A);
+}
+
+int one_minus(const double2 *chi0, const double2 *K, int n, int n_w, double2 *A, hipStream_t s) {
+  const int nb = (n + 15) / 16, groups = (nb + kOmCols - 1) / kOmCols;
+  const size_t lds = sizeof(double2) * 2 * 16 * 16 * ((nb + groups - 1) / groups);
+  const long long rows = (long long)n_w * n;
+  TDX_HIP(hipFuncSetAttribute((const void *)k_one_minus,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(k_one_minus, dim3((unsigned)((rows + 63) / 64), groups), dim3(256), lds, s,
+                     chi0, K, n, rows, A);
+  TDX_HIP(hipGetLastError());
+  return TDX_OK;
 }
 
 constexpr int kLuThreads = 256;
@@ -262,6 +366,454 @@ __device__ inline double2 cdiv(double2 a, double2 b) {
   }
   const double r = b.x / b.y, d = b.y + b.x * r;
   return make_double2((a.x * r + a.y) / d, (a.y * r - a.x) / d);
+}
+
+// ------------------------------------------------ blocked LU, one w per workgroup
+// Right-looking LU with partial pivoting (largest |re|+|im|, lowest row on
+// ties) in panels of 16 columns, for bases up to kLuMaxN vectors.  An
+// unblocked elimination passes over the whole trailing matrix in global
+// memory once per column, with three barriers and a tree reduction each time;
+// here
+//  - a thread holds one row (or two) of the panel in registers; each wave
+//    offers its best pivot row through LDS, so a column takes one barrier;
+//  - rows do not move during the panel: the chosen ones are moved to the top
+//    and the displaced ones into their places as the columns to the right are
+//    solved against the panel's unit triangle (a thread per column);
+//  - the trailing matrix is updated once per panel on the FP64 MFMA from the
+//    panel's multipliers and solved rows in LDS.
+// A panel is a serial chain (about 2800 cycles a column, of which the pivot
+// search and the row's way through LDS take most), so two workgroups share a
+// CU where LDS allows (n <= 144): one's panel runs beside the other's update.
+// The matrix stays in global memory (L2).  500 matrices of 133: 2.36 ms
+// unblocked, 0.40 ms here; 80 of 304: 16.6 ms and 1.3 ms.
+constexpr int kNb = 16;
+// Above 304 vectors the two 16-row operands of an update exceed LDS: the
+// unblocked kernels run.
+constexpr int kLuMaxN = 304;
+
+// Maximum over the wave, every lane (NaN is ignored).
+template <int CTRL, int ROWS>
+__device__ inline double dpp_max(double x) {
+  const int lo = __double2loint(x), hi = __double2hiint(x);
+  return fmax(x, __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false),
+                                  __builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false)));
+}
+__device__ inline double wave_max(double x) {
+  x = dpp_max<0x111, 0xf>(x);  // row_shr:1
+  x = dpp_max<0x112, 0xf>(x);  // row_shr:2
+  x = dpp_max<0x114, 0xf>(x);  // row_shr:4
+  x = dpp_max<0x118, 0xf>(x);  // row_shr:8
+  x = dpp_max<0x142, 0xa>(x);  // row_bcast:15
+  x = dpp_max<0x143, 0xc>(x);  // row_bcast:31
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                          __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+
+__device__ inline double lane_get(double x, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                          __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+// 1 / z for finite z != 0: z is scaled by a power of two to about one, so
+// |z|^2 neither overflows nor vanishes; the reciprocal by two Newton steps.
+__device__ inline double2 crecip(double2 z) {
+  const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(z.x), fabs(z.y)));
+  const double x = ldexp(z.x, -e), y = ldexp(z.y, -e);
+  const double d = fma(x, x, y * y);
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(fma(-d, r, 1.0), r, r);
+  r = fma(fma(-d, r, 1.0), r, r);
+  return make_double2(ldexp(x * r, -e), ldexp(-y * r, -e));
+}
+
+// LDS of a factorisation (sizes in double2): the multipliers [16][mp] and the
+// solved rows [16][mp] of a panel, its 16 x 16 block, the waves' pivot rows,
+// the right-hand side and the reciprocal pivots.
+struct LuLds {
+  double2 *L, *U, *D, *cand, *b, *rinv;
+  double *key;                              // [2][4] the waves' pivot sizes
+  int *crow, *src, *dst, *q, *perm, *info;  // info: row moves, failing column + 1
+  int mp;
+};
+constexpr int kCand = kNb + 2;  // a pivot row, its right-hand side, its reciprocal pivot
+__host__ __device__ inline int lu_mp(int n) { return std::max(16, (n - 1) / 16 * 16); }
+__host__ __device__ inline size_t lu_lds_bytes(int n, bool keep) {
+  return sizeof(double2) * ((size_t)2 * kNb * lu_mp(n) + kNb * kNb + 2 * (size_t)n) +
+         sizeof(double) * 8 + sizeof(int) * (8 + 3 * kNb + 2 + (keep ? (size_t)n : 0));
+}
+__device__ inline LuLds lu_lds(double2 *sm, int n) {
+  LuLds w;
+  w.mp = lu_mp(n);
+  w.L = sm;
+  w.U = w.L + kNb * w.mp;
+  w.D = w.U + kNb * w.mp;
+  w.cand = w.U;  // a panel's candidates are read before its solved rows are written
+  w.b = w.D + kNb * kNb;
+  w.rinv = w.b + n;
+  w.key = (double *)(w.rinv + n);
+  w.crow = (int *)(w.key + 8);
+  w.src = w.crow + 8;
+  w.dst = w.src + kNb;
+  w.q = w.dst + kNb;
+  w.info = w.q + kNb;
+  w.perm = w.info + 2;
+  return w;
+}
+
+// f(0), f(1), ... with compile-time arguments.
+template <class F, int... J>
+__device__ __attribute__((always_inline)) void lu_steps(F &f, std::integer_sequence<int, J...>) {
+  (f(std::integral_constant<int, J>{}), ...);
+}
+
+// One panel: columns k0 .. k0 + nb - 1, rows k0 .. n - 1 (at most NT RPL).
+// The right-hand side rides along as a column of its own.
+template <int NT, int RPL, bool KEEP, bool FULL>
+__device__ __attribute__((always_inline)) void lu_panel(double2 *A, int n, int k0, int cols,
+                                                        const LuLds &w) {
+  const int nb = FULL ? kNb : cols;  // straight-line steps for whole panels
+  constexpr int kWaves = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double2 a[RPL][kNb + 1];
+  bool act[RPL];
+  int at[RPL];  // panel step that chose the row
+#pragma unroll
+  for (int s = 0; s < RPL; ++s) {
+    const int r = k0 + tid + NT * s, rc = std::min(r, n - 1);
+    act[s] = r < n;
+    at[s] = 0;
+    const double2 *row = A + (size_t)rc * n + k0;
+#pragma unroll
+    for (int c = 0; c < kNb; ++c) a[s][c] = row[std::min(c, nb - 1)];
+    a[s][kNb] = w.b[rc];
+  }
+  int dead = 0;  // first column without a usable pivot + 1 (the rest is garbage then)
+  auto step = [&](auto jc) __attribute__((always_inline)) {
+    constexpr int j = decltype(jc)::value;
+    if (j >= nb) return;
+    // the thread's best row, then the wave's; its reciprocal pivot is formed
+    // beside the search
+    double best = -1.0;
+    double2 piv = a[0][j];
+    int slot = 0;
+#pragma unroll
+    for (int s = 0; s < RPL; ++s) {
+      const double v = act[s] ? cabs1(a[s][j]) : -1.0;
+      if (v > best) {
+        best = v;
+        piv = a[s][j];
+        slot = s;
+      }
+    }
+    const double2 rc = crecip(piv);
+    const double mx = wave_max(best);
+    const int pl = __ffsll((long long)__ballot(best == mx)) - 1;
+    const int buf = (j & 1) * kWaves;
+    if (lane == pl) {
+      double2 *o = w.cand + (buf + wave) * kCand;
+      o[0] = rc;
+#pragma unroll
+      for (int c = j; c <= kNb; ++c) {
+        double2 x = a[0][c];
+        if (RPL > 1 && slot == RPL - 1) x = a[RPL - 1][c];
+        o[c + 1] = x;
+      }
+      w.key[buf + wave] = mx;
+      w.crow[buf + wave] = tid + NT * slot;
+    }
+    __syncthreads();
+    double pmax = w.key[buf];
+    int row = w.crow[buf], from = 0;
+#pragma unroll
+    for (int v = 1; v < kWaves; ++v) {
+      const double k = w.key[buf + v];
+      const int r = w.crow[buf + v];
+      if (k > pmax || (k == pmax && r < row)) {
+        pmax = k;
+        row = r;
+        from = v;
+      }
+    }
+    if (dead == 0 && !(pmax > 0.0 && pmax < INFINITY)) dead = k0 + j + 1;
+    const double2 *uc = w.cand + (buf + from) * kCand;
+    double2 u[kNb + 1];
+    const double2 inv = uc[0];
+#pragma unroll
+    for (int c = j + 1; c <= kNb; ++c) u[c] = uc[c + 1];
+    if (tid == 0) {
+      w.q[j] = k0 + row;
+      w.rinv[k0 + j] = inv;
+    }
+#pragma unroll
+    for (int s = 0; s < RPL; ++s) {
+      if (row == tid + NT * s) {
+        act[s] = false;
+        at[s] = j;
+      }
+      const double2 x = a[s][j];
+      double2 l = make_double2(fma(x.x, inv.x, -(x.y * inv.y)), fma(x.x, inv.y, x.y * inv.x));
+      if (act[s])
+        a[s][j] = l;
+      else
+        l = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int c = j + 1; c <= kNb; ++c) {
+        a[s][c].x = fma(-l.x, u[c].x, fma(l.y, u[c].y, a[s][c].x));
+        a[s][c].y = fma(-l.x, u[c].y, fma(-l.y, u[c].x, a[s][c].y));
+      }
+    }
+  };
+  lu_steps(step, std::make_integer_sequence<int, kNb>{});
+  if (dead && tid == 0) w.info[1] = dead;
+  __syncthreads();
+  if (dead) return;
+  // rows k0 .. k0 + nb - 1 that were not chosen take the places of the chosen
+  // rows below them, in order (the first wave holds all of them)
+  const bool displaced = act[0] && tid < nb;
+  int rank = 0;
+  if (wave == 0) {
+    const unsigned long long dm = __ballot(displaced), below = (1ull << lane) - 1;
+    const int qj = lane < nb ? w.q[lane] : 0;
+    const bool vac = lane < nb && qj >= k0 + nb;
+    const unsigned long long vm = __ballot(vac);
+    if (vac) w.dst[__popcll(vm & below)] = qj;
+    rank = __popcll(dm & below);
+    if (displaced) w.src[rank] = k0 + lane;
+    if (lane == 0) w.info[0] = __popcll(dm);
+    __threadfence_block();
+  }
+#pragma unroll
+  for (int s = 0; s < RPL; ++s) {
+    const int r = k0 + tid + NT * s;
+    if (r >= n) continue;
+    if (act[s]) {
+      const int p = s == 0 && displaced ? w.dst[rank] : r;
+#pragma unroll
+      for (int c = 0; c < kNb; ++c) {
+        if (c >= nb) continue;
+        w.L[c * w.mp + p - k0 - nb] = a[s][c];
+        if constexpr (KEEP) A[(size_t)p * n + k0 + c] = a[s][c];
+      }
+      w.b[p] = a[s][kNb];
+    } else {
+#pragma unroll
+      for (int c = 0; c < kNb; ++c) {
+        w.D[at[s] * kNb + c] = a[s][c];
+        if (c < nb) A[(size_t)(k0 + at[s]) * n + k0 + c] = a[s][c];
+      }
+      w.b[k0 + at[s]] = a[s][kNb];
+    }
+  }
+}
+
+// Factors A (in place; multipliers stored below the diagonal if KEEP) and
+// applies the forward elimination to w.b.  Returns 0 or the failing column
+// + 1 (uniform).
+template <int NT, int RPL, bool KEEP>
+__device__ __attribute__((always_inline)) int lu_factor(double2 *A, int n, const LuLds &w) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c16 = lane & 15, kq = lane >> 4;
+  if (tid == 0) w.info[1] = 0;
+  __syncthreads();
+  for (int k0 = 0; k0 < n; k0 += kNb) {
+    const int nb = std::min(kNb, n - k0), e = k0 + nb, m = n - e;
+    if (nb < kNb)
+      lu_panel<NT, 1, KEEP, false>(A, n, k0, nb, w);
+    else if (RPL == 1 || n - k0 <= NT)
+      lu_panel<NT, 1, KEEP, true>(A, n, k0, nb, w);
+    else
+      lu_panel<NT, RPL, KEEP, true>(A, n, k0, nb, w);
+    __syncthreads();
+    if (w.info[1]) return w.info[1];
+    // columns right of the panel and, with KEEP, the finished ones left of it:
+    // row moves, then U12 = L11^-1 A12 for those to the right (a partial panel
+    // is the last one: nothing to its right)
+    const int nmove = __builtin_amdgcn_readfirstlane(w.info[0]), left = KEEP ? k0 : 0;
+    for (int t = tid; t < m + left; t += NT) {
+      const bool right = t < m;
+      const unsigned col = right ? e + t : t - m;
+      double2 v[kNb], d[kNb];
+#pragma unroll
+      for (int i = 0; i < kNb; ++i)
+        if (i < nb) {
+          const double2 x = (A + (size_t)__builtin_amdgcn_readfirstlane(w.q[i]) * n)[col];
+          v[i].x = x.x;
+          v[i].y = x.y;
+        }
+#pragma unroll
+      for (int i = 0; i < kNb; ++i)
+        if (i < nmove) {
+          const double2 x = (A + (size_t)__builtin_amdgcn_readfirstlane(w.src[i]) * n)[col];
+          d[i].x = x.x;
+          d[i].y = x.y;
+        }
+#pragma unroll
+      for (int i = 0; i < kNb; ++i)
+        if (i < nmove)
+          (A + (size_t)__builtin_amdgcn_readfirstlane(w.dst[i]) * n)[col] =
+              make_double2(d[i].x, d[i].y);
+      if (right) {
+#pragma unroll
+        for (int i = 1; i < kNb; ++i) {
+#pragma unroll
+          for (int j = 0; j < i; ++j) {
+            const double2 l = w.D[i * kNb + j];
+            v[i].x = fma(-l.x, v[j].x, fma(l.y, v[j].y, v[i].x));
+            v[i].y = fma(-l.x, v[j].y, fma(-l.y, v[j].x, v[i].y));
+          }
+          if (i % 3 == 0) __builtin_amdgcn_sched_barrier(0);  // else all of D is read at once
+        }
+#pragma unroll
+        for (int i = 0; i < kNb; ++i) w.U[i * w.mp + t] = v[i];
+      }
+#pragma unroll
+      for (int i = 0; i < kNb; ++i)
+        if (i < nb) (A + (size_t)(k0 + i) * n)[col] = make_double2(v[i].x, v[i].y);
+    }
+    if constexpr (KEEP) {
+      if (tid == NT - 1) {
+        int v[kNb], d[kNb];
+#pragma unroll
+        for (int i = 0; i < kNb; ++i) {
+          if (i < nb) v[i] = w.perm[w.q[i]];
+          if (i < nmove) d[i] = w.perm[w.src[i]];
+        }
+#pragma unroll
+        for (int i = 0; i < kNb; ++i) {
+          if (i < nb) w.perm[k0 + i] = v[i];
+          if (i < nmove) w.perm[w.dst[i]] = d[i];
+        }
+      }
+    }
+    __syncthreads();
+    if (m == 0) break;
+    // trailing update A22 -= L21 U12 in pieces of 16 x 32 dealt to the waves,
+    // each piece's values loaded while the one before is updated
+    const int mt = (m + 15) / 16, mg = (mt + 1) / 2, pieces = mt * mg;
+    double2 *B = A + (size_t)e * n + e;
+    double2 nx[2][4];
+    auto load = [&](int t) {
+      const int i0 = 16 * (t / mg), c0 = 32 * (t % mg) + c16;
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          nx[g][j] = B[(unsigned)(std::min(i0 + kq + 4 * j, m - 1) * n + std::min(c0 + 16 * g, m - 1))];
+    };
+    if (wave < pieces) load(wave);
+    for (int t = wave; t < pieces; t += NT / 64) {
+      const int i0 = 16 * (t / mg), c0 = 32 * (t % mg) + c16;
+      const bool two = c0 - c16 + 16 < m;  // uniform
+      f64x4 cr[2], ci[2];
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          cr[g][j] = nx[g][j].x;
+          ci[g][j] = nx[g][j].y;
+        }
+      if (t + NT / 64 < pieces) load(t + NT / 64);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        if (g == 1 && !two) break;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const double2 l = w.L[(4 * s + kq) * w.mp + i0 + c16];
+          const double2 u = w.U[(4 * s + kq) * w.mp + c0 + 16 * g];
+          cr[g] = mfma64(-l.x, u.x, cr[g]);
+          ci[g] = mfma64(-l.x, u.y, ci[g]);
+          cr[g] = mfma64(l.y, u.y, cr[g]);
+          ci[g] = mfma64(-l.y, u.x, ci[g]);
+        }
+      }
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = i0 + kq + 4 * j, c = c0 + 16 * g;
+          if (r < m && c < m) B[(unsigned)(r * n + c)] = make_double2(cr[g][j], ci[g][j]);
+        }
+    }
+    __syncthreads();
+  }
+  return 0;
+}
+
+// Back substitution U x = b in blocks of 16 rows, x overwrites w.b, down to
+// the block that holds row `stop`.  The first wave solves a block's triangle
+// while every thread's row of the columns above it is on its way.
+template <int NT>
+__device__ __attribute__((always_inline)) void lu_back(const double2 *A, int n, int stop,
+                                                       const LuLds &w) {
+  const int tid = threadIdx.x;
+  for (int k0 = (n - 1) / kNb * kNb; k0 >= 0; k0 -= kNb) {
+    const int nb = std::min(kNb, n - k0);
+    double2 u[kNb], v[kNb];
+    if (tid < 64) {
+      const double2 *row = A + (size_t)(k0 + std::min(tid, nb - 1)) * n + k0;
+#pragma unroll
+      for (int c = 0; c < kNb; ++c) v[c] = row[std::min(c, nb - 1)];
+    }
+    if (tid < k0) {
+      const double2 *row = A + (size_t)tid * n + k0;
+#pragma unroll
+      for (int c = 0; c < kNb; ++c) u[c] = row[std::min(c, nb - 1)];
+    }
+    if (tid < 64) {
+      const int i = std::min(tid, nb - 1);
+      double2 x = w.b[k0 + i];
+      const double2 inv = w.rinv[k0 + i];
+#pragma unroll
+      for (int c = kNb - 1; c >= 0; --c) {
+        if (c >= nb) continue;
+        const double2 y = make_double2(fma(x.x, inv.x, -(x.y * inv.y)), fma(x.x, inv.y, x.y * inv.x));
+        const double2 xc = make_double2(lane_get(y.x, c), lane_get(y.y, c));
+        if (tid < c) {
+          x.x = fma(-v[c].x, xc.x, fma(v[c].y, xc.y, x.x));
+          x.y = fma(-v[c].x, xc.y, fma(-v[c].y, xc.x, x.y));
+        }
+        if (tid == c) w.b[k0 + c] = xc;
+      }
+    }
+    __syncthreads();
+    if (k0 <= stop) break;
+    for (int r = tid; r < k0; r += NT) {
+      if (r != tid) {
+        const double2 *row = A + (size_t)r * n + k0;
+#pragma unroll
+        for (int c = 0; c < kNb; ++c) u[c] = row[std::min(c, nb - 1)];
+      }
+      double2 x = w.b[r];
+#pragma unroll
+      for (int c = 0; c < kNb; ++c) {
+        if (c >= nb) continue;
+        const double2 y = w.b[k0 + c];
+        x.x = fma(-u[c].x, y.x, fma(u[c].y, y.y, x.x));
+        x.y = fma(-u[c].x, y.y, fma(-u[c].y, y.x, x.y));
+      }
+      w.b[r] = x;
+    }
+    __syncthreads();
+  }
+}
+
+// chi_00 of one frequency per workgroup: LU of A_w, right-hand side
+// chi0_w[:, g0]; writes x[g0] and a status per frequency.
+template <int NT, int RPL>
+__global__ void __launch_bounds__(NT, NT == 256 && RPL == 1 ? 2 : 1)
+    k_lu_blocked(double2 *Aall, const double2 *chi0, int n, int g0, double2 *out, int *info) {
+  extern __shared__ double2 lu_sm[];
+  const LuLds w = lu_lds(lu_sm, n);
+  const int f = blockIdx.x, tid = threadIdx.x;
+  double2 *A = Aall + (size_t)f * n * n;
+  const double2 *C = chi0 + (size_t)f * n * n;
+  for (int i = tid; i < n; i += NT) w.b[i] = C[(size_t)i * n + g0];
+  const int fail = lu_factor<NT, RPL, false>(A, n, w);
+  if (!fail) lu_back<NT>(A, n, g0, w);
+  if (tid == 0) {
+    info[f] = fail;
+    out[f] = fail ? make_double2(NAN, NAN) : w.b[g0];
+  }
 }
 
 // LU with partial pivoting (largest |re|+|im|, lowest index on ties) of A_w,
@@ -379,6 +931,34 @@ __global__ void __launch_bounds__(kLuThreads)
   }
 }
 
+
+// The LU solves of n_w frequencies: blocked up to kLuMaxN vectors (one wave
+// where it holds the panel's rows), above it the unblocked kernel.
+int lu_solve(double2 *A, const double2 *chi0, int n, int n_w, int g0, double2 *out, int *info,
+             hipStream_t s) {
+  if (n > kLuMaxN) {
+    hipLaunchKernelGGL(k_lu_solve, dim3(n_w), dim3(kLuThreads), sizeof(double2) * 2 * n, s, A, chi0,
+                       n, g0, out, info);
+    TDX_HIP(hipGetLastError());
+    return TDX_OK;
+  }
+  const size_t lds = lu_lds_bytes(n, false);
+#define TDX_LU(NT, RPL)                                                                        \
+  TDX_HIP(hipFuncSetAttribute((const void *)k_lu_blocked<NT, RPL>,                             \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));          \
+  hipLaunchKernelGGL((k_lu_blocked<NT, RPL>), dim3(n_w), dim3(NT), lds, s, A, chi0, n, g0,     \
+                     out, info)
+  if (n <= 64) {
+    TDX_LU(64, 1);
+  } else if (n <= 256) {
+    TDX_LU(256, 1);
+  } else {
+    TDX_LU(256, 2);
+  }
+#undef TDX_LU
+  TDX_HIP(hipGetLastError());
+  return TDX_OK;
+}
 
 // Reverse mode of the Dyson step.  chi_00 = e^T A^{-1} chi0 e with
 // A = 1 - chi0 K (e = e_g0), so d chi_00 = a^T d chi0 b with
@@ -548,6 +1128,145 @@ __global__ void __launch_bounds__(kLuThreads)
     const double2 a = y[i];  // u = cbar conj(a)
     uw[i] = make_double2(cb.x * a.x + cb.y * a.y, cb.y * a.x - cb.x * a.y);
   }
+}
+
+// k_lu_vjp on the blocked factorisation (bases up to kLuMaxN vectors).
+template <int NT, int RPL>
+__global__ void __launch_bounds__(NT, NT == 256 && RPL == 1 ? 2 : 1)
+    k_lu_vjp_blocked(double2 *Aall, const double2 *chi0, const double2 *K, int n, int g0,
+                     const double2 *cbar, double2 *u, double2 *v, int *info, double2 *xout) {
+  extern __shared__ double2 lu_sm[];
+  const LuLds w = lu_lds(lu_sm, n);
+  const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double2 *A = Aall + (size_t)f * n * n;
+  const double2 *C = chi0 + (size_t)f * n * n;
+  double2 *uw = u + (size_t)f * n, *vw = v + (size_t)f * n;
+  for (int i = tid; i < n; i += NT) {
+    w.b[i] = C[(size_t)i * n + g0];
+    w.perm[i] = i;
+  }
+  const int fail = lu_factor<NT, RPL, true>(A, n, w);
+  if (tid == 0) info[f] = fail;
+  if (fail) {
+    for (int i = tid; i < n; i += NT) uw[i] = vw[i] = make_double2(NAN, NAN);
+    return;
+  }
+  lu_back<NT>(A, n, 0, w);
+  __syncthreads();
+  if (xout)
+    for (int i = tid; i < n; i += NT) xout[(size_t)f * n + i] = w.b[i];
+  // v = e + K x, a row per wave
+  for (int i = wave; i < n; i += NT / 64) {
+    double re = 0.0, im = 0.0;
+    for (int j = lane; j < n; j += 64) {
+      const double2 a = K[(size_t)i * n + j], b = w.b[j];
+      re = fma(a.x, b.x, fma(-a.y, b.y, re));
+      im = fma(a.x, b.y, fma(a.y, b.x, im));
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      re += __shfl_xor(re, o);
+      im += __shfl_xor(im, o);
+    }
+    if (lane == 0) vw[i] = make_double2(re + (i == g0 ? 1.0 : 0.0), im);
+  }
+  double2 *y = w.L;  // the panel operands are done with
+  for (int i = tid; i < n; i += NT) y[i] = make_double2(i == g0 ? 1.0 : 0.0, 0.0);
+  __syncthreads();
+  // r[c] -= sum_i M[k0 + i][c] y[k0 + i] over the columns c0 <= c < c1
+  auto apply = [&](int k0, int nb, int c0, int c1) {
+    for (int c = c0 + tid; c < c1; c += NT) {
+      double2 x = y[c];
+#pragma unroll
+      for (int i = 0; i < kNb; ++i) {
+        if (i >= nb) continue;
+        const double2 a = A[(size_t)(k0 + i) * n + c], b = y[k0 + i];
+        x.x = fma(-a.x, b.x, fma(a.y, b.y, x.x));
+        x.y = fma(-a.x, b.y, fma(-a.y, b.x, x.y));
+      }
+      y[c] = x;
+    }
+    __syncthreads();
+  };
+  // U^T y = e: forward, from the block of g0 (y is zero before it)
+  for (int k0 = g0 / kNb * kNb; k0 < n; k0 += kNb) {
+    const int nb = std::min(kNb, n - k0);
+    if (tid < 64) {
+      const int j = std::min(tid, nb - 1);
+      double2 m[kNb], x = y[k0 + j];
+#pragma unroll
+      for (int i = 0; i < kNb; ++i) m[i] = A[(size_t)(k0 + std::min(i, nb - 1)) * n + k0 + j];
+      const double2 inv = w.rinv[k0 + j];
+#pragma unroll
+      for (int i = 0; i < kNb; ++i) {
+        if (i >= nb) continue;
+        const double2 z = make_double2(fma(x.x, inv.x, -(x.y * inv.y)), fma(x.x, inv.y, x.y * inv.x));
+        const double2 yi = make_double2(lane_get(z.x, i), lane_get(z.y, i));
+        if (tid > i) {
+          x.x = fma(-m[i].x, yi.x, fma(m[i].y, yi.y, x.x));
+          x.y = fma(-m[i].x, yi.y, fma(-m[i].y, yi.x, x.y));
+        }
+        if (tid == i) y[k0 + i] = yi;
+      }
+    }
+    __syncthreads();
+    apply(k0, nb, k0 + nb, n);
+  }
+  // L^T z = y: backward, unit diagonal
+  for (int k0 = (n - 1) / kNb * kNb; k0 >= 0; k0 -= kNb) {
+    const int nb = std::min(kNb, n - k0);
+    if (tid < 64) {
+      const int j = std::min(tid, nb - 1);
+      double2 m[kNb], x = y[k0 + j];
+#pragma unroll
+      for (int i = 0; i < kNb; ++i) m[i] = A[(size_t)(k0 + std::min(i, nb - 1)) * n + k0 + j];
+#pragma unroll
+      for (int i = kNb - 1; i >= 0; --i) {
+        if (i >= nb) continue;
+        const double2 zi = make_double2(lane_get(x.x, i), lane_get(x.y, i));
+        if (tid < i) {
+          x.x = fma(-m[i].x, zi.x, fma(m[i].y, zi.y, x.x));
+          x.y = fma(-m[i].x, zi.y, fma(-m[i].y, zi.x, x.y));
+        }
+        if (tid == i) y[k0 + i] = zi;
+      }
+    }
+    __syncthreads();
+    apply(k0, nb, 0, k0);
+  }
+  // a = P^T z, u = cbar conj(a)
+  const double2 cb = cbar[f];
+  for (int i = tid; i < n; i += NT) {
+    const double2 a = y[i];
+    uw[w.perm[i]] = make_double2(cb.x * a.x + cb.y * a.y, cb.y * a.x - cb.x * a.y);
+  }
+}
+
+int lu_vjp(double2 *A, const double2 *chi0, const double2 *K, int n, int n_w, int g0,
+           const double2 *cbar, double2 *u, double2 *v, int *info, double2 *xout, hipStream_t s) {
+  if (n > kLuMaxN) {
+    hipLaunchKernelGGL(k_lu_vjp, dim3(n_w), dim3(kLuThreads),
+                       (sizeof(double2) * 2 + sizeof(int)) * (size_t)n, s, A, chi0, K, n, g0, cbar,
+                       u, v, info, xout);
+    TDX_HIP(hipGetLastError());
+    return TDX_OK;
+  }
+  const size_t lds = lu_lds_bytes(n, true);
+#define TDX_LU(NT, RPL)                                                                          \
+  TDX_HIP(hipFuncSetAttribute((const void *)k_lu_vjp_blocked<NT, RPL>,                           \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));            \
+  hipLaunchKernelGGL((k_lu_vjp_blocked<NT, RPL>), dim3(n_w), dim3(NT), lds, s, A, chi0, K, n, g0, \
+                     cbar, u, v, info, xout)
+  if (n <= 64) {
+    TDX_LU(64, 1);
+  } else if (n <= 256) {
+    TDX_LU(256, 1);
+  } else {
+    TDX_LU(256, 2);
+  }
+#undef TDX_LU
+  TDX_HIP(hipGetLastError());
+  return TDX_OK;
 }
 
 // ------------------------------------------------- ALDA kernel adjoint
@@ -792,12 +1511,8 @@ int tdx_dyson_noalloc(tdx_ctx *ctx, const double *chi0, const double *K, int n_g
   for (int w0 = 0; w0 < n_w; w0 += (int)cw) {
     const int nw = (int)std::min<long long>(cw, n_w - w0);
     const double2 *c = (const double2 *)chi0 + (size_t)w0 * n2;
-    dim3 g((n_g + kT - 1) / kT, (n_g + kT - 1) / kT, nw);
-    hipLaunchKernelGGL(k_one_minus, g, dim3(kT, kT), 0, s, c, (const double2 *)K, n_g, A);
-    TDX_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_lu_solve, dim3(nw), dim3(kLuThreads), sizeof(double2) * 2 * n_g, s, A,
-                       c, n_g, i_g0, (double2 *)chi00 + w0, info);
-    TDX_HIP(hipGetLastError());
+    TDX_TRY(one_minus(c, (const double2 *)K, n_g, nw, A, s));
+    TDX_TRY(lu_solve(A, c, n_g, nw, i_g0, (double2 *)chi00 + w0, info, s));
     hipLaunchKernelGGL(k_fold_status, dim3(1), dim3(256), 0, s, info, nw, w0, status);
     TDX_HIP(hipGetLastError());
   }
@@ -923,14 +1638,8 @@ int tdx_dyson_async(tdx_ctx *ctx, const double *chi0, const double *K, int n_g, 
   TDX_REQUIRE(n_w <= 65535, TDX_ERR_SHAPE, "n_w %d above 65535", n_w);
   hipStream_t s = as_stream(stream);
   double2 *A = (double2 *)work;
-  dim3 g((n_g + kT - 1) / kT, (n_g + kT - 1) / kT, n_w);
-  hipLaunchKernelGGL(k_one_minus, g, dim3(kT, kT), 0, s, (const double2 *)chi0,
-                     (const double2 *)K, n_g, A);
-  TDX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_lu_solve, dim3(n_w), dim3(kLuThreads), sizeof(double2) * 2 * n_g, s, A,
-                     (const double2 *)chi0, n_g, i_g0, (double2 *)chi00, info);
-  TDX_HIP(hipGetLastError());
-  return TDX_OK;
+  TDX_TRY(one_minus((const double2 *)chi0, (const double2 *)K, n_g, n_w, A, s));
+  return lu_solve(A, (const double2 *)chi0, n_g, n_w, i_g0, (double2 *)chi00, info, s);
 }
 
 int tdx_dyson(tdx_ctx *ctx, const double *chi0, const double *K, int n_g, int n_w, int i_g0,
@@ -966,15 +1675,9 @@ int tdx_dyson_vjp(tdx_ctx *ctx, const double *chi0, const double *K, int n_g, in
   TDX_REQUIRE(n_w <= 65535, TDX_ERR_SHAPE, "n_w %d above 65535", n_w);
   hipStream_t s = as_stream(stream);
   double2 *A = (double2 *)work;
-  dim3 g((n_g + kT - 1) / kT, (n_g + kT - 1) / kT, n_w);
-  hipLaunchKernelGGL(k_one_minus, g, dim3(kT, kT), 0, s, (const double2 *)chi0,
-                     (const double2 *)K, n_g, A);
-  TDX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_lu_vjp, dim3(n_w), dim3(kLuThreads), lds, s, A, (const double2 *)chi0,
-                     (const double2 *)K, n_g, i_g0, (const double2 *)chi00_bar, (double2 *)u,
-                     (double2 *)v, info, (double2 *)nullptr);
-  TDX_HIP(hipGetLastError());
-  return TDX_OK;
+  TDX_TRY(one_minus((const double2 *)chi0, (const double2 *)K, n_g, n_w, A, s));
+  return lu_vjp(A, (const double2 *)chi0, (const double2 *)K, n_g, n_w, i_g0,
+                (const double2 *)chi00_bar, (double2 *)u, (double2 *)v, info, nullptr, s);
 }
 
 int tdx_dyson_kernel_vjp(tdx_ctx *ctx, const double *chi0, const double *K, int n_g, int n_w,
@@ -996,13 +1699,9 @@ int tdx_dyson_kernel_vjp(tdx_ctx *ctx, const double *chi0, const double *K, int 
   double2 *u = (double2 *)((char *)w + mat), *v = u + (size_t)n_w * n_g;
   double2 *x = v + (size_t)n_w * n_g, *p = x + (size_t)n_w * n_g;
   int *info = (int *)(p + (size_t)n_w * n_g), *status = info + n_w;
-  dim3 g((n_g + kT - 1) / kT, (n_g + kT - 1) / kT, n_w);
-  hipLaunchKernelGGL(k_one_minus, g, dim3(kT, kT), 0, s, (const double2 *)chi0,
-                     (const double2 *)K, n_g, A);
-  TDX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_lu_vjp, dim3(n_w), dim3(kLuThreads), lds, s, A, (const double2 *)chi0,
-                     (const double2 *)K, n_g, i_g0, (const double2 *)chi00_bar, u, v, info, x);
-  TDX_HIP(hipGetLastError());
+  TDX_TRY(one_minus((const double2 *)chi0, (const double2 *)K, n_g, n_w, A, s));
+  TDX_TRY(lu_vjp(A, (const double2 *)chi0, (const double2 *)K, n_g, n_w, i_g0,
+                 (const double2 *)chi00_bar, u, v, info, x, s));
   hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, status);
   hipLaunchKernelGGL(k_fold_status, dim3(1), dim3(256), 0, s, info, n_w, 0, status);
   TDX_HIP(hipGetLastError());
