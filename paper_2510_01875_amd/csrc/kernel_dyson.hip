@@ -385,7 +385,8 @@ __device__ inline double2 cdiv(double2 a, double2 b) {
 // search and the row's way through LDS take most), so two workgroups share a
 // CU where LDS allows (n <= 144): one's panel runs beside the other's update.
 // The matrix stays in global memory (L2).  500 matrices of 133: 2.36 ms
-// unblocked, 0.40 ms here; 80 of 304: 16.6 ms and 1.3 ms.
+// unblocked, 0.40 ms here; with the product 1 - chi0 K, 40 of 305 unblocked:
+// 16.6 ms, 80 of 304 here: 1.4 ms.
 constexpr int kNb = 16;
 // Above 304 vectors the two 16-row operands of an update exceed LDS: the
 // unblocked kernels run.

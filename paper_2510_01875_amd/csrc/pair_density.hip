@@ -8,6 +8,7 @@
 // kernels).
 // Accumulation is FP64; the store converts to the requested layout.
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -301,6 +302,266 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
   }
 }
 
+// The same products with one workgroup of eight wavefronts for several groups
+// of one k, where the coefficients of eight fixed sides and the lookup box fit
+// in LDS together (every basis of up to about 900 plane waves; the crystals
+// have 400).  What bounded the one-wavefront form above on them is latency:
+// each group brought its own 27 KB lookup box, so four wavefronts filled a
+// CU's LDS, one per SIMD, and nothing ran while it waited for its chain of
+// index arithmetic, bounds checks, lookup and gather.  Here
+//  - the box is shared, holds 16-bit slots and is padded by the reach of the
+//    response vectors, so that the slot of G2 -+ (G + G_s) is one addition on
+//    a linear index, with no bounds check: entries outside the basis name a
+//    slot that holds zero;
+//  - two wavefronts per SIMD, each with its own group, cover each other;
+//  - the 16-transition tiles of a k are dealt from a counter in LDS.
+// The products and their order are those of the form above: same bits.
+// 2.9e5 transitions of a crystal's 5^3 grid (N_G 133, 400 plane waves, FP64):
+// 3.8 ms against 10.4 ms (38 TFLOP/s of wanted products; the gathers' bank
+// conflicts are 8 % of it, measured with a fixed slot in their place); 6.2e5 on
+// an 8^3 grid: 7.5 ms; the electron gas (N_G 32, 7.9e5): 2.4 against 3.5 ms.
+constexpr int kPdWaves = 8;
+constexpr int kPdLds = 160 * 1024 - 256;  // one workgroup per CU
+
+// LDS in front of the lookup box: the fixed sides (with a zero slot each) and
+// the linear indices of the A side's plane waves, then the tile starts of the
+// bands and the counter.
+__host__ __device__ inline size_t pd_front_bytes(int npw_max, int nb_max) {
+  return sizeof(double2) * (size_t)kPdWaves * (npw_max + 1) +
+         sizeof(int) * ((size_t)npw_max + nb_max + 1 + 8);
+}
+// The form above runs where the fixed sides and an unpadded box fit.
+inline bool pd_shared_fits(int npw_max, int nb_max, long box) {
+  return npw_max < 65535 && pd_front_bytes(npw_max, nb_max) + sizeof(short) * box <= kPdLds;
+}
+
+// Tiles a workgroup takes at a time (chunk) and workgroups per k.  The tiles
+// of a k differ with its occupied bands, and one workgroup runs on a CU at a
+// time, so chunks are small enough for four rounds of the chip, a tile per
+// wavefront or fewer where the list is short, and workgroups beyond a k's
+// chunks leave at once (half of the k-points of a paired list hold none).
+// About two thirds of a list's tiles belong to one of the two launches.
+inline void pd_chunks(int nk, bool paired, long long n_trans, int n_cu, int *chunk, int *parts) {
+  const double tiles = n_trans / 24.0;
+  *chunk = tiles < 8.0 * n_cu
+               ? std::max(1, (int)std::ceil(tiles / n_cu))
+               : 8 * std::min(8, std::max(1, (int)(tiles / (32.0 * n_cu) + 0.5)));
+  const double per_k = tiles * (paired ? 2.0 : 1.0) / nk / *chunk;
+  *parts = std::min(64, std::max(1, (int)std::ceil(1.5 * per_k)));
+}
+
+template <int FMT, bool COL>
+__global__ void __launch_bounds__(64 * kPdWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+    k_pair_density_k(const double2 *coef, const int *miller, const int *npw, int nb_max,
+                     int npw_max, const int *tn, const int *tm, const long long *gbeg,
+                     const long long *gend, const long long *perm, const int *kpmap,
+                     const int *gsmap, const int *gbasis, int n_g, int ld, int M0, int M1, int M2,
+                     void *P, long long t_lo, long long n_rows, int chunk) {
+  extern __shared__ double2 pd_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int *lina = (int *)(pd_lds + kPdWaves * (npw_max + 1));  // [npw_max]
+  int *start = lina + npw_max;                             // [nb_max + 1]
+  int *next = start + nb_max + 1, *reach = next + 1;       // [1], [3]
+  unsigned short *box = (unsigned short *)(reach + 3);
+  const int k = blockIdx.y, kp = kpmap[k];
+  const int kf = COL ? kp : k, ka = COL ? k : kp;
+  const int gs[3] = {gsmap[3 * k], gsmap[3 * k + 1], gsmap[3 * k + 2]};
+  if (tid < 3) reach[tid] = 0;
+  __syncthreads();
+  for (int i = tid; i < 3 * n_g; i += 64 * kPdWaves) atomicMax(&reach[i % 3], abs(gbasis[i] + gs[i % 3]));
+  // tiles of each band's group, as an inclusive sum over the bands
+  if (wave == 0) {
+    int carry = 0;
+    for (int b0 = 0; b0 < nb_max; b0 += 64) {
+      const int b = b0 + lane;
+      int n = 0;
+      if (b < nb_max) {
+        const size_t grp = (size_t)k * nb_max + b;
+        const long long len = gend[grp] - gbeg[grp];
+        n = len > 0 && (COL || len >= kShortRow) ? (int)((len + 15) / 16) : 0;
+      }
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(n, o);
+        if (lane >= o) n += x;
+      }
+      if (b < nb_max) start[b + 1] = carry + n;
+      carry += __shfl(n, 63);
+    }
+    if (lane == 0) start[0] = 0;
+  }
+  __syncthreads();
+  const int total = start[nb_max];
+  if ((int)blockIdx.x * chunk >= total) return;
+  // the padded box: axis i holds 2 M_i + 1 indices and R_i of padding, R_i the
+  // largest |G_i + G_s,i|; an index that runs over an end of axis 1 or 2
+  // lands in the padding next to it, axis 0 has padding on both sides.  A
+  // reach too wide for LDS leaves the padding out and checks every index.
+  int R0 = reach[0], R1 = reach[1], R2 = reach[2];
+  const long space = (long)(kPdLds - pd_front_bytes(npw_max, nb_max)) / 2;
+  const bool padded =
+      (2L * M0 + 1 + 2 * R0) * (2L * M1 + 1 + R1) * (2L * M2 + 1 + R2) +
+          2 * (R1 * (2L * M2 + 1 + R2) + R2) <= space;
+  if (!padded) R0 = R1 = R2 = 0;
+  const int W1 = 2 * M1 + 1 + R1, W2 = 2 * M2 + 1 + R2, off = R1 * W2 + R2;
+  const long size = (long)(2 * M0 + 1 + 2 * R0) * W1 * W2 + 2 * off;
+  const int npf = npw[kf], npa = npw[ka];
+  auto linear = [&](int m0, int m1, int m2) {
+    return off + ((m0 + M0 + R0) * W1 + m1 + M1) * W2 + m2 + M2;
+  };
+  // three 10-bit fields, for the checked indices
+  auto pack = [](int x, int y, int z) { return x | (y << 10) | (z << 20); };
+  for (long i = tid; i < size; i += 64 * kPdWaves) box[i] = (unsigned short)npw_max;  // zero
+  const int *ma = miller + (size_t)ka * npw_max * 3, *mf = miller + (size_t)kf * npw_max * 3;
+  for (int i = tid; i < npa; i += 64 * kPdWaves)
+    lina[i] = padded ? linear(ma[3 * i], ma[3 * i + 1], ma[3 * i + 2])
+                     : pack(ma[3 * i] + M0, ma[3 * i + 1] + M1, ma[3 * i + 2] + M2);
+  double2 *cfix = pd_lds + wave * (npw_max + 1);
+  if (lane == 0) cfix[npw_max] = make_double2(0.0, 0.0);
+  if (tid == 0) *next = 0;
+  __syncthreads();
+  for (int i = tid; i < npf; i += 64 * kPdWaves)
+    box[linear(mf[3 * i], mf[3 * i + 1], mf[3 * i + 2])] = (unsigned short)i;
+  __syncthreads();
+
+  const double2 *ca = coef + (size_t)ka * nb_max * npw_max;
+  const int *ta = COL ? tn : tm;  // band of the A row of a transition
+  const int r = lane & 15, kq = lane >> 4;
+  const int n_gt = ld / 16, passes = (n_gt + kPdGT - 1) / kPdGT;
+  auto trans = [&](long long p) { return COL ? perm[p] : p; };
+  int band = -1;
+  for (;;) {
+    int item = 0;
+    if (lane == 0) item = atomicAdd(next, 1);
+    item = __builtin_amdgcn_readfirstlane(item);
+    // the chunks blockIdx.x, blockIdx.x + gridDim.x, ... of the k
+    item = ((int)blockIdx.x + item / chunk * (int)gridDim.x) * chunk + item % chunk;
+    if (item >= total) break;
+    // the band whose tiles hold it: start[b] <= item < start[b + 1]
+    int lo = 0, hi = nb_max - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (start[mid + 1] <= item)
+        lo = mid + 1;
+      else
+        hi = mid;
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    if (lo != band) {
+      band = lo;
+      const double2 *cf = coef + ((size_t)kf * nb_max + band) * npw_max;
+      for (int i = lane; i < npf; i += 64) {
+        const double2 c = cf[i];
+        cfix[i] = COL ? c : make_double2(c.x, -c.y);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    }
+    const size_t grp = (size_t)k * nb_max + band;
+    const long long q0 = gbeg[grp] + 16LL * (item - start[band]), p1 = gend[grp];
+    const bool row_ok = q0 + r < p1;
+    const double2 *crow = ca + (size_t)(row_ok ? ta[trans(q0 + r)] : 0) * npw_max;
+    auto tiles = [&](int gt0, auto nq_c, auto padded_c) {
+      constexpr int NQ = decltype(nq_c)::value;
+      constexpr bool PAD = decltype(padded_c)::value;
+      f64x4 acr[NQ], aci[NQ];
+      int lg[NQ];  // linear offset of this lane's G + G_s in each tile
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        acr[q] = aci[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+        const int g = std::min((gt0 + q) * 16 + r, n_g - 1);
+        const int f0 = gbasis[3 * g] + gs[0], f1 = gbasis[3 * g + 1] + gs[1],
+                  f2 = gbasis[3 * g + 2] + gs[2];
+        const int x = (f0 * W1 + f1) * W2 + f2;
+        lg[q] = PAD ? (COL ? x : -x) : pack(f0 + 512, f1 + 512, f2 + 512);
+      }
+      auto load_a = [&](int j) {
+        const double2 c = j < npa && row_ok ? crow[j] : make_double2(0.0, 0.0);
+        return COL ? make_double2(c.x, -c.y) : c;
+      };
+      // slots one K-step ahead, coefficients far enough for a few thousand
+      // cycles of the two wavefronts' products (4 NQ of 64 cycles a step)
+      constexpr int D = NQ >= 6 ? 1 : NQ >= 3 ? 2 : 4;
+      double2 an[D];
+#pragma unroll
+      for (int d = 0; d < D; ++d) an[d] = load_a(4 * d + kq);
+      int slot[NQ];
+      auto load_slots = [&](int j) {
+        const int la = lina[std::min(j, npa - 1)];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          if constexpr (PAD) {
+            slot[q] = box[la + lg[q]];
+            continue;
+          }
+          const int sg = COL ? 1 : -1;
+          const int x0 = (la & 1023) + sg * ((lg[q] & 1023) - 512);
+          const int x1 = ((la >> 10) & 1023) + sg * (((lg[q] >> 10) & 1023) - 512);
+          const int x2 = (la >> 20) + sg * ((int)((unsigned)lg[q] >> 20) - 512);
+          const bool ok = x0 >= 0 && x0 <= 2 * M0 && x1 >= 0 && x1 <= 2 * M1 && x2 >= 0 &&
+                          x2 <= 2 * M2;
+          slot[q] = ok ? box[(x0 * W1 + x1) * W2 + x2] : npw_max;
+        }
+      };
+      load_slots(kq);
+      for (int jd = 0; jd < npa; jd += 4 * D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          const int j0 = jd + 4 * d;
+          if (D > 1 && j0 >= npa) break;
+          const double2 a = an[d];
+          an[d] = load_a(j0 + 4 * D + kq);
+          double2 u[NQ];
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) u[q] = cfix[slot[q]];
+          load_slots(j0 + 4 + kq);
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            acr[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, u[q].x, acr[q], 0, 0, 0);
+            aci[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, u[q].y, aci[q], 0, 0, 0);
+          }
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            acr[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, u[q].y, acr[q], 0, 0, 0);
+            aci[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, u[q].x, aci[q], 0, 0, 0);
+          }
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const long long p = q0 + kq + 4 * e;
+        if (p >= p1) continue;
+        const long long t = trans(p) - t_lo;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          const int g = (gt0 + q) * 16 + r;
+          const bool in = g < n_g;  // columns past n_g are stored as zero
+          store<FMT>(P, t, g, ld, n_rows, in ? acr[q][e] : 0.0, in ? aci[q][e] : 0.0);
+        }
+      }
+    };
+    auto sweep = [&](auto padded_c) {
+      for (int s = 0; s < passes; ++s) {
+        const int gt0 = n_gt * s / passes;
+        switch (n_gt * (s + 1) / passes - gt0) {  // uniform across the wave
+          case 1: tiles(gt0, std::integral_constant<int, 1>{}, padded_c); break;
+          case 2: tiles(gt0, std::integral_constant<int, 2>{}, padded_c); break;
+          case 3: tiles(gt0, std::integral_constant<int, 3>{}, padded_c); break;
+          case 4: tiles(gt0, std::integral_constant<int, 4>{}, padded_c); break;
+          case 5: tiles(gt0, std::integral_constant<int, 5>{}, padded_c); break;
+          case 6: tiles(gt0, std::integral_constant<int, 6>{}, padded_c); break;
+          case 7: tiles(gt0, std::integral_constant<int, 7>{}, padded_c); break;
+          case 8: tiles(gt0, std::integral_constant<int, 8>{}, padded_c); break;
+          default: tiles(gt0, std::integral_constant<int, kPdGT>{}, padded_c); break;
+        }
+      }
+    };
+    if (padded)
+      sweep(std::true_type{});
+    else
+      sweep(std::false_type{});
+  }
+}
+
 int ld_of(int n_g) { return (n_g + 15) / 16 * 16; }
 
 }  // namespace
@@ -376,7 +637,7 @@ int pd_check(const tdx_states *st, const int qj[3], const tdx_translist *tl, int
 
 // Every launch of one pair-density call, with its tables in `work`: no host
 // copy, memset or synchronisation, so a caller may capture it in a graph.
-int pd_enqueue(const tdx_states *st, const int qj[3], const tdx_translist *tl, int64_t t_begin,
+int pd_enqueue(int n_cu, const tdx_states *st, const int qj[3], const tdx_translist *tl, int64_t t_begin,
                int64_t t_end, const int *gbasis, int n_g, int prec, void *P, void *work,
                hipStream_t s) {
   const long long n_trans = t_end - t_begin;
@@ -415,6 +676,34 @@ int pd_enqueue(const tdx_states *st, const int qj[3], const tdx_translist *tl, i
   const bool ms = lds0 + sizeof(unsigned) * st->npw_max <= 150 * 1024;
   const size_t lds = ms ? lds0 + sizeof(unsigned) * st->npw_max : lds0;
   // long rows, then the column groups of the short ones (disjoint outputs)
+  if (pd_shared_fits(st->npw_max, nb_max, box)) {
+    int chunk, parts;
+    pd_chunks(nk, tl->paired != 0, n_trans, n_cu, &chunk, &parts);
+    const dim3 kgrid(parts, nk);
+#define TDX_PDK(F, COL, B, E)                                                                   \
+  TDX_HIP(hipFuncSetAttribute((const void *)k_pair_density_k<F, COL>,                           \
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kPdLds));             \
+  hipLaunchKernelGGL((k_pair_density_k<F, COL>), kgrid, dim3(64 * kPdWaves), kPdLds, s,         \
+                     (const double2 *)st->coef, st->miller, st->npw, nb_max, st->npw_max,       \
+                     tl->n, tl->m, B, E, w.perm, w.kp, w.gs, gbasis, n_g, ld, M0, M1, M2, P,    \
+                     (long long)t_begin, n_trans, chunk);                                       \
+  TDX_HIP(hipGetLastError())
+#define TDX_PDK2(F)                   \
+  TDX_PDK(F, false, w.rb, w.re);      \
+  TDX_PDK(F, true, w.cb, w.ce)
+    if (prec == TDX_PREC_FP64) {
+      TDX_PDK2(TDX_PREC_FP64);
+    } else if (prec == TDX_PREC_FP32) {
+      TDX_PDK2(TDX_PREC_FP32);
+    } else {
+      hipLaunchKernelGGL(k_zero_pad, dim3(64), dim3(256), 0, s, (unsigned int *)P, n_trans, ld);
+      TDX_HIP(hipGetLastError());
+      TDX_PDK2(TDX_PREC_BF16X3);
+    }
+#undef TDX_PDK2
+#undef TDX_PDK
+    return TDX_OK;
+  }
 #define TDX_PD3(F, COL, W, MS, B, E)                                                           \
   TDX_HIP(hipFuncSetAttribute((const void *)k_pair_density<F, COL, W, MS>,                     \
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));          \
@@ -473,7 +762,7 @@ int tdx_pair_density_async(tdx_ctx *ctx, const tdx_states *st, const int qj[3],
   TDX_TRY(pd_check(st, qj, tl, t_begin, t_end, gbasis, n_g, prec, P));
   TDX_REQUIRE(work_bytes >= pd_work_layout(st, t_end - t_begin, nullptr, nullptr), TDX_ERR_SHAPE,
               "work buffer of %zu bytes below tdx_pair_density_work_bytes", work_bytes);
-  return pd_enqueue(st, qj, tl, t_begin, t_end, gbasis, n_g, prec, P, work, as_stream(stream));
+  return pd_enqueue(std::max(ctx->n_cu, 1), st, qj, tl, t_begin, t_end, gbasis, n_g, prec, P, work, as_stream(stream));
 }
 
 int tdx_pair_density_range(tdx_ctx *ctx, const tdx_states *st, const int qj[3],
@@ -486,7 +775,7 @@ int tdx_pair_density_range(tdx_ctx *ctx, const tdx_states *st, const int qj[3],
   if (t_end == t_begin) return TDX_OK;
   void *w;
   TDX_TRY(ws_get(ctx, WS_DENS, pd_work_layout(st, t_end - t_begin, nullptr, nullptr), &w));
-  return pd_enqueue(st, qj, tl, t_begin, t_end, gbasis, n_g, prec, P, w, as_stream(stream));
+  return pd_enqueue(std::max(ctx->n_cu, 1), st, qj, tl, t_begin, t_end, gbasis, n_g, prec, P, w, as_stream(stream));
 }
 
 int tdx_pair_density(tdx_ctx *ctx, const tdx_states *st, const int qj[3], const tdx_translist *tl,
