@@ -471,6 +471,11 @@ int tdx_itcf(tdx_ctx *ctx, const double *S, const double *omega, int n_w,
              double beta, const double *tau, int n_tau, double *F,
              tdx_stream stream);
 
+/* tdx_itcf for the n_set rows of S [n_set][n_w], F [n_set][n_tau], in one
+ * launch: each row as tdx_itcf gives it (bitwise).  n_set = 0 writes nothing. */
+int tdx_itcf_sets(tdx_ctx *ctx, const double *S, int n_set, const double *omega, int n_w,
+                  double beta, const double *tau, int n_tau, double *F, tdx_stream stream);
+
 /* ------------------------------------------------------------------ */
 /* The eta-convergence test in imaginary time (Sec. 2, Eq. 2, Fig. 2)  */
 /* ------------------------------------------------------------------ */

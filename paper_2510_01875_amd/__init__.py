@@ -157,6 +157,8 @@ _dyson_async = _sig("tdx_dyson_async", [C.c_void_p, C.c_void_p, C.c_void_p, C.c_
                                         C.c_int, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p])
 _itcf = _sig("tdx_itcf", [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_double, C.c_void_p,
                           C.c_int, C.c_void_p, C.c_void_p])
+_itcf_sets = _sig("tdx_itcf_sets", [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_int,
+                                    C.c_double, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p])
 
 _metrics = _sig("tdx_itcf_metrics", [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_int,
                                      C.c_double, C.c_double, C.c_void_p, C.c_void_p])
@@ -220,7 +222,7 @@ EXPORTED = ["tdx_create", "tdx_destroy", "tdx_last_error", "tdx_abi_version",
             "tdx_chi0", "tdx_kernel_matrix",
             "tdx_xc_kernel_grid", "tdx_kernel_matrix_from_grid",
             "tdx_dyson", "tdx_dyson_noalloc", "tdx_dyson_noalloc_max_bytes", "tdx_dsf",
-            "tdx_itcf", "tdx_itcf_metrics", "tdx_eta_reference", "tdx_dielectric", "tdx_sg_filter", "tdx_derivative_psd", "tdx_sg_scores", "tdx_residual_itcf", "tdx_sg_select", "tdx_kg_dsf", "tdx_kg_work_bytes", "tdx_kg_conductivity", "tdx_chi0_plan_create", "tdx_chi0_plan_launch",
+            "tdx_itcf", "tdx_itcf_sets", "tdx_itcf_metrics", "tdx_eta_reference", "tdx_dielectric", "tdx_sg_filter", "tdx_derivative_psd", "tdx_sg_scores", "tdx_residual_itcf", "tdx_sg_select", "tdx_kg_dsf", "tdx_kg_work_bytes", "tdx_kg_conductivity", "tdx_chi0_plan_create", "tdx_chi0_plan_launch",
             "tdx_chi0_plan_destroy", "tdx_chi0_batched", "tdx_chi0_variants",
             "tdx_chi0_set_config", "tdx_chi0_get_config", "tdx_chi0_set_slice_length", "tdx_chi0_bf16x3_slicing", "tdx_autotune_chi0", "tdx_tune_save",
             "tdx_tune_load", "tdx_dyson_work_bytes", "tdx_dyson_async", "tdx_itcf_vjp",
@@ -240,13 +242,12 @@ def abi_version():
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
-def _ptr(t: torch.Tensor):
+def _ptr(t: torch.Tensor) -> int:
     assert t.is_cuda and t.is_contiguous()
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 # ---------------------------------------------------------------- context
@@ -573,6 +574,17 @@ def itcf(ctx: Context, S: torch.Tensor, omega: torch.Tensor, beta: float, tau: t
     return F
 
 
+def itcf_sets(ctx: Context, S: torch.Tensor, omega: torch.Tensor, beta: float, tau: torch.Tensor,
+              stream=None) -> torch.Tensor:
+    """F [n_set][n_tau] of the rows of S [n_set][n_w], each as itcf gives it, in
+    one launch."""
+    n_set = S.shape[0]
+    F = torch.empty((n_set, tau.shape[0]), dtype=torch.float64, device=tau.device)
+    check(_itcf_sets(ctx.handle, _ptr(S), n_set, _ptr(omega), omega.shape[0], beta, _ptr(tau),
+                     tau.shape[0], _ptr(F), _stream(stream)))
+    return F
+
+
 # ------------------------------------------------ eta test in imaginary time
 METRICS = ("F(beta/2)", "int_0^beta F", "F~(beta/2)", "int_0^beta F~", "chi(q)")
 
@@ -655,9 +667,11 @@ def derivative_psd(ctx: Context, S: torch.Tensor, omega: torch.Tensor, nu: torch
 
 
 def sg_scores(ctx: Context, S: torch.Tensor, Sp: torch.Tensor, hdiag: torch.Tensor,
-              omega: torch.Tensor, nu: torch.Tensor, stream=None) -> torch.Tensor:
+              omega: torch.Tensor, nu: torch.Tensor, stream=None,
+              out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """[n_filt][5] scores (SG_SCORES) of a filter bank (Sec. 3; tdx.h)."""
-    out = torch.empty((Sp.shape[0], 5), dtype=torch.float64, device=S.device)
+    if out is None:
+        out = torch.empty((Sp.shape[0], 5), dtype=torch.float64, device=S.device)
     check(_sgs(ctx.handle, _ptr(S), _ptr(Sp), _ptr(hdiag), _ptr(omega), omega.shape[0],
                Sp.shape[0], _ptr(nu) if nu.numel() else None, nu.shape[0], _ptr(out),
                _stream(stream)))
@@ -665,10 +679,12 @@ def sg_scores(ctx: Context, S: torch.Tensor, Sp: torch.Tensor, hdiag: torch.Tens
 
 
 def residual_itcf(ctx: Context, F_ref: torch.Tensor, F_p: torch.Tensor, tau: torch.Tensor,
-                  beta: float, stream=None) -> torch.Tensor:
+                  beta: float, stream=None,
+                  out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """[n_set][3] conditions (RESIDUAL) on F_n = F_ref - F_p (Eqs. 5 and 7)."""
     F_p = F_p.reshape(-1, tau.shape[0]).contiguous()
-    out = torch.empty((F_p.shape[0], 3), dtype=torch.float64, device=F_p.device)
+    if out is None:
+        out = torch.empty((F_p.shape[0], 3), dtype=torch.float64, device=F_p.device)
     check(_resid(ctx.handle, _ptr(F_ref), _ptr(F_p), F_p.shape[0], _ptr(tau), tau.shape[0],
                  beta, _ptr(out), _stream(stream)))
     return out
@@ -701,13 +717,15 @@ def attenuate(ctx: Context, S: torch.Tensor, omega: torch.Tensor, beta: float,
     scores, F of every filtered spectrum (Eq. 1), the residual conditions
     (Eqs. 5 and 7) and the selected window of each degree."""
     Sp, hd = sg_filter(ctx, S, windows, degrees, stream)
-    sc = sg_scores(ctx, S, Sp, hd, omega, nu, stream)
+    # scores and residuals in one buffer, read back in one copy
+    n = Sp.shape[0]
+    buf = torch.empty(8 * n, dtype=torch.float64, device=S.device)
+    sc = sg_scores(ctx, S, Sp, hd, omega, nu, stream, out=buf[:5 * n].view(n, 5))
     F_ref = itcf(ctx, S, omega, beta, tau, stream)
-    F_p = (torch.stack([itcf(ctx, Sp[f], omega, beta, tau, stream) for f in range(Sp.shape[0])])
-           if Sp.shape[0] else torch.empty((0, tau.shape[0]), dtype=torch.float64,
-                                           device=S.device))
-    rs = residual_itcf(ctx, F_ref, F_p, tau, beta, stream)
-    sc_h, rs_h = sc.cpu().numpy(), rs.cpu().numpy()
+    F_p = itcf_sets(ctx, Sp, omega, beta, tau, stream)
+    rs = residual_itcf(ctx, F_ref, F_p, tau, beta, stream, out=buf[5 * n:].view(n, 3))
+    host = buf.cpu().numpy()
+    sc_h, rs_h = host[:5 * n].reshape(n, 5), host[5 * n:].reshape(n, 3)
     deg = np.asarray(degrees)
     best = {}
     for d in sorted(set(int(x) for x in degrees)):
@@ -1110,7 +1128,7 @@ def eta_scan(ctx: Context, w, st: States, iq: int, etas, prec: str = "bf16x3",
     beta, n = st.beta, st.density
     tau = torch.as_tensor(w.tau_grid(iq), device=dev)
     S = torch.stack([dsf(ctx, dyson(ctx, c, K, i_g0, stream), om, beta, n, stream) for c in chis])
-    F = torch.stack([itcf(ctx, S[i], om, beta, tau, stream) for i in range(len(etas))])
+    F = itcf_sets(ctx, S, om, beta, tau, stream)
     if plan is not None:
         plan.close()
     del chis, P

@@ -5,6 +5,7 @@
 // spectrum of dS/dw, a curvature penalty), the imaginary-time conditions on
 // the residual F_n = F_TDDFT - F_p, and the selection.  All FP64; every
 // reduction is a fixed-order tree, so results are bitwise reproducible.
+#include <algorithm>
 #include <cmath>
 
 #include "internal.h"
@@ -16,17 +17,22 @@ constexpr int kSgMaxDeg = 8;
 constexpr int kRedThreads = 256;
 constexpr int kMaxTargets = 16;
 
-// Fixed-order sum over the block (blockDim.x == kRedThreads); every thread
-// gets the total.
-__device__ double block_sum(double v, double *sh) {
+// Fixed-order sums of N values over the block (blockDim.x == kRedThreads):
+// within each wave by shuffles, then the four waves in order; every thread
+// gets the totals.  Two barriers for all N (a tree in LDS takes ten for each).
+template <int N>
+__device__ void block_sums(double (&v)[N], double *sh) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1)
+#pragma unroll
+    for (int x = 0; x < N; ++x) v[x] += __shfl_xor(v[x], o);
   __syncthreads();
-  sh[threadIdx.x] = v;
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int x = 0; x < N; ++x) sh[4 * x + (threadIdx.x >> 6)] = v[x];
   __syncthreads();
-  for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  return sh[0];
+#pragma unroll
+  for (int x = 0; x < N; ++x) v[x] = ((sh[4 * x] + sh[4 * x + 1]) + sh[4 * x + 2]) + sh[4 * x + 3];
 }
 
 // Output point i of the degree-P filter with w-point windows: the
@@ -102,15 +108,21 @@ __device__ void sg_point(const double *S, int n, int w, int i, double *out, doub
   *hii = hw;
 }
 
-// grid (ceil(n / 256), n_filt): filter f = blockIdx.y, point i.
-__global__ void __launch_bounds__(256)
-    k_sg_filter(const double *S, int n, const int *win, const int *deg, double *Sp,
-                double *hdiag) {
-  const int f = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
+// Windows and degrees of up to 256 filters, passed by value (two copies of
+// the host lists on the stream cost more than the filters).
+struct SgBank {
+  int window[256];
+  unsigned char degree[256];
+};
+
+// grid (ceil(n / 64), filters): filter f0 + blockIdx.y, point i.
+__global__ void __launch_bounds__(64)
+    k_sg_filter(const double *S, int n, SgBank bank, int f0, double *Sp, double *hdiag) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int w = win[f];
+  const int f = f0 + blockIdx.y, w = bank.window[blockIdx.y];
   double val = 0.0, hw = 0.0;
-  switch (deg[f]) {  // uniform over the block
+  switch (bank.degree[blockIdx.y]) {  // uniform over the block
     case 0: sg_point<0>(S, n, w, i, &val, &hw); break;
     case 1: sg_point<1>(S, n, w, i, &val, &hw); break;
     case 2: sg_point<2>(S, n, w, i, &val, &hw); break;
@@ -126,60 +138,70 @@ __global__ void __launch_bounds__(256)
 }
 
 // Power of the central-difference derivative D_i = (y_{i+1} - y_{i-1}) /
-// (w_{i+1} - w_{i-1}), i = 1..n-2, at frequency nu (cycles per unit of w):
-// |(1/(n-2)) sum_i D_i exp(-2 pi i nu w_i)|^2.  Block-wide.
-__device__ double deriv_power(const double *y, const double *om, int n, double nu, double *sh) {
-  double re = 0.0, im = 0.0;
+// (w_{i+1} - w_{i-1}), i = 1..n-2, of N series at frequency nu (cycles per
+// unit of w): |(1/(n-2)) sum_i D_i exp(-2 pi i nu w_i)|^2.  Block-wide.
+template <int N>
+__device__ void deriv_power(const double *const (&y)[N], const double *om, int n, double nu,
+                            double *sh, double (&p)[N]) {
+  double v[2 * N] = {};
   for (int i = 1 + threadIdx.x; i + 1 < n; i += kRedThreads) {
-    const double d = (y[i + 1] - y[i - 1]) / (om[i + 1] - om[i - 1]);
     double sn, cs;
     sincospi(-2.0 * nu * om[i], &sn, &cs);
-    re += d * cs;
-    im += d * sn;
+    const double dw = om[i + 1] - om[i - 1];
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      const double d = (y[x][i + 1] - y[x][i - 1]) / dw;
+      v[2 * x] += d * cs;
+      v[2 * x + 1] += d * sn;
+    }
   }
-  re = block_sum(re, sh);
-  im = block_sum(im, sh);
+  block_sums(v, sh);
   const double m = (double)(n - 2);
-  return (re * re + im * im) / (m * m);
+#pragma unroll
+  for (int x = 0; x < N; ++x) p[x] = (v[2 * x] * v[2 * x] + v[2 * x + 1] * v[2 * x + 1]) / (m * m);
 }
 
 // one block per (set, nu): psd[set][k]
 __global__ void __launch_bounds__(kRedThreads)
     k_deriv_psd(const double *S, const double *om, int n, const double *nu, int n_nu,
                 double *psd) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[16];
   const int k = blockIdx.x, set = blockIdx.y;
-  const double p = deriv_power(S + (size_t)set * n, om, n, nu[k], sh);
-  if (threadIdx.x == 0) psd[(size_t)set * n_nu + k] = p;
+  const double *const y[1] = {S + (size_t)set * n};
+  double p[1];
+  deriv_power(y, om, n, nu[k], sh, p);
+  if (threadIdx.x == 0) psd[(size_t)set * n_nu + k] = p[0];
 }
 
 // one block per filter: scores[f] = (RSS, k_eff, AICc, P_freq, P_curv)
 __global__ void __launch_bounds__(kRedThreads)
     k_sg_scores(const double *S, const double *Sp, const double *hdiag, const double *om, int n,
                 const double *nu, int n_nu, double *scores) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[16];
   const int f = blockIdx.x;
   const double *y = Sp + (size_t)f * n, *hd = hdiag + (size_t)f * n;
-  double rss = 0.0, k = 0.0, c_p = 0.0, c_0 = 0.0;
+  double v[4] = {};  // RSS, sum of the diagonal, curvatures after and before
   for (int i = threadIdx.x; i < n; i += kRedThreads) {
     const double e = y[i] - S[i];
-    rss += e * e;
-    k += hd[i];
+    v[0] += e * e;
+    v[1] += hd[i];
     if (i > 0 && i + 1 < n) {
       const double a = y[i + 1] - 2.0 * y[i] + y[i - 1];
       const double b = S[i + 1] - 2.0 * S[i] + S[i - 1];
-      c_p += a * a;
-      c_0 += b * b;
+      v[2] += a * a;
+      v[3] += b * b;
     }
   }
-  rss = block_sum(rss, sh);
-  k = block_sum(k, sh);
-  c_p = block_sum(c_p, sh);
-  c_0 = block_sum(c_0, sh);
+  block_sums(v, sh);
+  const double *const ys[2] = {y, S};
   double pf = 0.0;
-  for (int t = 0; t < n_nu; ++t)
-    pf += deriv_power(y, om, n, nu[t], sh) / deriv_power(S, om, n, nu[t], sh);
+  for (int t = 0; t < n_nu; ++t) {
+    double p[2];
+    deriv_power(ys, om, n, nu[t], sh, p);
+    pf += p[0] / p[1];
+  }
   if (threadIdx.x == 0) {
+    const double rss = v[0], k = v[1];
     const double dn = (double)n, den = dn - k - 1.0;
     const double aicc = den > 0.0 ? dn * log(rss / dn) + 2.0 * k + 2.0 * k * (k + 1.0) / den
                                   : INFINITY;
@@ -188,7 +210,7 @@ __global__ void __launch_bounds__(kRedThreads)
     o[1] = k;
     o[2] = aicc;
     o[3] = n_nu > 0 ? pf / n_nu : 0.0;
-    o[4] = c_0 > 0.0 ? c_p / c_0 : NAN;
+    o[4] = v[3] > 0.0 ? v[2] / v[3] : NAN;
   }
 }
 
@@ -198,48 +220,48 @@ __global__ void __launch_bounds__(kRedThreads)
 __global__ void __launch_bounds__(kRedThreads)
     k_residual_itcf(const double *Fr, const double *Fp, const double *tau, int n_tau,
                     double beta, double *out) {
-  __shared__ double sh[kRedThreads];
+  __shared__ double sh[8];
+  __shared__ int mid;  // index of beta/2 (the last one, -1 if none)
   const int set = blockIdx.x;
   const double *fp = Fp + (size_t)set * n_tau;
   const double tol = 1e-12 * beta;
   const double t_end = tau[n_tau - 1];
   const bool half = fabs(t_end - 0.5 * beta) <= tol, full = fabs(t_end - beta) <= tol;
+  if (threadIdx.x == 0) mid = -1;
+  __syncthreads();
   // integrals over the grid; a grid ending at beta/2 covers half of [0, beta]
   // and F_n(tau) = F_n(beta - tau) for every S, so each doubles
   const double span = half ? 0.5 * beta : beta;
-  double a = 0.0, e = 0.0;
+  double a[1] = {}, e = 0.0;
   for (int j = threadIdx.x; j < n_tau; j += kRedThreads) {
     const double d = Fr[j] - fp[j];
     e = fmax(e, fabs(d / Fr[j]));
-    if (j + 1 < n_tau) a += 0.5 * (tau[j + 1] - tau[j]) * (d + (Fr[j + 1] - fp[j + 1]));
+    if (j + 1 < n_tau) a[0] += 0.5 * (tau[j + 1] - tau[j]) * (d + (Fr[j + 1] - fp[j + 1]));
+    if (fabs(tau[j] - 0.5 * beta) <= tol) atomicMax(&mid, j);
   }
-  a = block_sum(a, sh);
-  const double mean = a / span;
-  double q = 0.0;
+  block_sums(a, sh);
+  const double mean = a[0] / span;
+  double q[1] = {};
   for (int j = threadIdx.x; j + 1 < n_tau; j += kRedThreads) {
     const double d0 = Fr[j] - fp[j] - mean, d1 = Fr[j + 1] - fp[j + 1] - mean;
-    q += 0.5 * (tau[j + 1] - tau[j]) * (d0 * d0 + d1 * d1);
+    q[0] += 0.5 * (tau[j + 1] - tau[j]) * (d0 * d0 + d1 * d1);
   }
-  q = block_sum(q, sh);
-  // max over the block by the same tree (all values are >= 0)
+  block_sums(q, sh);
+  // max over the block (all values are >= 0)
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) e = fmax(e, __shfl_xor(e, o));
   __syncthreads();
-  sh[threadIdx.x] = e;
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = e;
   __syncthreads();
-  for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    int mid = -1;
-    for (int j = 0; j < n_tau; ++j)
-      if (fabs(tau[j] - 0.5 * beta) <= tol) mid = j;
+    e = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
     const bool ok = n_tau > 1 && tau[0] == 0.0 && (half || full) && mid >= 0;
     const double fm = ok ? Fr[mid] : NAN;
     // root-mean-square deviation over [0, beta]: the integral over the grid
     // is q * beta / span, its mean over [0, beta] q / span
-    const double sigma = sqrt(q / span);
+    const double sigma = sqrt(q[0] / span);
     double *o = out + (size_t)set * 3;
-    o[0] = ok ? sh[0] : NAN;
+    o[0] = ok ? e : NAN;
     o[1] = ok ? mean / fm : NAN;
     o[2] = ok ? sigma / fm : NAN;
   }
@@ -268,17 +290,18 @@ int tdx_sg_filter(tdx_ctx *ctx, const double *S, int n_w, const int *windows,
   }
   TDX_TRY(check_device(ctx));
   if (n_filt == 0) return TDX_OK;
-  hipStream_t s = as_stream(stream);
-  void *w1;
-  TDX_TRY(ws_get(ctx, WS_SG, sizeof(int) * 2 * (size_t)n_filt, &w1));
-  int *d_win = (int *)w1, *d_deg = d_win + n_filt;
-  TDX_HIP(hipMemcpyAsync(d_win, windows, sizeof(int) * n_filt, hipMemcpyHostToDevice, s));
-  TDX_HIP(hipMemcpyAsync(d_deg, degrees, sizeof(int) * n_filt, hipMemcpyHostToDevice, s));
-  hipLaunchKernelGGL(k_sg_filter, dim3((n_w + 255) / 256, n_filt), dim3(256), 0, s, S, n_w,
-                     d_win, d_deg, Sp, hdiag);
-  TDX_HIP(hipGetLastError());
-  // the window and degree lists are pageable host memory copied on the stream
-  TDX_HIP(hipStreamSynchronize(s));
+  for (int f0 = 0; f0 < n_filt; f0 += 256) {
+    SgBank bank;
+    const int nf = std::min(256, n_filt - f0);
+    for (int f = 0; f < nf; ++f) {
+      bank.window[f] = windows[f0 + f];
+      bank.degree[f] = (unsigned char)degrees[f0 + f];
+    }
+    hipLaunchKernelGGL(k_sg_filter, dim3((n_w + 63) / 64, nf), dim3(64), 0, as_stream(stream), S,
+                       n_w, bank, f0, Sp, hdiag);
+    TDX_HIP(hipGetLastError());
+  }
+  TDX_HIP(hipStreamSynchronize(as_stream(stream)));  // as the interface promises
   return TDX_OK;
 }
 

@@ -25,27 +25,53 @@ __global__ void k_dsf(const double2 *chi, const double *w, int n, double beta, d
   S[i] = v;
 }
 
-// F(tau) = sum_j c_j S_j (e^{-tau w_j} + e^{-(beta - tau) w_j}), one block
-// per tau, fixed-order tree reduction.
+// Sum over a wave, every lane (fixed order).
+__device__ inline double wave_sum(double x) {
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
+  return x;
+}
+
+// F_s(tau) = sum_j c_j S_sj (e^{-tau w_j} + e^{-(beta - tau) w_j}) for the rows
+// S_s of n_set spectra: a block forms the kernel's values of one tau in LDS,
+// 1024 frequencies at a time, and its waves take the spectra in turn.  One
+// launch serves a whole filter bank: 86 launches of 4 us each were a third of
+// the attenuation search's 1.07 ms (their host side most of the rest).
+constexpr int kItcfSets = 8;      // spectra per block, two per wave
+constexpr int kItcfChunk = 1024;  // kernel values in LDS
 __global__ void __launch_bounds__(256)
-    k_itcf(const double *S, const double *w, int n, double beta, const double *tau, double *F) {
-  __shared__ double sh[256];
-  const int it = blockIdx.x;
-  const double t = tau[it];
-  double acc = 0.0;
-  for (int j = threadIdx.x; j < n; j += 256) {
-    double c = 0.0;
-    if (j > 0) c += 0.5 * (w[j] - w[j - 1]);
-    if (j + 1 < n) c += 0.5 * (w[j + 1] - w[j]);
-    acc += c * S[j] * (exp(-t * w[j]) + exp(-(beta - t) * w[j]));
-  }
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
+    k_itcf(const double *S, int n_set, const double *w, int n, double beta, const double *tau,
+           int n_tau, double *F) {
+  __shared__ double e[kItcfChunk];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int s0 = blockIdx.y * kItcfSets + 2 * wave;
+  const double t = tau[blockIdx.x];
+  double acc[2] = {0.0, 0.0};
+  for (int j0 = 0; j0 < n; j0 += kItcfChunk) {
+    const int m = min(kItcfChunk, n - j0);
+    if (j0 > 0) __syncthreads();
+    for (int i = threadIdx.x; i < m; i += 256) {
+      const int j = j0 + i;
+      const double wj = w[j];
+      double c = 0.0;
+      if (j > 0) c += 0.5 * (wj - w[j - 1]);
+      if (j + 1 < n) c += 0.5 * (w[j + 1] - wj);
+      e[i] = c * (exp(-t * wj) + exp(-(beta - t) * wj));
+    }
     __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      if (s0 + x >= n_set) continue;
+      const double *row = S + (size_t)(s0 + x) * n + j0;
+      for (int i = lane; i < m; i += 64) acc[x] = fma(e[i], row[i], acc[x]);
+    }
   }
-  if (threadIdx.x == 0) F[it] = sh[0];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    if (s0 + x >= n_set) continue;
+    const double f = wave_sum(acc[x]);
+    if (lane == 0) F[(size_t)(s0 + x) * n_tau + blockIdx.x] = f;
+  }
 }
 
 // Imaginary-time metrics of one ITCF per block (Sec. 2, Eq. 2):
@@ -58,27 +84,23 @@ __global__ void __launch_bounds__(256)
 __global__ void __launch_bounds__(64)
     k_itcf_metrics(const double *F, int n_tau, const double *tau, double beta, double dens,
                    double *m) {
-  __shared__ double sh[64];
   const int set = blockIdx.x;
   const double *f = F + (size_t)set * n_tau;
   const double tol = 1e-12 * beta;
   const double t_end = tau[n_tau - 1];
   const bool half = fabs(t_end - 0.5 * beta) <= tol, full = fabs(t_end - beta) <= tol;
   double acc = 0.0;
-  for (int j = threadIdx.x; j + 1 < n_tau; j += 64)
-    acc += 0.5 * (tau[j + 1] - tau[j]) * (f[j] + f[j + 1]);
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 32; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
+  int mid = -1;  // index of beta/2 (the last one)
+  for (int j = threadIdx.x; j < n_tau; j += 64) {
+    if (j + 1 < n_tau) acc += 0.5 * (tau[j + 1] - tau[j]) * (f[j] + f[j + 1]);
+    if (fabs(tau[j] - 0.5 * beta) <= tol) mid = j;
   }
+  acc = wave_sum(acc);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) mid = max(mid, __shfl_xor(mid, o));
   if (threadIdx.x == 0) {
-    int mid = -1;
-    for (int j = 0; j < n_tau; ++j)
-      if (fabs(tau[j] - 0.5 * beta) <= tol) mid = j;
     const bool ok = n_tau > 1 && tau[0] == 0.0 && (half || full) && mid >= 0;
-    const double A = (half ? 2.0 : 1.0) * sh[0];
+    const double A = (half ? 2.0 : 1.0) * acc;
     const double f0 = f[0], fm = ok ? f[mid] : NAN;
     double *o = m + (size_t)set * 5;
     o[0] = ok ? fm : NAN;
@@ -107,7 +129,7 @@ __device__ inline double im_chi_of(const double *S, const double *w, int j, doub
 __global__ void __launch_bounds__(256)
     k_dielectric(const double *S, const double *w, int n, double beta, double dens, double q2,
                  double2 *chi, double2 *eps_inv, double2 *sigma) {
-  __shared__ double sh[256];
+  __shared__ double sh[4];
   const int i = blockIdx.x;
   const double wi = w[i];
   double acc = 0.0;
@@ -124,14 +146,11 @@ __global__ void __launch_bounds__(256)
     }
     acc += t;
   }
-  sh[threadIdx.x] = acc;
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    const double re = sh[0] / M_PI, im = im_chi_of(S, w, i, beta, dens);
+    const double re = (((sh[0] + sh[1]) + sh[2]) + sh[3]) / M_PI, im = im_chi_of(S, w, i, beta, dens);
     const double v = 4.0 * M_PI / q2;
     const double er = 1.0 + v * re, ei = v * im;  // eps^{-1}
     const double d = er * er + ei * ei;
@@ -164,16 +183,30 @@ int tdx_dsf(tdx_ctx *ctx, const double *chi00, const double *omega, int n_w, dou
   return TDX_OK;
 }
 
+int tdx_itcf_sets(tdx_ctx *ctx, const double *S, int n_set, const double *omega, int n_w,
+                  double beta, const double *tau, int n_tau, double *F, tdx_stream stream) {
+  clear_error();
+  TDX_REQUIRE(ctx && omega && tau && (n_set == 0 || (S && F)), TDX_ERR_INVALID_ARG,
+              "null argument");
+  TDX_REQUIRE(n_w > 0 && n_tau > 0 && n_set >= 0, TDX_ERR_SHAPE, "bad sizes");
+  TDX_REQUIRE(std::isfinite(beta) && beta > 0, TDX_ERR_INVALID_ARG, "bad beta");
+  // the grid's second axis holds 65535 blocks
+  constexpr int kMost = 65535 * kItcfSets;
+  for (int s0 = 0; s0 < n_set; s0 += kMost) {
+    const int ns = n_set - s0 < kMost ? n_set - s0 : kMost;
+    hipLaunchKernelGGL(k_itcf, dim3(n_tau, (ns + kItcfSets - 1) / kItcfSets), dim3(256), 0,
+                       as_stream(stream), S + (size_t)s0 * n_w, ns, omega, n_w, beta, tau, n_tau,
+                       F + (size_t)s0 * n_tau);
+    TDX_HIP(hipGetLastError());
+  }
+  return TDX_OK;
+}
+
 int tdx_itcf(tdx_ctx *ctx, const double *S, const double *omega, int n_w, double beta,
              const double *tau, int n_tau, double *F, tdx_stream stream) {
   clear_error();
   TDX_REQUIRE(ctx && S && omega && tau && F, TDX_ERR_INVALID_ARG, "null argument");
-  TDX_REQUIRE(n_w > 0 && n_tau > 0, TDX_ERR_SHAPE, "bad sizes");
-  TDX_REQUIRE(std::isfinite(beta) && beta > 0, TDX_ERR_INVALID_ARG, "bad beta");
-  hipLaunchKernelGGL(k_itcf, dim3(n_tau), dim3(256), 0, as_stream(stream), S, omega, n_w, beta,
-                     tau, F);
-  TDX_HIP(hipGetLastError());
-  return TDX_OK;
+  return tdx_itcf_sets(ctx, S, 1, omega, n_w, beta, tau, n_tau, F, stream);
 }
 
 int tdx_itcf_metrics(tdx_ctx *ctx, const double *F, int n_set, const double *tau, int n_tau,
