@@ -1,0 +1,134 @@
+"""The Kubo-Greenwood conductivity by bands on seeded synthetic states: bands
+around the groups of 5 and the tiles of 16, plane waves around the K-step of
+16 and past what LDS holds, frequencies around the blocks of the sums, and
+lists that are complete, hold one direction, miss transitions or are in
+another order.  Reference: the defining sums, in FP64 on the CPU."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -53
+
+
+@pytest.fixture(scope="module")
+def tdx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_01875_amd as m
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(tdx):
+    c = tdx.Context(0)
+    yield c
+    c.close()
+
+
+def _system(tdx, npw, nb, seed):
+    import torch
+    rng = np.random.default_rng(seed)
+    d = tdx.StatesDims()
+    d.n_k, d.npw_max, d.nb_max = 2, npw + 3, nb
+    st = tdx.States(d, 0)
+    ax = np.arange(-6, 7)
+    cube = np.stack(np.meshgrid(ax, ax, ax, indexing="ij"), -1).reshape(-1, 3)
+    n = [npw, npw + 3]
+    mil = np.zeros((2, npw + 3, 3), dtype=np.int32)
+    coef = np.zeros((2, nb, npw + 3), dtype=np.complex128)
+    for k in range(2):
+        mil[k, :n[k]] = rng.permutation(cube)[:n[k]]
+        coef[k, :, :n[k]] = rng.standard_normal((nb, n[k])) + 1j * rng.standard_normal((nb, n[k]))
+    occ = np.where(np.arange(nb) < (nb + 1) // 2, rng.uniform(0.5, 1.0, (2, nb)), 0.0)
+    eps = np.cumsum(rng.uniform(0.05, 0.2, (2, nb)), axis=1)
+    for t, x in ((st.npw, np.array(n, dtype=np.int32)), (st.nb, np.full(2, nb, dtype=np.int32)),
+                 (st.miller, mil), (st.eps, eps), (st.occ, occ), (st.coef, coef)):
+        t.copy_(torch.from_numpy(x))
+    b = rng.standard_normal((3, 3))
+    st.c.kgrid[:] = [2, 1, 1]
+    st.c.mmax[:] = [6, 6, 6]
+    st.c.bvec[:] = list(b.reshape(-1))
+    st.c.omega_cell = 37.0
+    return st, n, mil, coef, b
+
+
+def _list(tdx, tr, form, seed):
+    """The list tr in another form: the kept transitions, in their order or not."""
+    import torch
+    T = len(tr)
+    rng = np.random.default_rng(seed)
+    keep = np.arange(T)
+    n, m = tr.n.cpu().numpy(), tr.m.cpu().numpy()
+    if form == "up":
+        keep = keep[n[:T] < m[:T]]
+    elif form == "down":
+        keep = keep[n[:T] > m[:T]]
+    elif form == "gaps":
+        keep = keep[rng.random(T) < 0.6]
+    elif form == "shuffled":
+        keep = rng.permutation(T)
+    out = tdx.Transitions(len(keep), 0)
+    idx = torch.from_numpy(keep).cuda()
+    for a in ("k", "n", "m", "delta", "df"):
+        if len(keep):
+            getattr(out, a).copy_(getattr(tr, a)[idx])
+    return out
+
+
+# (plane waves, bands, frequencies)
+CASES = [(1, 2, 1), (15, 5, 7), (16, 6, 8), (17, 16, 9), (30, 17, 255), (33, 33, 257), (61, 40, 300),
+         (1600, 7, 64)]
+
+
+@pytest.mark.parametrize("form", ["full", "up", "down", "gaps", "shuffled"])
+@pytest.mark.parametrize("npw,nb,n_w", CASES)
+def test_conductivity_matches_the_defining_sums(tdx, ctx, npw, nb, n_w, form):
+    import torch
+    print("kg bands", npw, nb, n_w, form, flush=True)
+    st, n, mil, coef, b = _system(tdx, npw, nb, 31 * npw + nb)
+    tr = _list(tdx, tdx.transitions(ctx, st, (0, 0, 0), 1e-3), form, nb)
+    T = len(tr)
+    k, nn, mm = (x.cpu().numpy()[:T] for x in (tr.k, tr.n, tr.m))
+    delta, df = tr.delta.cpu().numpy()[:T], tr.df.cpu().numpy()[:T]
+    om, eta = np.linspace(-1.0, 3.0, n_w), 0.07
+    W, mag = np.zeros(T), np.zeros(T)
+    for t in range(T):
+        kk = k[t]
+        kf = mil[kk, :n[kk]] + np.array([(2.0 * kk - 1.0) / 4.0, 0.0, 0.0])
+        g = kf @ b
+        cm, cn = coef[kk, mm[t], :n[kk]], coef[kk, nn[t], :n[kk]]
+        p = (np.conj(cm) * cn) @ g
+        W[t] = df[t] / delta[t] * np.sum(np.abs(p) ** 2) / 3.0
+        # the products' magnitudes, with those of the sums that make k + G
+        a = np.abs(kf) @ np.abs(b)
+        mag[t] = np.abs(df[t] / delta[t]) * np.sum((np.abs(cm) * np.abs(cn) @ a) ** 2) / 3.0
+    pref = 2.0 / (37.0 * 2)
+    den = om[:, None] - delta[None, :] + 1j * eta
+    ref = 1j * pref * (W[None, :] / den).sum(axis=1)
+    # |p|^2 as a sum of n terms on both sides (each relative error, then
+    # squared), k + G and the weight's operations, the denominator's, the sum over t
+    steps = 2 * (2 * (2 * (npw + 3) + 12)) + 40 + 2 * T
+    tol = pref * steps * EPS * (mag[None, :] / np.abs(den)).sum(axis=1)
+    got = tdx.kg_conductivity(ctx, st, torch.as_tensor(om, device="cuda"), eta, 1e-3,
+                              tr=tr).cpu().numpy()
+    assert np.all(np.abs(got - ref) <= tol), float(np.max(np.abs(got - ref) / (tol + 1e-300)))
+
+
+def test_extreme_broadening_takes_the_division(tdx, ctx):
+    """eta^2 under and over the range of the reciprocal estimate: all terms
+    finite, sigma as the division gives it."""
+    import torch
+    st, *_ = _system(tdx, 17, 12, 5)
+    tr = tdx.transitions(ctx, st, (0, 0, 0), 1e-3)
+    om = torch.linspace(-1.0, 3.0, 33, device="cuda", dtype=torch.float64) + 1e-3
+    base = tdx.kg_conductivity(ctx, st, om, 1e-9, 1e-3, tr=tr).cpu().numpy()
+    tiny = tdx.kg_conductivity(ctx, st, om, 1e-150, 1e-3, tr=tr).cpu().numpy()
+    # off the poles Im sigma depends on eta to O(eta^2 / x^2) only
+    x = om.cpu().numpy()[:, None] - tr.delta.cpu().numpy()[None, :]
+    assert np.min(np.abs(x)) > 1e-5
+    scale = np.max(np.abs(base.imag))
+    assert np.max(np.abs(tiny.imag - base.imag)) <= 1e-7 * scale
+    huge = tdx.kg_conductivity(ctx, st, om, 1e145, 1e-3, tr=tr).cpu().numpy()
+    assert np.all(np.isfinite(huge)) and np.max(np.abs(huge)) < 1e-140 * scale * 1e3
