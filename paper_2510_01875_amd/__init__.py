@@ -834,8 +834,8 @@ def chi0_vjp(ctx: Context, tr: Transitions, P: torch.Tensor, n_g: int, omega: to
     n = t_end - int(t_begin)
     ld = (n_g + 15) // 16 * 16
     w_bar = (w_out if w_out is not None else
-             torch.zeros((max(n, 1), 3), dtype=torch.float64, device=dev))
-    rho_bar = (torch.zeros((max(n, 1), ld), dtype=torch.complex128, device=dev)
+             torch.empty((max(n, 1), 3), dtype=torch.float64, device=dev))
+    rho_bar = (torch.empty((max(n, 1), ld), dtype=torch.complex128, device=dev)
                if want_rho else None)
     check(_chi0_vjp(ctx.handle, C.byref(tr.c), int(t_begin), t_end, _ptr(P), n_g, _ptr(omega),
                     omega.shape[0], eta, pref, _ptr(u), _ptr(v), _ptr(w_bar),

@@ -6,6 +6,7 @@
 // are bitwise reproducible.
 #include <algorithm>
 #include <cmath>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -41,8 +42,10 @@ constexpr int kVjpRow = kVjpG + 1;     // padded LDS row (complex)
 //          = (Re sum_w lambda dw/d(df), Re sum_w lambda dw/d(delta), Re sum_w lambda dw/d(eta)),
 // and rhobar_t(G) = sum_w conj(c1) u_G + c2 v_G with c1 = pref w_t conj(beta),
 // c2 = pref w_t alpha.
+// Any number of response vectors: rhobar accumulates in global memory per 64
+// frequencies.
 __global__ void __launch_bounds__(256)
-    k_chi0_vjp(const double2 *P, int ld, long long t_lo, long long n_trans, int n_g,
+    k_chi0_vjp_wide(const double2 *P, int ld, long long t_lo, long long n_trans, int n_g,
                const double *delta, const double *df, int paired, const double *omega, int n_w,
                double eta, double pref, const double2 *u, const double2 *v, double *wbar,
                double2 *rhobar) {
@@ -201,6 +204,271 @@ __global__ void __launch_bounds__(256)
     wbar[3 * t + 1] = dft * sdr;
     wbar[3 * t + 2] = dft * sei;
   }
+}
+
+// The weights' values and the sums over frequency of one transition.
+struct VjpSums {
+  double sf = 0.0, sd = 0.0, se = 0.0;
+};
+
+// f(0), f(1), .. with constants, for indexes of register arrays.
+template <typename F, int... I>
+__device__ inline void for_each_of(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+
+// One (frequency, transition): alpha = a, beta = b to c1 = pref w conj(b) and
+// c2 = pref w a, and the terms of the real cotangents.
+__device__ inline void vjp_weight(double w, double dl, double dft, double eta, double pref,
+                                  int paired, double &ar, double &ai, double &br, double &bi,
+                                  VjpSums &s) {
+  const double lr = pref * (ar * br + ai * bi), li = pref * (ai * br - ar * bi);
+  const double dr = w - dl;
+  const double inv = 1.0 / (dr * dr + eta * eta);
+  // r1 = 1 / (w - delta + i eta) and its square
+  const double r1r = dr * inv, r1i = -eta * inv;
+  const double q1r = r1r * r1r - r1i * r1i, q1i = 2.0 * r1r * r1i;
+  double gr = r1r, gi = r1i, hr = q1r, hi = q1i, er = q1r, ei = q1i;
+  if (paired) {
+    // r2 = 1 / (w + delta + i eta): g = r1 - r2, h = r1^2 + r2^2, e = r1^2 - r2^2
+    const double d2 = w + dl;
+    const double inv2 = 1.0 / (d2 * d2 + eta * eta);
+    const double r2r = d2 * inv2, r2i = -eta * inv2;
+    const double q2r = r2r * r2r - r2i * r2i, q2i = 2.0 * r2r * r2i;
+    gr = r1r - r2r;
+    gi = r1i - r2i;
+    hr = q1r + q2r;
+    hi = q1i + q2i;
+    er = q1r - q2r;
+    ei = q1i - q2i;
+  }
+  s.sf += lr * gr - li * gi;
+  s.sd += lr * hr - li * hi;
+  s.se += lr * ei + li * er;  // dw/d(eta) = -i df e: df Im(sum lambda e)
+  const double wr = dft * gr, wim = dft * gi;
+  const double c1r = pref * (wr * br + wim * bi), c1i = pref * (wim * br - wr * bi);
+  const double c2r = pref * (wr * ar - wim * ai), c2i = pref * (wr * ai + wim * ar);
+  ar = c1r;
+  ai = c1i;
+  br = c2r;
+  bi = c2i;
+}
+
+// A workgroup takes `tt` tiles of 16 transitions, kWaves / tt waves each, which
+// deal the tiles of 16 frequencies among them; a wave keeps rhobar of its
+// transitions (kTiles tiles of 16 response vectors) in registers over all its
+// frequencies, and the waves of a tile add theirs through LDS at the end, in
+// order.  alpha and beta leave the MFMA in the lane layout that it takes c1 and
+// c2 in.  rho sits in LDS; u and v come from L2, 2 KB per 512 MFMA cycles.  The
+// bound is the FP64 MFMA, 32 n_w n_g n_t operations with n_w and n_g rounded
+// up to 16; 16 transitions per workgroup keep the last round of workgroups
+// short and give a short list 8 waves per tile.  With up to kTiles = 9, two
+// waves per SIMD cover each other's loads; the registers of more tiles leave
+// one, which loads a step ahead.
+// Measured at 50000 transitions, 133 vectors, 500 frequencies: 4957 us with 64
+// transitions per workgroup (1.5 rounds), u and v through LDS and rhobar read
+// and written per 64 frequencies, 2071 us (51 TFLOP/s of the 73 that the MFMA
+// reaches; 57 with the padding); 200 transitions, 300 vectors, 100
+// frequencies: 456 to 122 us; 5000, 300, 300: 1494 to 563 us.
+template <int kTiles, int kWaves>
+__global__ void __launch_bounds__(64 * kWaves, kWaves / 4)
+    k_chi0_vjp(const double2 *P, int ld, long long t_lo, long long n_trans, int n_g,
+               const double *delta, const double *df, int paired, const double *omega, int n_w,
+               double eta, double pref, const double2 *u, const double2 *v, int tt, double *wbar,
+               double2 *rhobar) {
+  // rows of P, wbar and rhobar are local (row i is transition t_lo + i)
+  extern __shared__ double2 vjp_lds[];  // rho [16 tt][ld + 1], then the partial sums
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int col = lane & 15, quad = lane >> 4;
+  const int ww = kWaves / tt, tile = wave / ww, share = wave % ww;
+  const long long tb = (long long)blockIdx.x * 16 * tt;
+  for (int e = tid; e < 16 * tt * ld; e += 64 * kWaves) {
+    const int r = e / ld, c = e % ld;
+    vjp_lds[r * (ld + 1) + c] =
+        tb + r < n_trans && c < n_g ? P[(size_t)(tb + r) * ld + c] : make_double2(0.0, 0.0);
+  }
+  __syncthreads();
+  const long long t = tb + 16 * tile + col;
+  const long long tc = t < n_trans ? t : n_trans - 1;
+  const double dl = delta[t_lo + tc], dft = df[t_lo + tc];
+  const double2 *brow = vjp_lds + (16 * tile + col) * (ld + 1) + 4 * quad;
+  const int n_wt = (n_w + 15) / 16, n_gt = ld / 16, last = n_g - 1;
+  constexpr bool kAhead = kWaves == 4;
+  VjpSums sums;
+  f64x4 out[kTiles][2];
+#pragma unroll
+  for (int g = 0; g < kTiles; ++g) out[g][0] = out[g][1] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int wt = share; wt < n_wt; wt += ww) {
+    f64x4 ab[4];  // alpha, beta: real and imaginary parts
+#pragma unroll
+    for (int x = 0; x < 4; ++x) ab[x] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const size_t row = (size_t)std::min(16 * wt + col, n_w - 1) * n_g;
+    // past n_g rho is zero
+    auto load_rows = [&](double2 (&a)[2][4], int g) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const size_t k = row + std::min(16 * g + 4 * quad + i, last);
+        a[0][i] = u[k];
+        a[1][i] = v[k];
+      }
+    };
+    double2 next[2][4];
+    if (kAhead) load_rows(next, 0);
+    for (int g = 0; g < n_gt; ++g) {
+      double2 a[2][4], b[4];
+      if (!kAhead) load_rows(a, g);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (kAhead) {
+          a[0][i] = next[0][i];
+          a[1][i] = next[1][i];
+        }
+        b[i] = brow[16 * g + i];
+      }
+      if (kAhead && g + 1 < n_gt) load_rows(next, g + 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // conj(a) b
+        ab[0] = mfma64(a[0][i].x, b[i].x, ab[0]);
+        ab[1] = mfma64(a[0][i].x, b[i].y, ab[1]);
+        ab[2] = mfma64(a[1][i].x, b[i].x, ab[2]);
+        ab[3] = mfma64(a[1][i].x, b[i].y, ab[3]);
+        ab[0] = mfma64(a[0][i].y, b[i].y, ab[0]);
+        ab[1] = mfma64(-a[0][i].y, b[i].x, ab[1]);
+        ab[2] = mfma64(a[1][i].y, b[i].y, ab[2]);
+        ab[3] = mfma64(-a[1][i].y, b[i].x, ab[3]);
+      }
+    }
+    // lane holds frequency 16 wt + quad + 4 j, transition t
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int wi = 16 * wt + quad + 4 * j;
+      double ar = ab[0][j], ai = ab[1][j], br = ab[2][j], bi = ab[3][j];
+      if (wi < n_w)
+        vjp_weight(omega[wi], dl, dft, eta, pref, paired, ar, ai, br, bi, sums);
+      else
+        ar = ai = br = bi = 0.0;
+      ab[0][j] = ar;
+      ab[1][j] = ai;
+      ab[2][j] = br;
+      ab[3][j] = bi;
+    }
+    if (!rhobar) continue;
+    auto load_cols = [&](double2 (&a)[2][4], int g) {
+      const int gi = 16 * g + col, gc = std::min(gi, last);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const size_t k = (size_t)std::min(16 * wt + quad + 4 * j, n_w - 1) * n_g + gc;
+        a[0][j] = u[k];
+        a[1][j] = v[k];
+      }
+    };
+    if (kAhead) load_cols(next, 0);
+    for_each_of(std::make_integer_sequence<int, kTiles>{}, [&](auto G) {
+      constexpr int g = G;
+      if (g >= n_gt) return;
+      double2 a[2][4];
+      if (!kAhead) load_cols(a, g);
+      if (kAhead) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          a[0][j] = next[0][j];
+          a[1][j] = next[1][j];
+        }
+        if (g + 1 < n_gt) load_cols(next, g + 1);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        out[g][0] = mfma64(ab[0][j], a[0][j].x, out[g][0]);
+        out[g][1] = mfma64(ab[0][j], a[0][j].y, out[g][1]);
+        out[g][0] = mfma64(ab[1][j], a[0][j].y, out[g][0]);
+        out[g][1] = mfma64(-ab[1][j], a[0][j].x, out[g][1]);
+        out[g][0] = mfma64(ab[2][j], a[1][j].x, out[g][0]);
+        out[g][1] = mfma64(ab[2][j], a[1][j].y, out[g][1]);
+        out[g][0] = mfma64(-ab[3][j], a[1][j].y, out[g][0]);
+        out[g][1] = mfma64(ab[3][j], a[1][j].x, out[g][1]);
+      }
+    });
+  }
+  __syncthreads();
+  if (rhobar) {
+    // two tiles of response vectors at a time: [wave][tile][j][lane]
+    double2 *red = vjp_lds;
+    for_each_of(std::make_integer_sequence<int, (kTiles + 1) / 2>{}, [&](auto H) {
+      constexpr int g0 = 2 * H, g1 = std::min(g0 + 1, kTiles - 1);
+      if (g0 >= n_gt) return;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        red[(wave * 8 + j) * 64 + lane] = make_double2(out[g0][0][j], out[g0][1][j]);
+        red[(wave * 8 + 4 + j) * 64 + lane] = make_double2(out[g1][0][j], out[g1][1][j]);
+      }
+      __syncthreads();
+      for (int e = tid; e < tt * 512; e += 64 * kWaves) {
+        const int l = e & 63, j = (e >> 6) & 3, x = (e >> 8) & 1, q = e >> 9;
+        const long long tr = tb + 16 * q + (l >> 4) + 4 * j;
+        const int gi = 16 * (g0 + x) + (l & 15);
+        if (g0 + x >= n_gt || tr >= n_trans) continue;
+        double2 z = make_double2(0.0, 0.0);
+        for (int k = 0; k < ww; ++k) {
+          const double2 y = red[((q * ww + k) * 8 + 4 * x + j) * 64 + l];
+          z.x += y.x;
+          z.y += y.y;
+        }
+        rhobar[(size_t)tr * ld + gi] = gi < n_g ? z : make_double2(0.0, 0.0);
+      }
+      __syncthreads();
+    });
+  }
+  // lanes of one column hold disjoint frequencies of the same transition
+  double *ws = (double *)vjp_lds;  // [wave][3][16]
+  sums.sf += __shfl_xor(sums.sf, 16);
+  sums.sd += __shfl_xor(sums.sd, 16);
+  sums.se += __shfl_xor(sums.se, 16);
+  sums.sf += __shfl_xor(sums.sf, 32);
+  sums.sd += __shfl_xor(sums.sd, 32);
+  sums.se += __shfl_xor(sums.se, 32);
+  if (quad == 0) {
+    ws[(wave * 3 + 0) * 16 + col] = sums.sf;
+    ws[(wave * 3 + 1) * 16 + col] = dft * sums.sd;
+    ws[(wave * 3 + 2) * 16 + col] = dft * sums.se;
+  }
+  __syncthreads();
+  for (int e = tid; e < tt * 48; e += 64 * kWaves) {
+    const int q = e / 48, c = e % 3, r = e % 48 / 3;
+    if (tb + 16 * q + r >= n_trans) continue;
+    double z = 0.0;
+    for (int k = 0; k < ww; ++k) z += ws[((q * ww + k) * 3 + c) * 16 + r];
+    wbar[3 * (tb + 16 * q + r) + c] = z;
+  }
+}
+
+template <int kTiles, int kWaves>
+int vjp_launch(int n_cu, const double2 *P, int ld, long long t_lo, long long n, int n_g,
+               const tdx_translist *tl, const double *omega, int n_w, double eta, double pref,
+               const double2 *u, const double2 *v, double *wbar, double2 *rhobar, hipStream_t s) {
+  // Transition tiles per workgroup: the fewest rounds of workgroups times
+  // frequency tiles per wave (the bound above), the fewest tiles on a tie.
+  const int n_wt = (n_w + 15) / 16;
+  const size_t red = sizeof(double2) * kWaves * 2 * 256;
+  int tt = 1;
+  long long best = 0;
+  for (int x = 1; x <= kWaves; x *= 2) {
+    if (sizeof(double2) * 16 * x * (ld + 1) > 160 * 1024) break;
+    const long long wgs = (n + 16 * x - 1) / (16 * x);
+    const int ww = kWaves / x;
+    const long long cost = ((wgs + n_cu - 1) / n_cu) * ((n_wt + ww - 1) / ww);
+    if (x == 1 || cost < best) tt = x, best = cost;
+  }
+  const size_t lds = std::max(red, sizeof(double2) * 16 * tt * (ld + 1));
+  const long long blocks = (n + 16 * tt - 1) / (16 * tt);
+  TDX_REQUIRE(blocks <= 0x7fffffffLL, TDX_ERR_SHAPE, "too many transitions");
+  TDX_HIP(hipFuncSetAttribute((const void *)k_chi0_vjp<kTiles, kWaves>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL((k_chi0_vjp<kTiles, kWaves>), dim3((unsigned)blocks), dim3(64 * kWaves), lds,
+                     s, P, ld, t_lo, n, n_g, tl->delta, tl->df, (int)tl->paired, omega, n_w, eta,
+                     pref, u, v, tt, wbar, rhobar);
+  TDX_HIP(hipGetLastError());
+  return TDX_OK;
 }
 
 // Per-state cotangents of one q from the transition cotangents
@@ -559,10 +827,23 @@ int tdx_chi0_vjp(tdx_ctx *ctx, const tdx_translist *tl, int64_t t_begin, int64_t
   TDX_TRY(check_device(ctx));
   const long long n = t_end - t_begin;
   if (n == 0) return TDX_OK;
+  const int ld = ld_of(n_g);
+  auto launch = [&](auto fn) {
+    return fn(std::max(ctx->n_cu, 1), (const double2 *)P, ld, (long long)t_begin, n, n_g, tl,
+              omega, n_w, eta, pref, (const double2 *)u, (const double2 *)v, w_bar,
+              (double2 *)rho_bar, as_stream(stream));
+  };
+  // one workgroup's registers hold rhobar of up to 320 response vectors
+  if (ld <= 48) return launch(vjp_launch<3, 8>);
+  if (ld <= 96) return launch(vjp_launch<6, 8>);
+  if (ld <= 144) return launch(vjp_launch<9, 8>);
+  if (ld <= 192) return launch(vjp_launch<12, 4>);
+  if (ld <= 256) return launch(vjp_launch<16, 4>);
+  if (ld <= 320) return launch(vjp_launch<20, 4>);
   const long long blocks = (n + kVjpT - 1) / kVjpT;
   TDX_REQUIRE(blocks <= 0x7fffffffLL, TDX_ERR_SHAPE, "too many transitions");
-  hipLaunchKernelGGL(k_chi0_vjp, dim3((unsigned)blocks), dim3(256), 0, as_stream(stream),
-                     (const double2 *)P, ld_of(n_g), (long long)t_begin, n, n_g, tl->delta,
+  hipLaunchKernelGGL(k_chi0_vjp_wide, dim3((unsigned)blocks), dim3(256), 0, as_stream(stream),
+                     (const double2 *)P, ld, (long long)t_begin, n, n_g, tl->delta,
                      tl->df, (int)tl->paired, omega, n_w, eta, pref, (const double2 *)u,
                      (const double2 *)v, w_bar, (double2 *)rho_bar);
   TDX_HIP(hipGetLastError());
