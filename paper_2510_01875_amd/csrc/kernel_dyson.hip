@@ -6,8 +6,8 @@
 // the local kernel f_xc(n) = d^2(n eps_xc)/dn^2 (Slater exchange + PW92
 // correlation, Phys. Rev. B 45, 13244 (1992)), and
 //   f_xc(G) = (1/N_r) sum_j f_xc(r_j) e^{-i G.r_j}.
-// Both transforms are separable DFTs (three passes of 1D pencil sums with a
-// twiddle table) on a box held in LDS.
+// Both transforms are separable DFTs (three passes of 1D pencil sums on the
+// FP64 MFMA) on a box held in LDS.
 //
 // Dyson: chi = chi0 + chi0 K chi, column G0 by LU with partial pivoting of
 // (1 - chi0 K), one workgroup per frequency.
@@ -26,37 +26,177 @@ namespace {
 constexpr int kMaxSide = 32;
 constexpr double kOccSkip = 1e-20;
 
-// One pass of 1D DFTs along `axis` of an N0 x N1 x N2 box in LDS (in place:
-// each thread owns whole pencils).  sign = +1: sum_m x_m e^{+2 pi i m j/N}.
-__device__ void dft_pass(double2 *box, const double2 *tw, int N0, int N1, int N2, int axis,
-                         double sign) {
-  const int Na = axis == 0 ? N0 : (axis == 1 ? N1 : N2);
-  const int npen = N0 * N1 * N2 / Na;
-  const int stride = axis == 0 ? N1 * N2 : (axis == 1 ? N2 : 1);
-  for (int p = threadIdx.x; p < npen; p += blockDim.x) {
-    int base;
-    if (axis == 0) {
-      base = p;  // p = i1 * N2 + i2
-    } else if (axis == 1) {
-      base = (p / N2) * N1 * N2 + (p % N2);
-    } else {
-      base = p * N2;
+// Places on an axis of N points: the first c of them are used, all (c = N) or
+// the c = 2 M + 1 with |m| <= M, 0 .. M and then -M .. -1.
+__device__ inline int dft_place(int i, int c, int N) {
+  return c == N || i <= (c - 1) / 2 ? i : N - c + i;
+}
+
+// The pencils along one axis of a box: nin places to nout places, for the
+// pencils at c_hi x c_lo places of the two other axes.
+struct DftPass {
+  int N, stride, nin, nout;
+  int n_hi, s_hi, c_hi, n_lo, s_lo, c_lo;
+  const double2 *tw;
+};
+
+typedef double dft_f64x4 __attribute__((ext_vector_type(4)));
+
+// One pass, in place: y_j = sum_m x_m e^{sign 2 pi i m j / N}.  16 pencils are
+// one product on the FP64 MFMA, its matrix the real one of (re, im) rows and
+// columns (rows past 2 nout and columns past 2 nin are padding), built from the
+// twiddle table as the sum goes; a wave reads its pencils whole before it
+// writes them.  kRows = ceil(2 nout / 16) tiles of rows, two tiles of pencils
+// at a time.
+template <int kRows>
+__device__ void dft_rows(double *box, const DftPass &d, double sign) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int col = lane & 15, quad = lane >> 4;
+  const int pencils = d.c_hi * d.c_lo, steps = (d.nin + 1) / 2;
+  const unsigned inv = (65536u + d.N - 1) / d.N;  // x / N for x < 1024
+  int jo[kRows];
+  bool live[kRows];
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    const int i = (16 * r + col) >> 1;
+    live[r] = i < d.nout;
+    jo[r] = dft_place(std::min(i, d.nout - 1), d.nout, d.N);
+  }
+  const bool cross = (col ^ quad) & 1;  // re from im or im from re
+  const double s = cross ? (col & 1 ? sign : -sign) : 1.0;
+  for (int p0 = wave * 32; p0 < pencils; p0 += waves * 32) {
+    int base[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int p = std::min(p0 + 16 * x + col, pencils - 1);
+      base[x] = 2 * (dft_place(p / d.c_lo, d.c_hi, d.n_hi) * d.s_hi +
+                     dft_place(p % d.c_lo, d.c_lo, d.n_lo) * d.s_lo);
     }
-    double2 v[kMaxSide];
-    for (int m = 0; m < Na; ++m) v[m] = box[base + m * stride];
-    for (int j = 0; j < Na; ++j) {
-      double re = 0.0, im = 0.0;
-      int idx = 0;  // (m * j) mod Na
-      for (int m = 0; m < Na; ++m) {
-        const double2 t = tw[idx];
-        const double ti = sign * t.y;
-        re = fma(v[m].x, t.x, fma(-v[m].y, ti, re));
-        im = fma(v[m].x, ti, fma(v[m].y, t.x, im));
-        idx += j;
-        if (idx >= Na) idx -= Na;
+    const bool two = p0 + 16 < pencils;
+    dft_f64x4 y[2][kRows];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) y[x][r] = dft_f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int k = 0; k < steps; ++k) {
+      const int i = 2 * k + (quad >> 1);
+      const bool in = i < d.nin;
+      const int m = dft_place(std::min(i, d.nin - 1), d.nin, d.N);
+      const int at = 2 * m * d.stride + (quad & 1);
+      const double b0 = box[base[0] + at], b1 = box[base[1] + at];
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        const unsigned mj = m * jo[r];
+        const double2 t = d.tw[mj - (mj * inv >> 16) * d.N];
+        const double a = in && live[r] ? s * (cross ? t.y : t.x) : 0.0;
+        y[0][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b0, y[0][r], 0, 0, 0);
+        if (two) y[1][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b1, y[1][r], 0, 0, 0);
       }
-      box[base + j * stride] = make_double2(re, im);
     }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int r = 0; r < kRows; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int row = 16 * r + quad + 4 * e, i = row >> 1;
+          if (i < d.nout && p0 + 16 * x + col < pencils)
+            box[base[x] + 2 * dft_place(i, d.nout, d.N) * d.stride + (row & 1)] = y[x][r][e];
+        }
+  }
+}
+
+// DFT of a box in LDS (workgroup of whole waves): sign = +1 from the used
+// places (act) of each axis to all, sign = -1 from all to the used ones.  A
+// basis of plane waves with |m| <= M takes up (2 M + 1)^3 of the N^3 places, so
+// the first pass has fewer pencils, and each a shorter sum.
+__device__ void dft_box(double2 *box, const double2 *tw, const int (&N)[3], const int (&act)[3],
+                        double sign) {
+  for (int step = 0; step < 3; ++step) {
+    const int axis = sign > 0 ? 2 - step : step;
+    DftPass d;
+    d.N = axis == 0 ? N[0] : axis == 1 ? N[1] : N[2];
+    const int c = axis == 0 ? act[0] : axis == 1 ? act[1] : act[2];
+    d.stride = axis == 0 ? N[1] * N[2] : axis == 1 ? N[2] : 1;
+    d.nin = sign > 0 ? c : d.N;
+    d.nout = sign > 0 ? d.N : c;
+    d.n_hi = axis == 0 ? N[1] : N[0];
+    d.s_hi = axis == 0 ? N[2] : N[1] * N[2];
+    d.c_hi = axis == 0 ? N[1] : act[0];
+    d.n_lo = axis == 2 ? N[1] : N[2];
+    d.s_lo = axis == 2 ? N[2] : 1;
+    d.c_lo = axis == 2 ? act[1] : N[2];
+    d.tw = tw + (axis == 0 ? 0 : axis == 1 ? N[0] : N[0] + N[1]);
+    if (d.nout <= 8)
+      dft_rows<1>((double *)box, d, sign);
+    else if (d.nout <= 16)
+      dft_rows<2>((double *)box, d, sign);
+    else if (d.nout <= 24)
+      dft_rows<3>((double *)box, d, sign);
+    else
+      dft_rows<4>((double *)box, d, sign);
+    __syncthreads();
+  }
+}
+
+// Places that a basis uses on each axis (all where its reach wraps round);
+// box: scratch in LDS.  Ends behind a barrier.
+__device__ void dft_reach(const int *mk, int np, const int (&N)[3], int *box, int (&act)[3]) {
+  if (threadIdx.x < 3) box[threadIdx.x] = 0;
+  __syncthreads();
+  int far[3] = {0, 0, 0};
+  for (int i = threadIdx.x; i < np; i += blockDim.x)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) far[a] = std::max(far[a], std::abs(mk[3 * i + a]));
+#pragma unroll
+  for (int a = 0; a < 3; ++a) atomicMax(&box[a], far[a]);
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < 3; ++a) act[a] = 2 * (long)box[a] + 1 < N[a] ? 2 * box[a] + 1 : N[a];
+  __syncthreads();
+}
+
+__device__ inline int dft_spot(const int *m, const int (&N)[3]) {
+  const int a = ((m[0] % N[0]) + N[0]) % N[0];
+  const int b = ((m[1] % N[1]) + N[1]) % N[1];
+  const int d = ((m[2] % N[2]) + N[2]) % N[2];
+  return (a * N[1] + b) * N[2] + d;
+}
+
+// The orbitals of a workgroup's bands (n0, n0 + by, .. < nb with occupation),
+// one after the other as u(r) on the box: f(n, occupation).  The next one's
+// coefficients are on their way meanwhile.
+template <typename F>
+__device__ void each_orbital(double2 *box, const double2 *tw, const int (&N)[3],
+                             const int (&act)[3], const double2 *coef, const double *occ,
+                             const int *mk, int n0, int by, int nb, int np, int npw_max, F f) {
+  const int tid = threadIdx.x;
+  auto first = [&](int n) {
+    return n < nb && tid < np ? coef[(size_t)n * npw_max + tid] : make_double2(0.0, 0.0);
+  };
+  double o = n0 < nb ? occ[n0] : 0.0;
+  double2 c = first(n0);
+  const int spot = tid < np ? dft_spot(mk + 3 * tid, N) : 0;
+  for (int n = n0; n < nb; n += by) {
+    const double on = n + by < nb ? occ[n + by] : 0.0;
+    const double2 cn = first(n + by);
+    if (o >= kOccSkip) {
+      for (int j = tid; j < act[0] * act[1] * act[2]; j += blockDim.x) {
+        const int a = dft_place(j / (act[1] * act[2]), act[0], N[0]);
+        const int b = dft_place(j / act[2] % act[1], act[1], N[1]);
+        box[(a * N[1] + b) * N[2] + dft_place(j % act[2], act[2], N[2])] = make_double2(0.0, 0.0);
+      }
+      __syncthreads();
+      if (tid < np) box[spot] = c;
+      for (int i = tid + blockDim.x; i < np; i += blockDim.x)
+        box[dft_spot(mk + 3 * i, N)] = coef[(size_t)n * npw_max + i];
+      __syncthreads();
+      dft_box(box, tw, N, act, 1.0);
+      f(n, o);
+      __syncthreads();
+    }
+    o = on;
+    c = cn;
   }
 }
 
@@ -74,46 +214,66 @@ __device__ void make_twiddles(double2 *tw, int N0, int N1, int N2) {
   }
 }
 
-// Per-k density partial: dens[k][j] = sum_n f_nk |u_nk(r_j)|^2.
-__global__ void __launch_bounds__(256)
+constexpr int kDensThreads = 512;
+constexpr int kDensPoints = 160 * 1024 / 16 / kDensThreads;  // per thread, of what LDS holds
+
+// Workgroups per k: about four per CU in all, each a share of the bands.
+inline int dens_slices(int n_k, int n_cu) {
+  return std::max(1, std::min(16, (4 * n_cu + n_k - 1) / std::max(n_k, 1)));
+}
+
+// Density partials: dens[k][slice][j] = sum_n f_nk |u_nk(r_j)|^2 over the bands
+// n = slice, slice + slices, ..  Grid (n_k, slices).  FP64 issue is the bound.
+// 64 k of up to 480 plane waves (reach 5) on a 20^3 grid: 4928 us with one
+// workgroup per k, a thread per pencil (its values in scratch memory) and all
+// places summed; 267 us.
+__global__ void __launch_bounds__(kDensThreads)
     k_density(const double2 *coef, const double *occ, const int *nb, const int *npw,
               const int *miller, int nb_max, int npw_max, int N0, int N1, int N2,
               double *dens) {
   extern __shared__ double2 sm[];
-  const int Nr = N0 * N1 * N2;
+  const int N[3] = {N0, N1, N2}, Nr = N0 * N1 * N2;
   double2 *box = sm;
   double2 *tw = sm + Nr;
-  const int k = blockIdx.x;
-  make_twiddles(tw, N0, N1, N2);
-  double *out = dens + (size_t)k * Nr;
-  for (int j = threadIdx.x; j < Nr; j += blockDim.x) out[j] = 0.0;
-  const int nbk = nb[k], np = npw[k];
+  const int k = blockIdx.x, np = npw[k];
   const int *mk = miller + (size_t)k * npw_max * 3;
-  for (int n = 0; n < nbk; ++n) {
-    const double f = occ[(size_t)k * nb_max + n];
-    if (!(f >= kOccSkip)) continue;
-    __syncthreads();
-    for (int j = threadIdx.x; j < Nr; j += blockDim.x) box[j] = make_double2(0.0, 0.0);
-    __syncthreads();
-    const double2 *c = coef + ((size_t)k * nb_max + n) * npw_max;
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-      const int a = ((mk[3 * i] % N0) + N0) % N0;
-      const int b = ((mk[3 * i + 1] % N1) + N1) % N1;
-      const int d = ((mk[3 * i + 2] % N2) + N2) % N2;
-      box[(a * N1 + b) * N2 + d] = c[i];
-    }
-    __syncthreads();
-    dft_pass(box, tw + N0 + N1, N0, N1, N2, 2, 1.0);
-    __syncthreads();
-    dft_pass(box, tw + N0, N0, N1, N2, 1, 1.0);
-    __syncthreads();
-    dft_pass(box, tw, N0, N1, N2, 0, 1.0);
-    __syncthreads();
-    for (int j = threadIdx.x; j < Nr; j += blockDim.x) {
-      const double2 u = box[j];
-      out[j] = fma(f, u.x * u.x + u.y * u.y, out[j]);
-    }
+  int act[3];
+  make_twiddles(tw, N0, N1, N2);
+  dft_reach(mk, np, N, (int *)box, act);
+  double sum[kDensPoints];
+#pragma unroll
+  for (int i = 0; i < kDensPoints; ++i) sum[i] = 0.0;
+  each_orbital(box, tw, N, act, coef + (size_t)k * nb_max * npw_max, occ + (size_t)k * nb_max, mk,
+               blockIdx.y, gridDim.y, nb[k], np, npw_max, [&](int, double f) {
+#pragma unroll
+                 for (int i = 0; i < kDensPoints; ++i) {
+                   const int j = threadIdx.x + i * kDensThreads;
+                   if (j < Nr) {
+                     const double2 u = box[j];
+                     sum[i] = fma(f, u.x * u.x + u.y * u.y, sum[i]);
+                   }
+                 }
+               });
+  double *out = dens + ((size_t)k * gridDim.y + blockIdx.y) * Nr;
+#pragma unroll
+  for (int i = 0; i < kDensPoints; ++i) {
+    const int j = threadIdx.x + i * kDensThreads;
+    if (j < Nr) out[j] = sum[i];
   }
+}
+
+// Sum of n partials [n][Nr] at point j = 32 block + (thread & 31), for the
+// first 32 of 256 threads: eight strided sums, then those in order.
+__device__ double sum_partials(const double *dens, int n, int Nr, int j) {
+  __shared__ double part[8][32];
+  const int lane = threadIdx.x & 31, row = threadIdx.x >> 5;
+  double s = 0.0;
+  if (j < Nr)
+    for (int k = row; k < n; k += 8) s += dens[(size_t)k * Nr + j];
+  part[row][lane] = s;
+  __syncthreads();
+  for (int i = 1; i < 8; ++i) s += part[i][lane];  // row 0 holds its own
+  return s;
 }
 
 __device__ void pw92(double rs, double *e, double *e1, double *e2) {
@@ -133,12 +293,12 @@ __device__ void pw92(double rs, double *e, double *e1, double *e2) {
   *e2 = -4 * A * a1 * L1 + g * L2;
 }
 
-// Sum the per-k partials in k order, scale, apply f_xc(n) pointwise.
-__global__ void k_fxc_real(const double *dens, int nk, int Nr, double scale, double2 *fx) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= Nr) return;
-  double s = 0.0;
-  for (int k = 0; k < nk; ++k) s += dens[(size_t)k * Nr + j];
+// Sum the density partials, scale, apply f_xc(n) pointwise; 32 points a block.
+__global__ void __launch_bounds__(256)
+    k_fxc_real(const double *dens, int parts, int Nr, double scale, double2 *fx) {
+  const int j = blockIdx.x * 32 + (threadIdx.x & 31);
+  const double s = sum_partials(dens, parts, Nr, j);
+  if (threadIdx.x >= 32 || j >= Nr) return;
   const double n = s * scale;
   const double fxv = -(1.0 / 3.0) * cbrt(3.0 / M_PI) * pow(n, -2.0 / 3.0);
   const double rs = cbrt(3.0 / (4.0 * M_PI * n));
@@ -183,21 +343,17 @@ __device__ double fxc_deriv(double n) {
   return dx + dc;
 }
 
-// Forward transform of f_xc on the box (one workgroup), scaled by 1/N_r.
-__global__ void __launch_bounds__(256)
+// Forward transform of f_xc on the box (one workgroup), scaled by 1/N_r: 46 us
+// at 20^3 (316 us with a thread per pencil).
+__global__ void __launch_bounds__(kDensThreads)
     k_fxc_forward(double2 *fx, int N0, int N1, int N2) {
   extern __shared__ double2 sm[];
-  const int Nr = N0 * N1 * N2;
+  const int N[3] = {N0, N1, N2}, Nr = N0 * N1 * N2;
   double2 *box = sm, *tw = sm + Nr;
   make_twiddles(tw, N0, N1, N2);
   for (int j = threadIdx.x; j < Nr; j += blockDim.x) box[j] = fx[j];
   __syncthreads();
-  dft_pass(box, tw + N0 + N1, N0, N1, N2, 2, -1.0);
-  __syncthreads();
-  dft_pass(box, tw + N0, N0, N1, N2, 1, -1.0);
-  __syncthreads();
-  dft_pass(box, tw, N0, N1, N2, 0, -1.0);
-  __syncthreads();
+  dft_box(box, tw, N, N, -1.0);
   const double inv = 1.0 / Nr;
   for (int j = threadIdx.x; j < Nr; j += blockDim.x)
     fx[j] = make_double2(box[j].x * inv, box[j].y * inv);
@@ -1335,86 +1491,63 @@ __global__ void k_fbar(const double2 *Phi, const double2 *T, int n_g, int Nr, do
   fbar[j] += re / Nr;
 }
 
-// nbar[j] = fbar[j] f_xc'(n(r_j)), n from the per-k partials in k order.
-__global__ void k_nbar(const double *dens, int nk, int Nr, double scale, const double *fbar,
-                       double *nbar) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= Nr) return;
-  double s = 0.0;
-  for (int k = 0; k < nk; ++k) s += dens[(size_t)k * Nr + j];
+// nbar[j] = fbar[j] f_xc'(n(r_j)), n from the density partials; 32 points a block.
+__global__ void __launch_bounds__(256)
+    k_nbar(const double *dens, int parts, int Nr, double scale, const double *fbar,
+           double *nbar) {
+  const int j = blockIdx.x * 32 + (threadIdx.x & 31);
+  const double s = sum_partials(dens, parts, Nr, j);
+  if (threadIdx.x >= 32 || j >= Nr) return;
   nbar[j] = fbar[j] * fxc_deriv(s * scale);
 }
 
-// Density adjoint per k (the bands the forward density summed):
+// Density adjoint of the bands n = slice, slice + slices, .. of a k (those the
+// forward density summed); grid (n_k, slices):
 //   occ_bar[k][n] += scale sum_j nbar_j |u_nk(r_j)|^2,
 //   coef_bar[k][n](G) += 2 scale f_nk sum_j nbar_j u_nk(r_j) e^{-i G.r_j}
 // (the second a forward transform of nbar u on the box, read at the basis).
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kDensThreads)
     k_density_vjp(const double2 *coef, const double *occ, const int *nb, const int *npw,
                   const int *miller, int nb_max, int npw_max, int N0, int N1, int N2,
                   double scale, const double *nbar, double *occ_bar, double2 *coef_bar) {
   extern __shared__ double2 sm[];
-  __shared__ double red[256];
-  const int Nr = N0 * N1 * N2;
+  __shared__ double red[kDensThreads / 64];
+  const int N[3] = {N0, N1, N2}, Nr = N0 * N1 * N2;
   double2 *box = sm;
   double2 *tw = sm + Nr;
-  const int k = blockIdx.x;
-  make_twiddles(tw, N0, N1, N2);
-  const int nbk = nb[k], np = npw[k];
+  const int k = blockIdx.x, np = npw[k];
   const int *mk = miller + (size_t)k * npw_max * 3;
-  for (int n = 0; n < nbk; ++n) {
-    const double f = occ[(size_t)k * nb_max + n];
-    if (!(f >= kOccSkip)) continue;
-    __syncthreads();
-    for (int j = threadIdx.x; j < Nr; j += blockDim.x) box[j] = make_double2(0.0, 0.0);
-    __syncthreads();
-    const double2 *c = coef + ((size_t)k * nb_max + n) * npw_max;
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-      const int a = ((mk[3 * i] % N0) + N0) % N0;
-      const int b = ((mk[3 * i + 1] % N1) + N1) % N1;
-      const int d = ((mk[3 * i + 2] % N2) + N2) % N2;
-      box[(a * N1 + b) * N2 + d] = c[i];
-    }
-    __syncthreads();
-    dft_pass(box, tw + N0 + N1, N0, N1, N2, 2, 1.0);
-    __syncthreads();
-    dft_pass(box, tw + N0, N0, N1, N2, 1, 1.0);
-    __syncthreads();
-    dft_pass(box, tw, N0, N1, N2, 0, 1.0);
-    __syncthreads();
-    double s = 0.0;
-    for (int j = threadIdx.x; j < Nr; j += blockDim.x) {
-      const double2 u = box[j];
-      const double w = nbar[j];
-      s = fma(w, u.x * u.x + u.y * u.y, s);
-      box[j] = make_double2(w * u.x, w * u.y);
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-      if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) occ_bar[(size_t)k * nb_max + n] += scale * red[0];
-    if (coef_bar) {
-      dft_pass(box, tw + N0 + N1, N0, N1, N2, 2, -1.0);
-      __syncthreads();
-      dft_pass(box, tw + N0, N0, N1, N2, 1, -1.0);
-      __syncthreads();
-      dft_pass(box, tw, N0, N1, N2, 0, -1.0);
-      __syncthreads();
-      double2 *cb = coef_bar + ((size_t)k * nb_max + n) * npw_max;
-      const double g = 2.0 * scale * f;
-      for (int i = threadIdx.x; i < np; i += blockDim.x) {
-        const int a = ((mk[3 * i] % N0) + N0) % N0;
-        const int b = ((mk[3 * i + 1] % N1) + N1) % N1;
-        const int d = ((mk[3 * i + 2] % N2) + N2) % N2;
-        const double2 v = box[(a * N1 + b) * N2 + d];
-        cb[i].x += g * v.x;
-        cb[i].y += g * v.y;
-      }
-    }
-  }
+  int act[3];
+  make_twiddles(tw, N0, N1, N2);
+  dft_reach(mk, np, N, (int *)box, act);
+  each_orbital(
+      box, tw, N, act, coef + (size_t)k * nb_max * npw_max, occ + (size_t)k * nb_max, mk,
+      blockIdx.y, gridDim.y, nb[k], np, npw_max, [&](int n, double f) {
+        double s = 0.0;
+        for (int j = threadIdx.x; j < Nr; j += kDensThreads) {
+          const double2 u = box[j];
+          const double w = nbar[j];
+          s = fma(w, u.x * u.x + u.y * u.y, s);
+          box[j] = make_double2(w * u.x, w * u.y);
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+          for (int i = 1; i < kDensThreads / 64; ++i) s += red[i];
+          occ_bar[(size_t)k * nb_max + n] += scale * s;
+        }
+        if (!coef_bar) return;
+        dft_box(box, tw, N, act, -1.0);
+        double2 *cb = coef_bar + ((size_t)k * nb_max + n) * npw_max;
+        const double g = 2.0 * scale * f;
+        for (int i = threadIdx.x; i < np; i += kDensThreads) {
+          const double2 v = box[dft_spot(mk + 3 * i, N)];
+          cb[i].x += g * v.x;
+          cb[i].y += g * v.y;
+        }
+      });
 }
 
 // First failing frequency of a chunk of LU solves folded into the running
@@ -1551,21 +1684,23 @@ int tdx_xc_kernel_grid(tdx_ctx *ctx, const tdx_states *st, const int dens_grid[3
   hipStream_t s = as_stream(stream);
   const int N0 = dens_grid[0], N1 = dens_grid[1], N2 = dens_grid[2];
   void *w;
-  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * (size_t)st->n_k * Nr, &w));
+  const int slices = dens_slices(st->n_k, ctx->n_cu), parts = st->n_k * slices;
+  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * (size_t)parts * Nr, &w));
   double *dens = (double *)w;
   TDX_HIP(hipFuncSetAttribute((const void *)k_density, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds));
   TDX_HIP(hipFuncSetAttribute((const void *)k_fxc_forward,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(k_density, dim3(st->n_k), dim3(256), lds, s, (const double2 *)st->coef,
+  hipLaunchKernelGGL(k_density, dim3(st->n_k, slices), dim3(kDensThreads), lds, s, (const double2 *)st->coef,
                      st->occ, st->nb, st->npw, st->miller, st->nb_max, st->npw_max, N0, N1, N2,
                      dens);
   TDX_HIP(hipGetLastError());
   const double scale = 2.0 / (st->n_k * st->omega_cell);
-  hipLaunchKernelGGL(k_fxc_real, dim3((Nr + 255) / 256), dim3(256), 0, s, dens, st->n_k, Nr,
-                     scale, (double2 *)fxg);
+  hipLaunchKernelGGL(k_fxc_real, dim3((Nr + 31) / 32), dim3(256), 0, s, dens, parts, Nr, scale,
+                     (double2 *)fxg);
   TDX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_fxc_forward, dim3(1), dim3(256), lds, s, (double2 *)fxg, N0, N1, N2);
+  hipLaunchKernelGGL(k_fxc_forward, dim3(1), dim3(kDensThreads), lds, s, (double2 *)fxg, N0, N1,
+                     N2);
   TDX_HIP(hipGetLastError());
   TDX_HIP(hipStreamSynchronize(s));  // the density workspace may be reused after return
   return TDX_OK;
@@ -1768,21 +1903,22 @@ int tdx_density_vjp(tdx_ctx *ctx, const tdx_states *st, const int dens_grid[3],
   hipStream_t s = as_stream(stream);
   const int N0 = dens_grid[0], N1 = dens_grid[1], N2 = dens_grid[2];
   void *w;
-  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * ((size_t)st->n_k + 1) * Nr, &w));
-  double *dens = (double *)w, *nbar = dens + (size_t)st->n_k * Nr;
+  const int slices = dens_slices(st->n_k, ctx->n_cu), parts = st->n_k * slices;
+  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * ((size_t)parts + 1) * Nr, &w));
+  double *dens = (double *)w, *nbar = dens + (size_t)parts * Nr;
   TDX_HIP(hipFuncSetAttribute((const void *)k_density, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds));
   TDX_HIP(hipFuncSetAttribute((const void *)k_density_vjp,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(k_density, dim3(st->n_k), dim3(256), lds, s, (const double2 *)st->coef,
+  hipLaunchKernelGGL(k_density, dim3(st->n_k, slices), dim3(kDensThreads), lds, s, (const double2 *)st->coef,
                      st->occ, st->nb, st->npw, st->miller, st->nb_max, st->npw_max, N0, N1, N2,
                      dens);
   TDX_HIP(hipGetLastError());
   const double scale = 2.0 / (st->n_k * st->omega_cell);
-  hipLaunchKernelGGL(k_nbar, dim3((Nr + 255) / 256), dim3(256), 0, s, dens, st->n_k, Nr, scale,
-                     fxc_bar, nbar);
+  hipLaunchKernelGGL(k_nbar, dim3((Nr + 31) / 32), dim3(256), 0, s, dens, parts, Nr, scale, fxc_bar,
+                     nbar);
   TDX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_density_vjp, dim3(st->n_k), dim3(256), lds, s, (const double2 *)st->coef,
+  hipLaunchKernelGGL(k_density_vjp, dim3(st->n_k, slices), dim3(kDensThreads), lds, s, (const double2 *)st->coef,
                      st->occ, st->nb, st->npw, st->miller, st->nb_max, st->npw_max, N0, N1, N2,
                      scale, nbar, occ_bar, (double2 *)coef_bar);
   TDX_HIP(hipGetLastError());
