@@ -1,0 +1,118 @@
+"""The density of the local kernel and its adjoint on seeded synthetic states:
+grid sides around the tiles of 8 outputs and up to the largest, sides that the
+basis fills and sides with room, more plane waves than threads, one k and
+several, empty bands.  Reference: numpy FFTs and the oracle's f_xc, in FP64."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -53
+OMEGA = 50.0
+
+
+@pytest.fixture(scope="module")
+def tdx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_01875_amd as m
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(tdx):
+    c = tdx.Context(0)
+    yield c
+    c.close()
+
+
+def _system(tdx, reach, npw, nb, n_k, seed):
+    import torch
+    rng = np.random.default_rng(seed)
+    d = tdx.StatesDims()
+    d.n_k, d.npw_max, d.nb_max = n_k, npw, nb
+    st = tdx.States(d, 0)
+    box = np.stack(np.meshgrid(*[np.arange(-m, m + 1) for m in reach], indexing="ij"),
+                   -1).reshape(-1, 3)
+    n = [max(1, npw - 2 * k) for k in range(n_k)]
+    mil = np.zeros((n_k, npw, 3), dtype=np.int32)
+    coef = np.zeros((n_k, nb, npw), dtype=np.complex128)
+    for k in range(n_k):
+        mil[k, :n[k]] = rng.permutation(box)[:n[k]]
+        c = rng.standard_normal((nb, n[k])) + 1j * rng.standard_normal((nb, n[k]))
+        coef[k, :, :n[k]] = c / np.sqrt(n[k])
+    occ = rng.uniform(0.2, 1.0, (n_k, nb))
+    occ[:, 2::3] = 0.0
+    for t, x in ((st.npw, np.array(n, dtype=np.int32)), (st.nb, np.full(n_k, nb, dtype=np.int32)),
+                 (st.miller, mil), (st.occ, occ), (st.coef, coef)):
+        t.copy_(torch.from_numpy(x))
+    st.c.kgrid[:] = [n_k, 1, 1]
+    st.c.mmax[:] = list(reach)
+    st.c.omega_cell = OMEGA
+    return st, n, mil, coef, occ
+
+
+# (grid, reach of the basis, plane waves, bands, k)
+CASES = [((1, 1, 1), (0, 0, 0), 1, 4, 1), ((3, 5, 7), (1, 2, 3), 60, 5, 1),
+         ((8, 9, 16), (3, 4, 2), 100, 9, 2), ((17, 15, 24), (3, 7, 5), 300, 7, 3),
+         ((25, 13, 30), (2, 6, 4), 200, 40, 2), ((32, 32, 9), (5, 5, 4), 700, 6, 2),
+         ((9, 9, 32), (4, 4, 15), 1500, 4, 1), ((20, 20, 20), (5, 5, 5), 480, 20, 40)]
+
+
+@pytest.mark.parametrize("grid,reach,npw,nb,n_k", CASES)
+def test_density_and_its_adjoint(tdx, ctx, grid, reach, npw, nb, n_k):
+    import torch
+    from oracle.xc import fxc_alda, fxc_alda_deriv
+    print("dens grid", grid, reach, npw, nb, n_k, flush=True)
+    st, n, mil, coef, occ = _system(tdx, reach, npw, nb, n_k, 7 * npw + n_k)
+    Nr, scale = int(np.prod(grid)), 2.0 / (n_k * OMEGA)
+    # a component of u: 3 passes of at most 32 terms, 4 operations each, on
+    # both sides; relative to sum |c|
+    steps = 2 * 3 * 32 * 4
+    us, size = {}, {}
+    dens, dmag = np.zeros(grid), 0.0
+    for k in range(n_k):
+        idx = tuple(np.mod(mil[k, :n[k]], grid).T)
+        for b in range(nb):
+            box = np.zeros(grid, dtype=np.complex128)
+            box[idx] = coef[k, b, :n[k]]
+            us[k, b], size[k, b] = np.fft.ifftn(box) * Nr, np.abs(coef[k, b]).sum()
+            dens += occ[k, b] * np.abs(us[k, b]) ** 2 * scale
+            dmag += occ[k, b] * size[k, b] ** 2 * scale
+    d_dens = (2 * steps + 2 * n_k * nb) * EPS * dmag  # absolute
+    rel = d_dens / dens + 64 * EPS
+    fx = fxc_alda(dens)
+    ref = np.fft.fftn(fx) / Nr
+    # |d ln f_xc / d ln n| <= 1; the transform's own error
+    tol = np.mean(np.abs(fx) * 2 * rel) + steps * EPS * np.mean(np.abs(fx))
+    got = tdx.xc_kernel_grid(ctx, st, grid).cpu().numpy()
+    assert np.max(np.abs(got - ref)) <= tol
+    rng = np.random.default_rng(3)
+    fbar = rng.standard_normal(grid)
+    nbar = fbar * fxc_alda_deriv(dens)
+    occ0 = rng.standard_normal((n_k, nb))
+    cb0 = rng.standard_normal(coef.shape) + 1j * rng.standard_normal(coef.shape)
+    want_o, want_c = occ0.copy(), cb0.copy()
+    tol_o, tol_c = 4 * EPS * np.abs(occ0), 4 * EPS * np.abs(cb0)
+    for k in range(n_k):
+        idx = tuple(np.mod(mil[k, :n[k]], grid).T)
+        for b in range(nb):
+            if occ[k, b] == 0.0:
+                continue
+            u, s = us[k, b], size[k, b]
+            want_o[k, b] += scale * np.sum(nbar * np.abs(u) ** 2)
+            g = 2 * scale * occ[k, b]
+            want_c[k, b, :n[k]] += g * np.fft.fftn(nbar * u)[idx]
+            # |d ln f_xc' / d ln n| <= 2
+            err = np.abs(nbar) * 2 * 2 * rel
+            tol_o[k, b] += scale * np.sum(err * s * s + np.abs(nbar) * (2 * steps + Nr) * EPS * s * s)
+            tol_c[k, b, :n[k]] += g * np.sum(err * s + np.abs(nbar) * 2 * steps * EPS * s)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    ob, cb = dev(occ0), dev(cb0)
+    tdx.density_vjp(ctx, st, grid, dev(fbar.reshape(-1)), ob, cb)
+    assert np.all(np.abs(ob.cpu().numpy() - want_o) <= tol_o)
+    assert np.all(np.abs(cb.cpu().numpy() - want_c) <= tol_c)
+    ob = dev(occ0)
+    tdx.density_vjp(ctx, st, grid, dev(fbar.reshape(-1)), ob)
+    assert np.all(np.abs(ob.cpu().numpy() - want_o) <= tol_o)
