@@ -147,14 +147,14 @@ __device__ __attribute__((always_inline)) void chi0_tile_fp(
       for (int s = 0; s < C::kSteps; ++s) {
         const int tl = 2 * s + tau;
         const float2 rho = rq[tl * 16 + c16];
+        // a = w rho: its component `comp` for Re chi0, (Im a, -Re a)'s for Im
+        const float x = comp ? rho.y : rho.x, y = comp ? -rho.x : rho.y;
         float a[WPW], r[WPW];
 #pragma unroll
         for (int i = 0; i < WPW; ++i) {
           const float2 w = wt[wt_index<C>(tl, wave * WPW + i)];
-          const float are = w.x * rho.x - w.y * rho.y;
-          const float aim = w.x * rho.y + w.y * rho.x;
-          a[i] = comp ? aim : are;
-          r[i] = comp ? -are : aim;
+          a[i] = fmaf(w.x, x, -(w.y * y));
+          r[i] = fmaf(w.x, y, w.y * x);
         }
 #pragma unroll
         for (int b = 0; b < NSUB; ++b) {
@@ -233,6 +233,214 @@ int launch_fp(const void *P, int ld, const double *delta, const double *df, int 
 }
 
 
+// ------------------------------------------------- all columns in one tile
+// Bases of 17 to 144 vectors.  The rows (w, G) of w_t(w) rho_t(G) are one list
+// of n_w n_g, dealt to the waves in tiles of 16 whatever frequencies these
+// hold, against all columns G': no row is padding, one set of rho rows in LDS
+// (contiguous in memory) serves rows and columns, and a tile of A is formed
+// once for all columns.  The bound is the FP32 MFMA, with which the other
+// vector instructions share the issue (they add to its time, whether or not
+// they are placed between MFMAs): the K-steps of a chunk are unrolled so that
+// LDS addresses cost none (not for 32 columns, whose six row tiles would
+// spill).  The sums run over the same transitions in the same order as in the
+// tiles above, so the results are bitwise those.  N_G 116, 500 frequencies,
+// 100000 paired transitions: 55.9 to 44.8 ms (120 TFLOP/s without the padding
+// of the columns, 133 with it; a large sgemm reaches 151); N_G 60, 200
+// frequencies: 87 to 118 TFLOP/s; N_G 20, 300 frequencies: 40 to 65.  More
+// columns leave a wave too few accumulators per row tile, and their padding
+// is small.
+constexpr int kFlatChunk = 32;
+constexpr long long kRun = 4096;  // transitions summed in FP32 between folds
+
+// Frequencies that 64 R rows (w, G), w n_g + G, of a workgroup touch, at most
+// (n_g > 16 (NSUB - 1)).
+template <int R, int NSUB>
+constexpr int flat_freqs() {
+  return (64 * R - 1) / (16 * (NSUB - 1) + 1) + 2;
+}
+
+template <int R, int NSUB, bool PAIRED>
+__global__ void __launch_bounds__(256, 2)
+    k_chi0_fp_rows(const void *P, const double *delta, const double *df, long long n_trans,
+                   long long slice_len, const double *omega, int n_w, double eta, int n_g,
+                   double2 *part) {
+  constexpr int kF = flat_freqs<R, NSUB>(), kLd = 16 * NSUB, kSteps = kFlatChunk / 2;
+  constexpr int kPer = (kF * kFlatChunk + 255) / 256, kBytes = kFlatChunk * kLd * 8;
+  constexpr int kUnroll = NSUB > 2 ? kSteps : 2;
+  extern __shared__ float2 flat_lds[];  // two chunks of rows, two of weights
+  float2 *wts = flat_lds + 2 * kFlatChunk * kLd;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tau = lane >> 5, comp = (lane >> 4) & 1, c16 = lane & 15;
+  const int L = xcd_logical(blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y);
+  const long long rows = (long long)n_w * n_g, row0 = (long long)(L % gridDim.x) * 64 * R;
+  const int sl = L / gridDim.x;
+  const long long t_lo = sl * slice_len, t_hi = std::min(n_trans, t_lo + slice_len);
+  part += (size_t)sl * rows * n_g;
+  const int wf = (int)(row0 / n_g);
+  // this lane's row of each tile: its vector and its frequency's place
+  int g[R], f[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    const long long x = std::min(row0 + 16 * (wave * R + i) + c16, rows - 1);
+    f[i] = (int)(x / n_g) - wf;
+    g[i] = (int)(x % n_g);
+  }
+  // this thread's weights of a chunk: number e = tid + 256 i is frequency
+  // e % kF of transition e / kF
+  const double e2 = eta * eta;
+  const float etaf = (float)eta;
+  double om[kPer], wd[kPer], wv[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) om[i] = omega[std::min(wf + (tid + 256 * i) % kF, n_w - 1)];
+  auto load_w = [&](long long tc) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const long long t = std::min(tc + std::min((tid + 256 * i) / kF, kFlatChunk - 1), n_trans - 1);
+      wd[i] = delta[t];
+      wv[i] = df[t];
+    }
+  };
+  // the arithmetic of store_weights (chi0_tile.h)
+  auto store_w = [&](float2 *w, long long tc) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int e = tid + 256 * i;
+      if (e >= kF * kFlatChunk) break;
+      float2 v;
+      if constexpr (PAIRED) {
+        const float dr = (float)fma(om[i] - wd[i], om[i] + wd[i], -e2);
+        const float di = (float)(2.0 * om[i] * eta);
+        const float sc =
+            (float)(2.0 * wv[i] * wd[i]) * __builtin_amdgcn_rcpf(fmaf(dr, dr, di * di));
+        v = make_float2(sc * dr, -sc * di);
+      } else {
+        const float x = (float)(om[i] - wd[i]);
+        const float sc = (float)wv[i] * __builtin_amdgcn_rcpf(fmaf(x, x, etaf * etaf));
+        v = make_float2(sc * x, -sc * etaf);
+      }
+      w[e] = tc + e / kF < t_hi ? v : make_float2(0.f, 0.f);
+    }
+  };
+  // a chunk's rows are contiguous: 1 KB pieces dealt to the waves in turn
+  // (past the list the last bytes again: their weights are zero)
+  const char *Pb = (const char *)P;
+  const long long end = n_trans * kLd * 8 - 16;
+  auto copy = [&](float2 *dst, long long tc) {
+#pragma unroll
+    for (int i = 0; i < kBytes / 4096; ++i) {
+      const int o = 4096 * i + 1024 * wave;
+      dma16(Pb + std::min(tc * kLd * 8 + o + 16 * lane, end),
+            (unsigned int *)((char *)dst + o));
+    }
+  };
+  f32x4 ar[R][NSUB], ai[R][NSUB];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int b = 0; b < NSUB; ++b) ar[i][b] = ai[i][b] = f32x4{0, 0, 0, 0};
+  copy(flat_lds, t_lo);
+  load_w(t_lo);
+  store_w(wts, t_lo);
+  wait_vm();
+  __syncthreads();
+  int cur = 0;
+  bool first = true;
+  for (long long rs = t_lo; rs < t_hi; rs += kRun) {
+    const long long re = std::min(t_hi, rs + kRun);
+    for (long long tc = rs; tc < re; tc += kFlatChunk) {
+      const long long nx = tc + kFlatChunk;
+      const bool more = nx < t_hi;
+      if (more) {
+        load_w(nx);
+        copy(flat_lds + (cur ^ 1) * kFlatChunk * kLd, nx);
+      }
+      // K-step s: this lane's transition 2 s + tau
+      const float2 *rq = flat_lds + cur * kFlatChunk * kLd + tau * kLd;
+      const float2 *wq = wts + cur * kFlatChunk * kF + tau * kF;
+      const float *bq = (const float *)rq + 2 * c16 + comp;
+      float2 rho[R], w[R];
+      float bv[NSUB];
+      auto read = [&](int s) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          rho[i] = rq[2 * s * kLd + g[i]];
+          w[i] = wq[2 * s * kF + f[i]];
+        }
+#pragma unroll
+        for (int b = 0; b < NSUB; ++b) bv[b] = bq[4 * s * kLd + 32 * b];
+      };
+      read(0);
+#pragma unroll kUnroll
+      for (int s = 0; s < kSteps; ++s) {
+        // a = w rho: its component `comp` for Re chi0, and (Im a, -Re a)'s
+        float a[R], q[R], x[NSUB];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          const float u = comp ? rho[i].y : rho[i].x, v = comp ? -rho[i].x : rho[i].y;
+          a[i] = fmaf(w[i].x, u, -(w[i].y * v));
+          q[i] = fmaf(w[i].x, v, w[i].y * u);
+        }
+#pragma unroll
+        for (int b = 0; b < NSUB; ++b) x[b] = bv[b];
+        read((s + 1) % kSteps);
+#pragma unroll
+        for (int b = 0; b < NSUB; ++b)
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+            ar[i][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], x[b], ar[i][b], 0, 0, 0);
+            ai[i][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(q[i], x[b], ai[i][b], 0, 0, 0);
+          }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (more) store_w(wts + (cur ^ 1) * kFlatChunk * kF, nx);
+      wait_vm();
+      __syncthreads();
+      cur ^= 1;
+    }
+    // into the slice's FP64 partial, [w][G][G'] = [row][G'] (element j of a
+    // lane is row 4 (lane / 16) + j, column lane % 16)
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int b = 0; b < NSUB; ++b) {
+        const int col = 16 * b + c16;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const long long row = row0 + 16 * (wave * R + i) + 4 * (lane >> 4) + j;
+          if (row < rows && col < n_g) {
+            double2 *d = part + row * n_g + col;
+            double2 v = make_double2((double)ar[i][b][j], (double)ai[i][b][j]);
+            if (!first) {
+              const double2 o = *d;
+              v.x += o.x;
+              v.y += o.y;
+            }
+            *d = v;
+          }
+        }
+        ar[i][b] = ai[i][b] = f32x4{0, 0, 0, 0};
+      }
+    first = false;
+  }
+}
+
+template <int R, int NSUB>
+int launch_rows(const void *P, const double *delta, const double *df, int paired,
+                long long n_trans, long long slice_len, int slices, const double *omega, int n_w,
+                double eta, int n_g, double2 *part, hipStream_t s) {
+  const void *fn = paired ? (const void *)k_chi0_fp_rows<R, NSUB, true>
+                          : (const void *)k_chi0_fp_rows<R, NSUB, false>;
+  const size_t lds = 2 * sizeof(float2) * kFlatChunk * (16 * NSUB + flat_freqs<R, NSUB>());
+  const long long tiles = ((long long)n_w * n_g + 64 * R - 1) / (64 * R);
+  TDX_REQUIRE(tiles * slices < (1LL << 31), TDX_ERR_SHAPE, "too many tiles");
+  TDX_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  void *args[] = {(void *)&P,     (void *)&delta, (void *)&df,  (void *)&n_trans, (void *)&slice_len,
+                  (void *)&omega, (void *)&n_w,   (void *)&eta, (void *)&n_g,     (void *)&part};
+  TDX_HIP(hipLaunchKernel(fn, dim3((unsigned)tiles, (unsigned)slices), dim3(256), args, lds, s));
+  return TDX_OK;
+}
+
 // Tile variants: (frequencies per wave, column blocks, transitions per
 // chunk); variant 0 is the default.
 struct FpVariant {
@@ -259,10 +467,27 @@ void chi0_fp32_shape(int v, int *wblock, int *cols, int *chunk) {
   *chunk = V.chunk;
 }
 
+// The launch of a basis of 17 to 144 vectors does not depend on the variant,
+// which still sets the slices (and so the order of the sums).
 int chi0_fp32_launch(int v, const void *P, int ld, const double *delta, const double *df,
                      int paired, long long n_trans, long long slice_len, int slices,
                      const double *omega, int n_w, double eta, int n_g, double2 *part,
                      hipStream_t s) {
+  switch (ld / 16) {
+#define TDX_ROWS(N, R)                                                                         \
+  case N:                                                                                      \
+    return launch_rows<R, N>(P, delta, df, paired, n_trans, slice_len, slices, omega, n_w, eta, \
+                             n_g, part, s);
+    TDX_ROWS(2, 6)
+    TDX_ROWS(3, 4)
+    TDX_ROWS(4, 3)
+    TDX_ROWS(5, 3)
+    TDX_ROWS(6, 2)
+    TDX_ROWS(7, 2)
+    TDX_ROWS(8, 2)
+    TDX_ROWS(9, 2)
+#undef TDX_ROWS
+  }
   return kVarF32[v].launch(P, ld, delta, df, paired, n_trans, slice_len, slices, omega, n_w, eta,
                            n_g, part, s);
 }

@@ -1,0 +1,64 @@
+"""FP32 chi0 at the edges of the tiles that hold all columns: bases around each
+count of 16-column blocks and past the last, rows (frequency, vector) that end
+inside and at a tile, lists around the chunk of 32 transitions, past a run of
+4096 and in several slices, full and paired.  Reference: the defining sum in
+FP64 on the CPU."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+ETA, PREF = 0.06, 0.013
+
+
+@pytest.fixture(scope="module")
+def tdx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_01875_amd as m
+    return m
+
+
+@pytest.fixture(scope="module")
+def ctx(tdx):
+    c = tdx.Context(0)
+    yield c
+    c.close()
+
+
+# (vectors, frequencies, transitions)
+CASES = [(16, 9, 40), (17, 1, 1), (31, 13, 33), (32, 12, 32), (33, 40, 31), (48, 11, 100),
+         (49, 3, 65), (64, 16, 64), (65, 7, 4097), (80, 5, 96), (81, 4, 50), (96, 6, 33),
+         (97, 9, 8200), (112, 8, 40), (113, 5, 70), (128, 2, 129), (129, 3, 31), (144, 4, 64),
+         (145, 3, 40)]
+
+
+@pytest.mark.parametrize("paired", [False, True])
+@pytest.mark.parametrize("n_g,n_w,n_t", CASES)
+def test_chi0_matches_the_defining_sum(tdx, ctx, n_g, n_w, n_t, paired):
+    import torch
+    print("chi0 fp32 rows", n_g, n_w, n_t, paired, flush=True)
+    rng = np.random.default_rng(100 * n_g + n_t)
+    tr = tdx.Transitions(n_t, 0, paired=paired)
+    dl, df = rng.uniform(0.05, 1.5, n_t), rng.uniform(0.1, 1.0, n_t)
+    tr.delta.copy_(torch.from_numpy(dl))
+    tr.df.copy_(torch.from_numpy(df))
+    ld = (n_g + 15) // 16 * 16
+    P = np.zeros((n_t, ld), dtype=np.complex64)
+    P[:, :n_g] = rng.standard_normal((n_t, n_g)) + 1j * rng.standard_normal((n_t, n_g))
+    rho = P[:, :n_g].astype(np.complex128)
+    om = np.linspace(0.0, 2.0, n_w)
+    w = df / (om[:, None] - dl + 1j * ETA)
+    if paired:
+        w = w - df / (om[:, None] + dl + 1j * ETA)
+    ref = np.stack([PREF * (rho.T * wi) @ rho.conj() for wi in w])
+    a = np.abs(rho)
+    # FP32: the weight (8 operations), w rho, and a run of at most 4096
+    # transitions (two products each for Re and Im)
+    steps = 2 * (2 * min(n_t, 4096) + 12)
+    tol = steps * EPS * np.stack([PREF * (a.T * wi) @ a for wi in np.abs(w)])
+    Pd = torch.from_numpy(P).cuda()
+    got = tdx.chi0(ctx, tr, Pd, n_g, "fp32", torch.from_numpy(om).cuda(), ETA, PREF)
+    assert np.all(np.abs(got.cpu().numpy().reshape(ref.shape) - ref) <= tol)
