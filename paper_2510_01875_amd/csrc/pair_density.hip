@@ -314,12 +314,14 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
 //    a linear index, with no bounds check: entries outside the basis name a
 //    slot that holds zero;
 //  - two wavefronts per SIMD, each with its own group, cover each other;
-//  - the 16-transition tiles of a k are dealt from a counter in LDS.
+//  - the 16-transition tiles of a chunk are dealt from a counter in LDS, the
+//    chunks of all k from one in global memory.
 // The products and their order are those of the form above: same bits.
 // 2.9e5 transitions of a crystal's 5^3 grid (N_G 133, 400 plane waves, FP64):
-// 3.8 ms against 10.4 ms (38 TFLOP/s of wanted products; the gathers' bank
-// conflicts are 8 % of it, measured with a fixed slot in their place); 6.2e5 on
-// an 8^3 grid: 7.5 ms; the electron gas (N_G 32, 7.9e5): 2.4 against 3.5 ms.
+// 3.0 ms against 10.4 ms (47 TFLOP/s of wanted products; 3.8 ms with a grid of
+// one workgroup per chunk; the gathers' bank conflicts are 8 % of that, measured
+// with a fixed slot in their place); 1.5e5 on a 4^3 grid: 1.8 ms (2.0 with the
+// grid); the electron gas (N_G 32, 7.9e5): 2.5 against 3.5 ms.
 constexpr int kPdWaves = 8;
 constexpr int kPdLds = 160 * 1024 - 256;  // one workgroup per CU
 
@@ -330,24 +332,76 @@ __host__ __device__ inline size_t pd_front_bytes(int npw_max, int nb_max) {
   return sizeof(double2) * (size_t)kPdWaves * (npw_max + 1) +
          sizeof(int) * ((size_t)npw_max + nb_max + 1 + 8);
 }
-// The form above runs where the fixed sides and an unpadded box fit.
+// The form above runs where the fixed sides and an unpadded box fit (and the
+// lookup tables of the other form, whose space it uses, hold two ints per k and
+// four).
 inline bool pd_shared_fits(int npw_max, int nb_max, long box) {
-  return npw_max < 65535 && pd_front_bytes(npw_max, nb_max) + sizeof(short) * box <= kPdLds;
+  return box >= 6 && npw_max < 65535 &&
+         pd_front_bytes(npw_max, nb_max) + sizeof(short) * box <= kPdLds;
 }
 
-// Tiles a workgroup takes at a time (chunk) and workgroups per k.  The tiles
-// of a k differ with its occupied bands, and one workgroup runs on a CU at a
-// time, so chunks are small enough for four rounds of the chip, a tile per
-// wavefront or fewer where the list is short, and workgroups beyond a k's
-// chunks leave at once (half of the k-points of a paired list hold none).
-// About two thirds of a list's tiles belong to one of the two launches.
-inline void pd_chunks(int nk, bool paired, long long n_trans, int n_cu, int *chunk, int *parts) {
+// Tiles a workgroup takes at a time.  One workgroup runs per CU and takes the
+// next chunk of any k when it has finished one: a grid of one workgroup per
+// chunk left 39 % of the wavefronts' time idle, since an XCD deals workgroups
+// to its shader engines in turn whatever their load, and half of the k-points
+// of a paired list hold none.  A chunk is a tile per wavefront, fewer where
+// the list is short, and more where a tile is short against the tables that are
+// built for each (about 15 us; 16 n_gt npw cycles per tile).  About two thirds
+// of a list's tiles belong to one of the two launches.
+inline int pd_chunk(long long n_trans, int n_gt, int npw_max, int n_cu) {
   const double tiles = n_trans / 24.0;
-  *chunk = tiles < 8.0 * n_cu
-               ? std::max(1, (int)std::ceil(tiles / n_cu))
-               : 8 * std::min(8, std::max(1, (int)(tiles / (32.0 * n_cu) + 0.5)));
-  const double per_k = tiles * (paired ? 2.0 : 1.0) / nk / *chunk;
-  *parts = std::min(64, std::max(1, (int)std::ceil(1.5 * per_k)));
+  if (tiles < 8.0 * n_cu) return std::max(1, (int)std::ceil(tiles / n_cu));
+  const int least = (2800 + n_gt * npw_max - 1) / (n_gt * npw_max);
+  return 8 * std::min({8, least, std::max(1, (int)(tiles / (32.0 * n_cu) + 0.5))});
+}
+
+// The chunks of each k for the two launches: [row form][n_k + 1] and [column
+// form][n_k + 1], entry k + 1 the number of k's.  Grid (n_k, 2), one wavefront.
+__global__ void __launch_bounds__(64)
+    k_pd_count(const long long *rb, const long long *re, const long long *cb, const long long *ce,
+               int nk, int nb_max, int chunk, int *first) {
+  const int k = blockIdx.x, col = blockIdx.y;
+  const long long *beg = (col ? cb : rb) + (size_t)k * nb_max;
+  const long long *end = (col ? ce : re) + (size_t)k * nb_max;
+  int n = 0;
+  for (int b = threadIdx.x; b < nb_max; b += 64) {
+    const long long len = end[b] - beg[b];
+    n += len > 0 && (col || len >= kShortRow) ? (int)((len + 15) / 16) : 0;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) n += __shfl_xor(n, o);
+  if (threadIdx.x == 0) first[col * (nk + 1) + k + 1] = (n + chunk - 1) / chunk;
+}
+
+// ... and from them each k's first chunk (entry n_k: all), with the launches'
+// counters of chunks taken, zero.  Two blocks.
+__global__ void __launch_bounds__(1024) k_pd_first(int nk, int *first, int *taken) {
+  __shared__ int sum[16];
+  int *f = first + blockIdx.x * (nk + 1);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int carry = 0;
+  for (int k0 = 0; k0 < nk; k0 += 1024) {
+    int n = k0 + tid < nk ? f[k0 + tid + 1] : 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int x = __shfl_up(n, o);
+      if (lane >= o) n += x;
+    }
+    if (lane == 63) sum[wave] = n;
+    __syncthreads();
+    int all = 0;
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) n += sum[w];
+      all += sum[w];
+    }
+    if (k0 + tid < nk) f[k0 + tid + 1] = carry + n;
+    carry += all;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    f[0] = 0;
+    taken[blockIdx.x] = 0;
+  }
 }
 
 template <int FMT, bool COL>
@@ -356,209 +410,220 @@ __global__ void __launch_bounds__(64 * kPdWaves) __attribute__((amdgpu_waves_per
                      int npw_max, const int *tn, const int *tm, const long long *gbeg,
                      const long long *gend, const long long *perm, const int *kpmap,
                      const int *gsmap, const int *gbasis, int n_g, int ld, int M0, int M1, int M2,
-                     void *P, long long t_lo, long long n_rows, int chunk) {
+                     void *P, long long t_lo, long long n_rows, int chunk, int nk,
+                     const int *first, int *taken) {
   extern __shared__ double2 pd_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int *lina = (int *)(pd_lds + kPdWaves * (npw_max + 1));  // [npw_max]
   int *start = lina + npw_max;                             // [nb_max + 1]
   int *next = start + nb_max + 1, *reach = next + 1;       // [1], [3]
-  unsigned short *box = (unsigned short *)(reach + 3);
-  const int k = blockIdx.y, kp = kpmap[k];
-  const int kf = COL ? kp : k, ka = COL ? k : kp;
-  const int gs[3] = {gsmap[3 * k], gsmap[3 * k + 1], gsmap[3 * k + 2]};
-  if (tid < 3) reach[tid] = 0;
-  __syncthreads();
-  for (int i = tid; i < 3 * n_g; i += 64 * kPdWaves) atomicMax(&reach[i % 3], abs(gbasis[i] + gs[i % 3]));
-  // tiles of each band's group, as an inclusive sum over the bands
-  if (wave == 0) {
-    int carry = 0;
-    for (int b0 = 0; b0 < nb_max; b0 += 64) {
-      const int b = b0 + lane;
-      int n = 0;
-      if (b < nb_max) {
-        const size_t grp = (size_t)k * nb_max + b;
-        const long long len = gend[grp] - gbeg[grp];
-        n = len > 0 && (COL || len >= kShortRow) ? (int)((len + 15) / 16) : 0;
-      }
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int x = __shfl_up(n, o);
-        if (lane >= o) n += x;
-      }
-      if (b < nb_max) start[b + 1] = carry + n;
-      carry += __shfl(n, 63);
-    }
-    if (lane == 0) start[0] = 0;
-  }
-  __syncthreads();
-  const int total = start[nb_max];
-  if ((int)blockIdx.x * chunk >= total) return;
-  // the padded box: axis i holds 2 M_i + 1 indices and R_i of padding, R_i the
-  // largest |G_i + G_s,i|; an index that runs over an end of axis 1 or 2
-  // lands in the padding next to it, axis 0 has padding on both sides.  A
-  // reach too wide for LDS leaves the padding out and checks every index.
-  int R0 = reach[0], R1 = reach[1], R2 = reach[2];
-  const long space = (long)(kPdLds - pd_front_bytes(npw_max, nb_max)) / 2;
-  const bool padded =
-      (2L * M0 + 1 + 2 * R0) * (2L * M1 + 1 + R1) * (2L * M2 + 1 + R2) +
-          2 * (R1 * (2L * M2 + 1 + R2) + R2) <= space;
-  if (!padded) R0 = R1 = R2 = 0;
-  const int W1 = 2 * M1 + 1 + R1, W2 = 2 * M2 + 1 + R2, off = R1 * W2 + R2;
-  const long size = (long)(2 * M0 + 1 + 2 * R0) * W1 * W2 + 2 * off;
-  const int npf = npw[kf], npa = npw[ka];
-  auto linear = [&](int m0, int m1, int m2) {
-    return off + ((m0 + M0 + R0) * W1 + m1 + M1) * W2 + m2 + M2;
-  };
-  // three 10-bit fields, for the checked indices
-  auto pack = [](int x, int y, int z) { return x | (y << 10) | (z << 20); };
-  for (long i = tid; i < size; i += 64 * kPdWaves) box[i] = (unsigned short)npw_max;  // zero
-  const int *ma = miller + (size_t)ka * npw_max * 3, *mf = miller + (size_t)kf * npw_max * 3;
-  for (int i = tid; i < npa; i += 64 * kPdWaves)
-    lina[i] = padded ? linear(ma[3 * i], ma[3 * i + 1], ma[3 * i + 2])
-                     : pack(ma[3 * i] + M0, ma[3 * i + 1] + M1, ma[3 * i + 2] + M2);
+  int *place = reach + 3;                                  // [2]
+  unsigned short *box = (unsigned short *)(place + 2);
   double2 *cfix = pd_lds + wave * (npw_max + 1);
-  if (lane == 0) cfix[npw_max] = make_double2(0.0, 0.0);
-  if (tid == 0) *next = 0;
-  __syncthreads();
-  for (int i = tid; i < npf; i += 64 * kPdWaves)
-    box[linear(mf[3 * i], mf[3 * i + 1], mf[3 * i + 2])] = (unsigned short)i;
-  __syncthreads();
+  const int chunks = first[nk];
+  for (int x = blockIdx.x; x < chunks;) {
+    // the chunk's k
+    for (int i = tid; i < nk; i += 64 * kPdWaves)
+      if (first[i] <= x && x < first[i + 1]) place[1] = i;
+    __syncthreads();
+    const int k = place[1], item0 = (x - first[k]) * chunk, kp = kpmap[k];
+    const int kf = COL ? kp : k, ka = COL ? k : kp;
+    const int gs[3] = {gsmap[3 * k], gsmap[3 * k + 1], gsmap[3 * k + 2]};
+    if (tid < 3) reach[tid] = 0;
+    __syncthreads();
+    for (int i = tid; i < 3 * n_g; i += 64 * kPdWaves) atomicMax(&reach[i % 3], abs(gbasis[i] + gs[i % 3]));
+    // tiles of each band's group, as an inclusive sum over the bands
+    if (wave == 0) {
+      int carry = 0;
+      for (int b0 = 0; b0 < nb_max; b0 += 64) {
+        const int b = b0 + lane;
+        int n = 0;
+        if (b < nb_max) {
+          const size_t grp = (size_t)k * nb_max + b;
+          const long long len = gend[grp] - gbeg[grp];
+          n = len > 0 && (COL || len >= kShortRow) ? (int)((len + 15) / 16) : 0;
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int x = __shfl_up(n, o);
+          if (lane >= o) n += x;
+        }
+        if (b < nb_max) start[b + 1] = carry + n;
+        carry += __shfl(n, 63);
+      }
+      if (lane == 0) start[0] = 0;
+    }
+    __syncthreads();
+    const int end = std::min(start[nb_max], item0 + chunk);
+    // the padded box: axis i holds 2 M_i + 1 indices and R_i of padding, R_i the
+    // largest |G_i + G_s,i|; an index that runs over an end of axis 1 or 2
+    // lands in the padding next to it, axis 0 has padding on both sides.  A
+    // reach too wide for LDS leaves the padding out and checks every index.
+    int R0 = reach[0], R1 = reach[1], R2 = reach[2];
+    const long space = (long)(kPdLds - pd_front_bytes(npw_max, nb_max)) / 2;
+    const bool padded =
+        (2L * M0 + 1 + 2 * R0) * (2L * M1 + 1 + R1) * (2L * M2 + 1 + R2) +
+            2 * (R1 * (2L * M2 + 1 + R2) + R2) <= space;
+    if (!padded) R0 = R1 = R2 = 0;
+    const int W1 = 2 * M1 + 1 + R1, W2 = 2 * M2 + 1 + R2, off = R1 * W2 + R2;
+    const long size = (long)(2 * M0 + 1 + 2 * R0) * W1 * W2 + 2 * off;
+    const int npf = npw[kf], npa = npw[ka];
+    auto linear = [&](int m0, int m1, int m2) {
+      return off + ((m0 + M0 + R0) * W1 + m1 + M1) * W2 + m2 + M2;
+    };
+    // three 10-bit fields, for the checked indices
+    auto pack = [](int x, int y, int z) { return x | (y << 10) | (z << 20); };
+    for (long i = tid; i < size; i += 64 * kPdWaves) box[i] = (unsigned short)npw_max;  // zero
+    const int *ma = miller + (size_t)ka * npw_max * 3, *mf = miller + (size_t)kf * npw_max * 3;
+    for (int i = tid; i < npa; i += 64 * kPdWaves)
+      lina[i] = padded ? linear(ma[3 * i], ma[3 * i + 1], ma[3 * i + 2])
+                       : pack(ma[3 * i] + M0, ma[3 * i + 1] + M1, ma[3 * i + 2] + M2);
+    if (lane == 0) cfix[npw_max] = make_double2(0.0, 0.0);
+    if (tid == 0) *next = 0;
+    __syncthreads();
+    for (int i = tid; i < npf; i += 64 * kPdWaves)
+      box[linear(mf[3 * i], mf[3 * i + 1], mf[3 * i + 2])] = (unsigned short)i;
+    __syncthreads();
 
-  const double2 *ca = coef + (size_t)ka * nb_max * npw_max;
-  const int *ta = COL ? tn : tm;  // band of the A row of a transition
-  const int r = lane & 15, kq = lane >> 4;
-  const int n_gt = ld / 16, passes = (n_gt + kPdGT - 1) / kPdGT;
-  auto trans = [&](long long p) { return COL ? perm[p] : p; };
-  int band = -1;
-  for (;;) {
-    int item = 0;
-    if (lane == 0) item = atomicAdd(next, 1);
-    item = __builtin_amdgcn_readfirstlane(item);
-    // the chunks blockIdx.x, blockIdx.x + gridDim.x, ... of the k
-    item = ((int)blockIdx.x + item / chunk * (int)gridDim.x) * chunk + item % chunk;
-    if (item >= total) break;
-    // the band whose tiles hold it: start[b] <= item < start[b + 1]
-    int lo = 0, hi = nb_max - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (start[mid + 1] <= item)
-        lo = mid + 1;
+    const double2 *ca = coef + (size_t)ka * nb_max * npw_max;
+    const int *ta = COL ? tn : tm;  // band of the A row of a transition
+    const int r = lane & 15, kq = lane >> 4;
+    const int n_gt = ld / 16, passes = (n_gt + kPdGT - 1) / kPdGT;
+    auto trans = [&](long long p) { return COL ? perm[p] : p; };
+    int band = -1;
+    for (;;) {
+      int item = 0;
+      if (lane == 0) item = atomicAdd(next, 1);
+      item = item0 + __builtin_amdgcn_readfirstlane(item);
+      if (item >= end) break;
+      // the band whose tiles hold it: start[b] <= item < start[b + 1]
+      int lo = 0, hi = nb_max - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (start[mid + 1] <= item)
+          lo = mid + 1;
+        else
+          hi = mid;
+      }
+      lo = __builtin_amdgcn_readfirstlane(lo);
+      if (lo != band) {
+        band = lo;
+        const double2 *cf = coef + ((size_t)kf * nb_max + band) * npw_max;
+        for (int i = lane; i < npf; i += 64) {
+          const double2 c = cf[i];
+          cfix[i] = COL ? c : make_double2(c.x, -c.y);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      }
+      const size_t grp = (size_t)k * nb_max + band;
+      const long long q0 = gbeg[grp] + 16LL * (item - start[band]), p1 = gend[grp];
+      const bool row_ok = q0 + r < p1;
+      const double2 *crow = ca + (size_t)(row_ok ? ta[trans(q0 + r)] : 0) * npw_max;
+      auto tiles = [&](int gt0, auto nq_c, auto padded_c) {
+        constexpr int NQ = decltype(nq_c)::value;
+        constexpr bool PAD = decltype(padded_c)::value;
+        f64x4 acr[NQ], aci[NQ];
+        int lg[NQ];  // linear offset of this lane's G + G_s in each tile
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          acr[q] = aci[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+          const int g = std::min((gt0 + q) * 16 + r, n_g - 1);
+          const int f0 = gbasis[3 * g] + gs[0], f1 = gbasis[3 * g + 1] + gs[1],
+                    f2 = gbasis[3 * g + 2] + gs[2];
+          const int x = (f0 * W1 + f1) * W2 + f2;
+          lg[q] = PAD ? (COL ? x : -x) : pack(f0 + 512, f1 + 512, f2 + 512);
+        }
+        auto load_a = [&](int j) {
+          const double2 c = j < npa && row_ok ? crow[j] : make_double2(0.0, 0.0);
+          return COL ? make_double2(c.x, -c.y) : c;
+        };
+        // slots one K-step ahead, coefficients far enough for a few thousand
+        // cycles of the two wavefronts' products (4 NQ of 64 cycles a step)
+        constexpr int D = NQ >= 6 ? 1 : NQ >= 3 ? 2 : 4;
+        double2 an[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) an[d] = load_a(4 * d + kq);
+        int slot[NQ];
+        auto load_slots = [&](int j) {
+          const int la = lina[std::min(j, npa - 1)];
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            if constexpr (PAD) {
+              slot[q] = box[la + lg[q]];
+              continue;
+            }
+            const int sg = COL ? 1 : -1;
+            const int x0 = (la & 1023) + sg * ((lg[q] & 1023) - 512);
+            const int x1 = ((la >> 10) & 1023) + sg * (((lg[q] >> 10) & 1023) - 512);
+            const int x2 = (la >> 20) + sg * ((int)((unsigned)lg[q] >> 20) - 512);
+            const bool ok = x0 >= 0 && x0 <= 2 * M0 && x1 >= 0 && x1 <= 2 * M1 && x2 >= 0 &&
+                            x2 <= 2 * M2;
+            slot[q] = ok ? box[(x0 * W1 + x1) * W2 + x2] : npw_max;
+          }
+        };
+        load_slots(kq);
+        for (int jd = 0; jd < npa; jd += 4 * D) {
+#pragma unroll
+          for (int d = 0; d < D; ++d) {
+            const int j0 = jd + 4 * d;
+            if (D > 1 && j0 >= npa) break;
+            const double2 a = an[d];
+            an[d] = load_a(j0 + 4 * D + kq);
+            double2 u[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) u[q] = cfix[slot[q]];
+            load_slots(j0 + 4 + kq);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+              acr[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, u[q].x, acr[q], 0, 0, 0);
+              aci[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, u[q].y, aci[q], 0, 0, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+              acr[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, u[q].y, acr[q], 0, 0, 0);
+              aci[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, u[q].x, aci[q], 0, 0, 0);
+            }
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const long long p = q0 + kq + 4 * e;
+          if (p >= p1) continue;
+          const long long t = trans(p) - t_lo;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            const int g = (gt0 + q) * 16 + r;
+            const bool in = g < n_g;  // columns past n_g are stored as zero
+            store<FMT>(P, t, g, ld, n_rows, in ? acr[q][e] : 0.0, in ? aci[q][e] : 0.0);
+          }
+        }
+      };
+      auto sweep = [&](auto padded_c) {
+        for (int s = 0; s < passes; ++s) {
+          const int gt0 = n_gt * s / passes;
+          switch (n_gt * (s + 1) / passes - gt0) {  // uniform across the wave
+            case 1: tiles(gt0, std::integral_constant<int, 1>{}, padded_c); break;
+            case 2: tiles(gt0, std::integral_constant<int, 2>{}, padded_c); break;
+            case 3: tiles(gt0, std::integral_constant<int, 3>{}, padded_c); break;
+            case 4: tiles(gt0, std::integral_constant<int, 4>{}, padded_c); break;
+            case 5: tiles(gt0, std::integral_constant<int, 5>{}, padded_c); break;
+            case 6: tiles(gt0, std::integral_constant<int, 6>{}, padded_c); break;
+            case 7: tiles(gt0, std::integral_constant<int, 7>{}, padded_c); break;
+            case 8: tiles(gt0, std::integral_constant<int, 8>{}, padded_c); break;
+            default: tiles(gt0, std::integral_constant<int, kPdGT>{}, padded_c); break;
+          }
+        }
+      };
+      if (padded)
+        sweep(std::true_type{});
       else
-        hi = mid;
+        sweep(std::false_type{});
     }
-    lo = __builtin_amdgcn_readfirstlane(lo);
-    if (lo != band) {
-      band = lo;
-      const double2 *cf = coef + ((size_t)kf * nb_max + band) * npw_max;
-      for (int i = lane; i < npf; i += 64) {
-        const double2 c = cf[i];
-        cfix[i] = COL ? c : make_double2(c.x, -c.y);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    }
-    const size_t grp = (size_t)k * nb_max + band;
-    const long long q0 = gbeg[grp] + 16LL * (item - start[band]), p1 = gend[grp];
-    const bool row_ok = q0 + r < p1;
-    const double2 *crow = ca + (size_t)(row_ok ? ta[trans(q0 + r)] : 0) * npw_max;
-    auto tiles = [&](int gt0, auto nq_c, auto padded_c) {
-      constexpr int NQ = decltype(nq_c)::value;
-      constexpr bool PAD = decltype(padded_c)::value;
-      f64x4 acr[NQ], aci[NQ];
-      int lg[NQ];  // linear offset of this lane's G + G_s in each tile
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        acr[q] = aci[q] = f64x4{0.0, 0.0, 0.0, 0.0};
-        const int g = std::min((gt0 + q) * 16 + r, n_g - 1);
-        const int f0 = gbasis[3 * g] + gs[0], f1 = gbasis[3 * g + 1] + gs[1],
-                  f2 = gbasis[3 * g + 2] + gs[2];
-        const int x = (f0 * W1 + f1) * W2 + f2;
-        lg[q] = PAD ? (COL ? x : -x) : pack(f0 + 512, f1 + 512, f2 + 512);
-      }
-      auto load_a = [&](int j) {
-        const double2 c = j < npa && row_ok ? crow[j] : make_double2(0.0, 0.0);
-        return COL ? make_double2(c.x, -c.y) : c;
-      };
-      // slots one K-step ahead, coefficients far enough for a few thousand
-      // cycles of the two wavefronts' products (4 NQ of 64 cycles a step)
-      constexpr int D = NQ >= 6 ? 1 : NQ >= 3 ? 2 : 4;
-      double2 an[D];
-#pragma unroll
-      for (int d = 0; d < D; ++d) an[d] = load_a(4 * d + kq);
-      int slot[NQ];
-      auto load_slots = [&](int j) {
-        const int la = lina[std::min(j, npa - 1)];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          if constexpr (PAD) {
-            slot[q] = box[la + lg[q]];
-            continue;
-          }
-          const int sg = COL ? 1 : -1;
-          const int x0 = (la & 1023) + sg * ((lg[q] & 1023) - 512);
-          const int x1 = ((la >> 10) & 1023) + sg * (((lg[q] >> 10) & 1023) - 512);
-          const int x2 = (la >> 20) + sg * ((int)((unsigned)lg[q] >> 20) - 512);
-          const bool ok = x0 >= 0 && x0 <= 2 * M0 && x1 >= 0 && x1 <= 2 * M1 && x2 >= 0 &&
-                          x2 <= 2 * M2;
-          slot[q] = ok ? box[(x0 * W1 + x1) * W2 + x2] : npw_max;
-        }
-      };
-      load_slots(kq);
-      for (int jd = 0; jd < npa; jd += 4 * D) {
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-          const int j0 = jd + 4 * d;
-          if (D > 1 && j0 >= npa) break;
-          const double2 a = an[d];
-          an[d] = load_a(j0 + 4 * D + kq);
-          double2 u[NQ];
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) u[q] = cfix[slot[q]];
-          load_slots(j0 + 4 + kq);
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            acr[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, u[q].x, acr[q], 0, 0, 0);
-            aci[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, u[q].y, aci[q], 0, 0, 0);
-          }
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            acr[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, u[q].y, acr[q], 0, 0, 0);
-            aci[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, u[q].x, aci[q], 0, 0, 0);
-          }
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const long long p = q0 + kq + 4 * e;
-        if (p >= p1) continue;
-        const long long t = trans(p) - t_lo;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-          const int g = (gt0 + q) * 16 + r;
-          const bool in = g < n_g;  // columns past n_g are stored as zero
-          store<FMT>(P, t, g, ld, n_rows, in ? acr[q][e] : 0.0, in ? aci[q][e] : 0.0);
-        }
-      }
-    };
-    auto sweep = [&](auto padded_c) {
-      for (int s = 0; s < passes; ++s) {
-        const int gt0 = n_gt * s / passes;
-        switch (n_gt * (s + 1) / passes - gt0) {  // uniform across the wave
-          case 1: tiles(gt0, std::integral_constant<int, 1>{}, padded_c); break;
-          case 2: tiles(gt0, std::integral_constant<int, 2>{}, padded_c); break;
-          case 3: tiles(gt0, std::integral_constant<int, 3>{}, padded_c); break;
-          case 4: tiles(gt0, std::integral_constant<int, 4>{}, padded_c); break;
-          case 5: tiles(gt0, std::integral_constant<int, 5>{}, padded_c); break;
-          case 6: tiles(gt0, std::integral_constant<int, 6>{}, padded_c); break;
-          case 7: tiles(gt0, std::integral_constant<int, 7>{}, padded_c); break;
-          case 8: tiles(gt0, std::integral_constant<int, 8>{}, padded_c); break;
-          default: tiles(gt0, std::integral_constant<int, kPdGT>{}, padded_c); break;
-        }
-      }
-    };
-    if (padded)
-      sweep(std::true_type{});
-    else
-      sweep(std::false_type{});
+    if (chunks <= (int)gridDim.x) return;
+    __syncthreads();
+    if (tid == 0) place[0] = (int)gridDim.x + atomicAdd(taken, 1);
+    __syncthreads();
+    x = place[0];
   }
 }
 
@@ -650,15 +715,18 @@ int pd_enqueue(int n_cu, const tdx_states *st, const int qj[3], const tdx_transl
   hipLaunchKernelGGL(k_kq_map, dim3((nk + 255) / 256), dim3(256), 0, s, st->kgrid[0],
                      st->kgrid[1], st->kgrid[2], qj[0], qj[1], qj[2], w.kp, w.gs);
   TDX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_fill<int>, dim3(1024), dim3(256), 0, s, w.lut, (long long)nk * box, -1);
-  TDX_HIP(hipGetLastError());
+  const bool shared = pd_shared_fits(st->npw_max, nb_max, box);
+  if (!shared) {
+    hipLaunchKernelGGL(k_fill<int>, dim3(1024), dim3(256), 0, s, w.lut, (long long)nk * box, -1);
+    TDX_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_lut, dim3((st->npw_max + 255) / 256, nk), dim3(256), 0, s, st->miller,
+                       st->npw, st->npw_max, nk, M0, M1, M2, w.lut, box);
+    TDX_HIP(hipGetLastError());
+  }
   // every row start and end (re follows rb directly); k_cols writes every
   // column-group entry itself
   hipLaunchKernelGGL(k_fill<long long>, dim3(1024), dim3(256), 0, s, w.rb,
                      2LL * nk * nb_max, 0LL);
-  TDX_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_lut, dim3((st->npw_max + 255) / 256, nk), dim3(256), 0, s, st->miller,
-                     st->npw, st->npw_max, nk, M0, M1, M2, w.lut, box);
   TDX_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_rows, dim3(nk), dim3(256), 0, s, (const long long *)tl->k_offsets, tl->n,
                      nb_max, (long long)t_begin, (long long)t_end, w.rb, w.re);
@@ -676,17 +744,23 @@ int pd_enqueue(int n_cu, const tdx_states *st, const int qj[3], const tdx_transl
   const bool ms = lds0 + sizeof(unsigned) * st->npw_max <= 150 * 1024;
   const size_t lds = ms ? lds0 + sizeof(unsigned) * st->npw_max : lds0;
   // long rows, then the column groups of the short ones (disjoint outputs)
-  if (pd_shared_fits(st->npw_max, nb_max, box)) {
-    int chunk, parts;
-    pd_chunks(nk, tl->paired != 0, n_trans, n_cu, &chunk, &parts);
-    const dim3 kgrid(parts, nk);
+  if (shared) {
+    const int chunk = pd_chunk(n_trans, ld / 16, st->npw_max, n_cu);
+    int *taken = w.lut, *first = w.lut + 2;
+    hipLaunchKernelGGL(k_pd_count, dim3(nk, 2), dim3(64), 0, s, w.rb, w.re, w.cb, w.ce, nk, nb_max,
+                       chunk, first);
+    TDX_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_pd_first, dim3(2), dim3(1024), 0, s, nk, first, taken);
+    TDX_HIP(hipGetLastError());
+    const dim3 kgrid(n_cu);
 #define TDX_PDK(F, COL, B, E)                                                                   \
   TDX_HIP(hipFuncSetAttribute((const void *)k_pair_density_k<F, COL>,                           \
                               hipFuncAttributeMaxDynamicSharedMemorySize, kPdLds));             \
   hipLaunchKernelGGL((k_pair_density_k<F, COL>), kgrid, dim3(64 * kPdWaves), kPdLds, s,         \
                      (const double2 *)st->coef, st->miller, st->npw, nb_max, st->npw_max,       \
                      tl->n, tl->m, B, E, w.perm, w.kp, w.gs, gbasis, n_g, ld, M0, M1, M2, P,    \
-                     (long long)t_begin, n_trans, chunk);                                       \
+                     (long long)t_begin, n_trans, chunk, nk, first + (COL ? nk + 1 : 0),        \
+                     taken + (COL ? 1 : 0));                                                    \
   TDX_HIP(hipGetLastError())
 #define TDX_PDK2(F)                   \
   TDX_PDK(F, false, w.rb, w.re);      \
