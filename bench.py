@@ -809,9 +809,11 @@ def main():
                      "peak": PEAK_TFLOPS[args.prec], "unit": "TFLOP/s",
                      "frac": per_launch / (avg_ms * 1e-3) / 1e12 / PEAK_TFLOPS[args.prec],
                      "traffic": measured_traffic(w.name, args.prec),
-                     "kernel": {"bf16x3": "k_chi0_bf16x3", "fp32": "k_chi0_fp<float>",
-                                "fp64": "k_chi0_fp<double>"}[args.prec],
-                     "issued_mfma_frac": (3.0 if args.prec == "bf16x3" else 1.0)
+                     "kernel": {"bf16x3": "k_chi0_bf16x3", "fp32": "k_chi0_fp_rows",
+                                "fp64": "k_chi0_fp64"}[args.prec],
+                     # products issued per algorithmic one: three of the split
+                     # form, half in FP64 (over the Hermitian pairs)
+                     "issued_mfma_frac": {"bf16x3": 3.0, "fp64": 0.5}.get(args.prec, 1.0)
                      * per_launch / (avg_ms * 1e-3) / 1e12 / PEAK_TFLOPS[args.prec]},
     }
     log("feg_c1 leg ...")

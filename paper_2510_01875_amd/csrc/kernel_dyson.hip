@@ -217,9 +217,11 @@ __device__ void make_twiddles(double2 *tw, int N0, int N1, int N2) {
 constexpr int kDensThreads = 512;
 constexpr int kDensPoints = 160 * 1024 / 16 / kDensThreads;  // per thread, of what LDS holds
 
-// Workgroups per k: about four per CU in all, each a share of the bands.
-inline int dens_slices(int n_k, int n_cu) {
-  return std::max(1, std::min(16, (4 * n_cu + n_k - 1) / std::max(n_k, 1)));
+// Workgroups per k: about four per CU in all, each a share of the bands; one
+// where the workspace is limited (each keeps a partial of its own).
+inline int dens_slices(const tdx_ctx *ctx, int n_k) {
+  if (ctx->limit) return 1;
+  return std::max(1, std::min(16, (4 * ctx->n_cu + n_k - 1) / std::max(n_k, 1)));
 }
 
 // Density partials: dens[k][slice][j] = sum_n f_nk |u_nk(r_j)|^2 over the bands
@@ -1684,7 +1686,7 @@ int tdx_xc_kernel_grid(tdx_ctx *ctx, const tdx_states *st, const int dens_grid[3
   hipStream_t s = as_stream(stream);
   const int N0 = dens_grid[0], N1 = dens_grid[1], N2 = dens_grid[2];
   void *w;
-  const int slices = dens_slices(st->n_k, ctx->n_cu), parts = st->n_k * slices;
+  const int slices = dens_slices(ctx, st->n_k), parts = st->n_k * slices;
   TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * (size_t)parts * Nr, &w));
   double *dens = (double *)w;
   TDX_HIP(hipFuncSetAttribute((const void *)k_density, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1903,7 +1905,7 @@ int tdx_density_vjp(tdx_ctx *ctx, const tdx_states *st, const int dens_grid[3],
   hipStream_t s = as_stream(stream);
   const int N0 = dens_grid[0], N1 = dens_grid[1], N2 = dens_grid[2];
   void *w;
-  const int slices = dens_slices(st->n_k, ctx->n_cu), parts = st->n_k * slices;
+  const int slices = dens_slices(ctx, st->n_k), parts = st->n_k * slices;
   TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * ((size_t)parts + 1) * Nr, &w));
   double *dens = (double *)w, *nbar = dens + (size_t)parts * Nr;
   TDX_HIP(hipFuncSetAttribute((const void *)k_density, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -116,3 +116,26 @@ def test_density_and_its_adjoint(tdx, ctx, grid, reach, npw, nb, n_k):
     ob = dev(occ0)
     tdx.density_vjp(ctx, st, grid, dev(fbar.reshape(-1)), ob)
     assert np.all(np.abs(ob.cpu().numpy() - want_o) <= tol_o)
+
+
+def test_a_limited_workspace_holds_one_partial_per_k(tdx):
+    """The least workspace, one partial of the grid per k (and the adjoint's
+    one more grid), is enough, and less is refused."""
+    import torch
+    grid, n_k, nb = (9, 8, 10), 3, 12
+    st, *_ = _system(tdx, (2, 3, 4), 60, nb, n_k, 11)
+    need = 8 * n_k * int(np.prod(grid))
+    free = tdx.Context(0)
+    want = tdx.xc_kernel_grid(free, st, grid)
+    free.close()
+    small = tdx.Context(0)
+    small.set_workspace_limit(need - 1)
+    with pytest.raises(tdx.TdxError):
+        tdx.xc_kernel_grid(small, st, grid)
+    small.set_workspace_limit(need)
+    got = tdx.xc_kernel_grid(small, st, grid)
+    # sums of at most n_k nb positive terms in another order, then f_xc and
+    # the transform (|d ln f_xc / d ln n| <= 1)
+    size = float(want.abs().max())
+    assert float((got - want).abs().max()) <= (2 * n_k * nb + 2 * 64 + 800) * EPS * size * 4
+    small.close()
