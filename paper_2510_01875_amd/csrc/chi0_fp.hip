@@ -147,14 +147,14 @@ __device__ __attribute__((always_inline)) void chi0_tile_fp(
       for (int s = 0; s < C::kSteps; ++s) {
         const int tl = 2 * s + tau;
         const float2 rho = rq[tl * 16 + c16];
-        // a = w rho: its component `comp` for Re chi0, (Im a, -Re a)'s for Im
-        const float x = comp ? rho.y : rho.x, y = comp ? -rho.x : rho.y;
         float a[WPW], r[WPW];
 #pragma unroll
         for (int i = 0; i < WPW; ++i) {
           const float2 w = wt[wt_index<C>(tl, wave * WPW + i)];
-          a[i] = fmaf(w.x, x, -(w.y * y));
-          r[i] = fmaf(w.x, y, w.y * x);
+          const float are = w.x * rho.x - w.y * rho.y;
+          const float aim = w.x * rho.y + w.y * rho.x;
+          a[i] = comp ? aim : are;
+          r[i] = comp ? -are : aim;
         }
 #pragma unroll
         for (int b = 0; b < NSUB; ++b) {
@@ -234,7 +234,7 @@ int launch_fp(const void *P, int ld, const double *delta, const double *df, int 
 
 
 // ------------------------------------------------- all columns in one tile
-// Bases of 17 to 144 vectors.  The rows (w, G) of w_t(w) rho_t(G) are one list
+// Bases of 17 to 29 and of 33 to 144 vectors.  The rows (w, G) of w_t(w) rho_t(G) are one list
 // of n_w n_g, dealt to the waves in tiles of 16 whatever frequencies these
 // hold, against all columns G': no row is padding, one set of rho rows in LDS
 // (contiguous in memory) serves rows and columns, and a tile of A is formed
@@ -467,13 +467,16 @@ void chi0_fp32_shape(int v, int *wblock, int *cols, int *chunk) {
   *chunk = V.chunk;
 }
 
-// The launch of a basis of 17 to 144 vectors does not depend on the variant,
-// which still sets the slices (and so the order of the sums).
+// The launch of a basis of 17 to 144 vectors (but 30 to 32) does not depend on
+// the variant, which still sets the slices (and so the order of the sums).
 int chi0_fp32_launch(int v, const void *P, int ld, const double *delta, const double *df,
                      int paired, long long n_trans, long long slice_len, int slices,
                      const double *omega, int n_w, double eta, int n_g, double2 *part,
                      hipStream_t s) {
-  switch (ld / 16) {
+  // 30 to 32 vectors: hardly any padding to save, and the six row tiles of two
+  // column blocks spill (N_G 32, 700 frequencies, 2000 transitions: 240 us,
+  // 231 in the tiles of the variant; 29 and less come out ahead)
+  switch (ld == 32 && n_g > 29 ? 0 : ld / 16) {
 #define TDX_ROWS(N, R)                                                                         \
   case N:                                                                                      \
     return launch_rows<R, N>(P, delta, df, paired, n_trans, slice_len, slices, omega, n_w, eta, \
