@@ -322,16 +322,21 @@ __global__ void __launch_bounds__(256, 2)
       w[e] = tc + e / kF < t_hi ? v : make_float2(0.f, 0.f);
     }
   };
-  // a chunk's rows are contiguous: 1 KB pieces dealt to the waves in turn
-  // (past the list the last bytes again: their weights are zero)
+  // a chunk's rows are contiguous: 1 KB pieces dealt to the waves in turn.
+  // Past the list the last row again, each vector in its own column: the
+  // weights there are zero, and a value that is not finite spoils the sums of
+  // its own row and column of chi0 only.
   const char *Pb = (const char *)P;
-  const long long end = n_trans * kLd * 8 - 16;
   auto copy = [&](float2 *dst, long long tc) {
+    const char *src = Pb + tc * kLd * 8;
+    const bool whole = tc + kFlatChunk <= n_trans;  // uniform
+    const int last = (int)std::min<long long>(n_trans - tc, kFlatChunk) - 1;
 #pragma unroll
     for (int i = 0; i < kBytes / 4096; ++i) {
       const int o = 4096 * i + 1024 * wave;
-      dma16(Pb + std::min(tc * kLd * 8 + o + 16 * lane, end),
-            (unsigned int *)((char *)dst + o));
+      int at = o + 16 * lane;
+      if (!whole) at = std::min(at / (kLd * 8), last) * kLd * 8 + at % (kLd * 8);
+      dma16(src + at, (unsigned int *)((char *)dst + o));
     }
   };
   f32x4 ar[R][NSUB], ai[R][NSUB];

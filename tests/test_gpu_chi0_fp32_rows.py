@@ -62,3 +62,28 @@ def test_chi0_matches_the_defining_sum(tdx, ctx, n_g, n_w, n_t, paired):
     Pd = torch.from_numpy(P).cuda()
     got = tdx.chi0(ctx, tr, Pd, n_g, "fp32", torch.from_numpy(om).cuda(), ETA, PREF)
     assert np.all(np.abs(got.cpu().numpy().reshape(ref.shape) - ref) <= tol)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("n_g,n_t", [(48, 33), (64, 5), (113, 40), (144, 70)])
+def test_a_value_that_is_not_finite_stays_in_its_row_and_column(tdx, ctx, n_g, n_t, bad):
+    """The last transition's last vector, in a list that ends inside a chunk:
+    every entry outside that vector's row and column is the one of a list with
+    a zero in its place."""
+    import torch
+    print("chi0 fp32 rows, not finite", n_g, n_t, bad, flush=True)
+    n_w = 5
+    rng = np.random.default_rng(n_g + n_t)
+    tr = tdx.Transitions(n_t, 0, paired=True)
+    tr.delta.copy_(torch.from_numpy(rng.uniform(0.05, 1.5, n_t)))
+    tr.df.copy_(torch.from_numpy(rng.uniform(0.1, 1.0, n_t)))
+    P = np.zeros((n_t, (n_g + 15) // 16 * 16), dtype=np.complex64)
+    P[:, :n_g] = rng.standard_normal((n_t, n_g)) + 1j * rng.standard_normal((n_t, n_g))
+    om = torch.linspace(0.0, 2.0, n_w, dtype=torch.float64).cuda()
+    out = []
+    for x in (0.0, bad):
+        P[-1, n_g - 1] = x
+        out.append(tdx.chi0(ctx, tr, torch.from_numpy(P).cuda(), n_g, "fp32", om, ETA, PREF)
+                   .cpu().numpy().reshape(n_w, n_g, n_g))
+    assert np.array_equal(out[0][:, :-1, :-1], out[1][:, :-1, :-1])
+    assert not np.isfinite(out[1][:, -1, -1]).any()
