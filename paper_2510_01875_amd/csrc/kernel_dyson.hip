@@ -538,7 +538,8 @@ __device__ inline double2 cdiv(double2 a, double2 b) {
 //    and the displaced ones into their places as the columns to the right are
 //    solved against the panel's unit triangle (a thread per column);
 //  - the trailing matrix is updated once per panel on the FP64 MFMA from the
-//    panel's multipliers and solved rows in LDS.
+//    panel's multipliers and solved rows in LDS, whose products are summed from
+//    zero: an entry is rounded at its own size once a panel.
 // A panel is a serial chain (about 2800 cycles a column, of which the pivot
 // search and the row's way through LDS take most), so two workgroups share a
 // CU where LDS allows (n <= 144): one's panel runs beside the other's update.
@@ -864,13 +865,13 @@ __device__ __attribute__((always_inline)) int lu_factor(double2 *A, int n, const
       const int i0 = 16 * (t / mg), c0 = 32 * (t % mg) + c16;
       const bool two = c0 - c16 + 16 < m;  // uniform
       f64x4 cr[2], ci[2];
+      double2 old[2][4];
 #pragma unroll
-      for (int g = 0; g < 2; ++g)
+      for (int g = 0; g < 2; ++g) {
+        cr[g] = ci[g] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          cr[g][j] = nx[g][j].x;
-          ci[g][j] = nx[g][j].y;
-        }
+        for (int j = 0; j < 4; ++j) old[g][j] = nx[g][j];
+      }
       if (t + NT / 64 < pieces) load(t + NT / 64);
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
@@ -879,10 +880,10 @@ __device__ __attribute__((always_inline)) int lu_factor(double2 *A, int n, const
         for (int s = 0; s < 4; ++s) {
           const double2 l = w.L[(4 * s + kq) * w.mp + i0 + c16];
           const double2 u = w.U[(4 * s + kq) * w.mp + c0 + 16 * g];
-          cr[g] = mfma64(-l.x, u.x, cr[g]);
-          ci[g] = mfma64(-l.x, u.y, ci[g]);
-          cr[g] = mfma64(l.y, u.y, cr[g]);
-          ci[g] = mfma64(-l.y, u.x, ci[g]);
+          cr[g] = mfma64(l.x, u.x, cr[g]);
+          ci[g] = mfma64(l.x, u.y, ci[g]);
+          cr[g] = mfma64(-l.y, u.y, cr[g]);
+          ci[g] = mfma64(l.y, u.x, ci[g]);
         }
       }
 #pragma unroll
@@ -890,12 +891,33 @@ __device__ __attribute__((always_inline)) int lu_factor(double2 *A, int n, const
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int r = i0 + kq + 4 * j, c = c0 + 16 * g;
-          if (r < m && c < m) B[(unsigned)(r * n + c)] = make_double2(cr[g][j], ci[g][j]);
+          if (r < m && c < m) 
+            B[(unsigned)(r * n + c)] =
+                make_double2(old[g][j].x - cr[g][j], old[g][j].y - ci[g][j]);
         }
     }
     __syncthreads();
   }
   return 0;
+}
+
+// Products with the rows already solved are summed from zero, a block of 16 at a
+// time, and then subtracted: one at a time from the right-hand side each of
+// them is rounded at its size (errors of chi_00 against extended precision, N_G
+// 133: 1.07e-15 that way with the trailing update likewise, 7.9e-16 so; dot
+// products in a tree over the unblocked matrix 9.0e-16; N_G 17: 4.2, 3.4 and
+// 3.4e-16).
+
+// s += a b
+__device__ inline void cmadd(double2 &s, double2 a, double2 b) {
+  s.x = fma(a.x, b.x, fma(-a.y, b.y, s.x));
+  s.y = fma(a.x, b.y, fma(a.y, b.x, s.y));
+}
+
+// Lane c's (re, im) inv, in every lane.
+__device__ inline double2 lane_quotient(double re, double im, double2 inv, int c) {
+  const double x = fma(re, inv.x, -(im * inv.y)), y = fma(re, inv.y, im * inv.x);
+  return make_double2(lane_get(x, c), lane_get(y, c));
 }
 
 // Back substitution U x = b in blocks of 16 rows, x overwrites w.b, down to
@@ -920,17 +942,13 @@ __device__ __attribute__((always_inline)) void lu_back(const double2 *A, int n, 
     }
     if (tid < 64) {
       const int i = std::min(tid, nb - 1);
-      double2 x = w.b[k0 + i];
-      const double2 inv = w.rinv[k0 + i];
+      const double2 b = w.b[k0 + i], inv = w.rinv[k0 + i];
+      double2 sum = make_double2(0.0, 0.0);
 #pragma unroll
       for (int c = kNb - 1; c >= 0; --c) {
         if (c >= nb) continue;
-        const double2 y = make_double2(fma(x.x, inv.x, -(x.y * inv.y)), fma(x.x, inv.y, x.y * inv.x));
-        const double2 xc = make_double2(lane_get(y.x, c), lane_get(y.y, c));
-        if (tid < c) {
-          x.x = fma(-v[c].x, xc.x, fma(v[c].y, xc.y, x.x));
-          x.y = fma(-v[c].x, xc.y, fma(-v[c].y, xc.x, x.y));
-        }
+        const double2 xc = lane_quotient(b.x - sum.x, b.y - sum.y, inv, c);
+        if (tid < c) cmadd(sum, v[c], xc);
         if (tid == c) w.b[k0 + c] = xc;
       }
     }
@@ -942,15 +960,11 @@ __device__ __attribute__((always_inline)) void lu_back(const double2 *A, int n, 
 #pragma unroll
         for (int c = 0; c < kNb; ++c) u[c] = row[std::min(c, nb - 1)];
       }
-      double2 x = w.b[r];
+      double2 sum = make_double2(0.0, 0.0);
 #pragma unroll
-      for (int c = 0; c < kNb; ++c) {
-        if (c >= nb) continue;
-        const double2 y = w.b[k0 + c];
-        x.x = fma(-u[c].x, y.x, fma(u[c].y, y.y, x.x));
-        x.y = fma(-u[c].x, y.y, fma(-u[c].y, y.x, x.y));
-      }
-      w.b[r] = x;
+      for (int c = 0; c < kNb; ++c)
+        if (c < nb) cmadd(sum, u[c], w.b[k0 + c]);
+      w.b[r] = make_double2(w.b[r].x - sum.x, w.b[r].y - sum.y);
     }
     __syncthreads();
   }
@@ -1335,15 +1349,11 @@ __global__ void __launch_bounds__(NT, NT == 256 && RPL == 1 ? 2 : 1)
   // r[c] -= sum_i M[k0 + i][c] y[k0 + i] over the columns c0 <= c < c1
   auto apply = [&](int k0, int nb, int c0, int c1) {
     for (int c = c0 + tid; c < c1; c += NT) {
-      double2 x = y[c];
+      double2 sum = make_double2(0.0, 0.0);
 #pragma unroll
-      for (int i = 0; i < kNb; ++i) {
-        if (i >= nb) continue;
-        const double2 a = A[(size_t)(k0 + i) * n + c], b = y[k0 + i];
-        x.x = fma(-a.x, b.x, fma(a.y, b.y, x.x));
-        x.y = fma(-a.x, b.y, fma(-a.y, b.x, x.y));
-      }
-      y[c] = x;
+      for (int i = 0; i < kNb; ++i)
+        if (i < nb) cmadd(sum, A[(size_t)(k0 + i) * n + c], y[k0 + i]);
+      y[c] = make_double2(y[c].x - sum.x, y[c].y - sum.y);
     }
     __syncthreads();
   };
@@ -1352,19 +1362,15 @@ __global__ void __launch_bounds__(NT, NT == 256 && RPL == 1 ? 2 : 1)
     const int nb = std::min(kNb, n - k0);
     if (tid < 64) {
       const int j = std::min(tid, nb - 1);
-      double2 m[kNb], x = y[k0 + j];
+      double2 m[kNb], sum = make_double2(0.0, 0.0);
 #pragma unroll
       for (int i = 0; i < kNb; ++i) m[i] = A[(size_t)(k0 + std::min(i, nb - 1)) * n + k0 + j];
-      const double2 inv = w.rinv[k0 + j];
+      const double2 inv = w.rinv[k0 + j], r = y[k0 + j];
 #pragma unroll
       for (int i = 0; i < kNb; ++i) {
         if (i >= nb) continue;
-        const double2 z = make_double2(fma(x.x, inv.x, -(x.y * inv.y)), fma(x.x, inv.y, x.y * inv.x));
-        const double2 yi = make_double2(lane_get(z.x, i), lane_get(z.y, i));
-        if (tid > i) {
-          x.x = fma(-m[i].x, yi.x, fma(m[i].y, yi.y, x.x));
-          x.y = fma(-m[i].x, yi.y, fma(-m[i].y, yi.x, x.y));
-        }
+        const double2 yi = lane_quotient(r.x - sum.x, r.y - sum.y, inv, i);
+        if (tid > i) cmadd(sum, m[i], yi);
         if (tid == i) y[k0 + i] = yi;
       }
     }
@@ -1376,17 +1382,15 @@ __global__ void __launch_bounds__(NT, NT == 256 && RPL == 1 ? 2 : 1)
     const int nb = std::min(kNb, n - k0);
     if (tid < 64) {
       const int j = std::min(tid, nb - 1);
-      double2 m[kNb], x = y[k0 + j];
+      double2 m[kNb], sum = make_double2(0.0, 0.0);
 #pragma unroll
       for (int i = 0; i < kNb; ++i) m[i] = A[(size_t)(k0 + std::min(i, nb - 1)) * n + k0 + j];
+      const double2 r = y[k0 + j];
 #pragma unroll
       for (int i = kNb - 1; i >= 0; --i) {
         if (i >= nb) continue;
-        const double2 zi = make_double2(lane_get(x.x, i), lane_get(x.y, i));
-        if (tid < i) {
-          x.x = fma(-m[i].x, zi.x, fma(m[i].y, zi.y, x.x));
-          x.y = fma(-m[i].x, zi.y, fma(-m[i].y, zi.x, x.y));
-        }
+        const double2 zi = make_double2(lane_get(r.x - sum.x, i), lane_get(r.y - sum.y, i));
+        if (tid < i) cmadd(sum, m[i], zi);
         if (tid == i) y[k0 + i] = zi;
       }
     }

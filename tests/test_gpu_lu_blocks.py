@@ -83,3 +83,25 @@ def test_vanishing_pivot_is_reported(tdx, ctx, n, col):
     assert f"frequency 1 (column {col})" in str(err.value)
     with pytest.raises(tdx.TdxError):
         tdx.dyson_vjp(ctx, chi0, K, 0, torch.ones(3, dtype=torch.complex128, device="cuda"))
+
+
+@pytest.mark.parametrize("n", [33, 64, 133, 257, 304])
+def test_back_substitution_keeps_small_products(tdx, ctx, n):
+    """x_0 = (1 - sum_j u_0j x_j) / 2 with n - 1 products of 2^-54 each, every one
+    of which a running difference from 1 would lose."""
+    import torch
+    print("lu small products", n, flush=True)
+    chi0 = np.zeros((1, n, n), dtype=np.complex128)
+    chi0[0, 1:, 0], chi0[0, 0, 1:], chi0[0, 0, 0] = 2.0 ** -20, 2.0 ** -33, 1.0
+    K = -np.eye(n, dtype=np.complex128)
+    A = (np.eye(n) + chi0[0]).real
+    b = chi0[0, :, 0].real.astype(np.longdouble)
+    x = np.linalg.solve(A, b.astype(np.float64)).astype(np.longdouble)
+    for _ in range(3):
+        x += np.linalg.solve(A, (b - A.astype(np.longdouble) @ x).astype(np.float64))
+    got = tdx.dyson(ctx, torch.from_numpy(chi0).cuda(), torch.from_numpy(K).cuda(), 0)
+    got = got.cpu().numpy()[0]
+    # one rounding of half a unit for each block of 16 columns, six for the
+    # elimination of the right-hand side and the quotient
+    assert abs(np.longdouble(got.real) - x[0]) <= EPS * (n / 32 + 6) * x[0]
+    assert got.imag == 0.0
