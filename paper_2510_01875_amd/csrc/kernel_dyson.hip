@@ -667,7 +667,13 @@ __device__ __attribute__((always_inline)) void lu_panel(double2 *A, int n, int k
     }
     const double2 rc = crecip(piv);
     const double mx = wave_max(best);
-    const int pl = __ffsll((long long)__ballot(best == mx)) - 1;
+    // the lowest row of those: a lane's second row lies below all first ones
+    unsigned long long at_most = __ballot(best == mx);
+    if constexpr (RPL > 1) {
+      const unsigned long long upper = __ballot(best == mx && slot == 0);
+      if (upper) at_most = upper;
+    }
+    const int pl = __ffsll((long long)at_most) - 1;
     const int buf = (j & 1) * kWaves;
     if (lane == pl) {
       double2 *o = w.cand + (buf + wave) * kCand;

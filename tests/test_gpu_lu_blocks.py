@@ -105,3 +105,23 @@ def test_back_substitution_keeps_small_products(tdx, ctx, n):
     # elimination of the right-hand side and the quotient
     assert abs(np.longdouble(got.real) - x[0]) <= EPS * (n / 32 + 6) * x[0]
     assert got.imag == 0.0
+
+
+@pytest.mark.parametrize("n,low,high", [(133, 5, 70), (257, 5, 256), (300, 40, 259), (304, 130, 300)])
+def test_lowest_row_of_equal_pivots(tdx, ctx, n, low, high):
+    """Rows `low` and `high` tie in the first column: x_0 + x_low = 0 and
+    x_0 + 2^60 x_low = 2^60.  With the lower one first x_0 is -1 (to rounding);
+    the other order subtracts 2^60 from itself and finds 0."""
+    import torch
+    print("lu tie", n, low, high, flush=True)
+    A = np.eye(n)
+    A[0, 0] = A[high, high] = 0.0
+    A[low, 0] = A[high, 0] = A[0, high] = 1.0
+    A[high, low] = 2.0 ** 60
+    # 1 - chi0 K = A with K = -1; the right-hand side is column `low` of chi0 and
+    # v = e_low + K x
+    chi0 = torch.from_numpy((A - np.eye(n)).astype(np.complex128)[None]).cuda()
+    K = torch.from_numpy(-np.eye(n, dtype=np.complex128)).cuda()
+    cbar = torch.ones(1, dtype=torch.complex128, device="cuda")
+    _, v = tdx.dyson_vjp(ctx, chi0, K, low, cbar)
+    assert abs(complex(v[0, 0]) - 1.0) < 1e-12
