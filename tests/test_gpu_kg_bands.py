@@ -132,3 +132,45 @@ def test_extreme_broadening_takes_the_division(tdx, ctx):
     assert np.max(np.abs(tiny.imag - base.imag)) <= 1e-7 * scale
     huge = tdx.kg_conductivity(ctx, st, om, 1e145, 1e-3, tr=tr).cpu().numpy()
     assert np.all(np.isfinite(huge)) and np.max(np.abs(huge)) < 1e-140 * scale * 1e3
+
+
+@pytest.mark.parametrize("npw", [31, 64, 250, 480])
+def test_small_terms_of_a_momentum_element_are_kept(tdx, ctx, npw):
+    """One plane wave holds 1 of p_mn, each other 2^-54: a sum in one go would
+    lose them all."""
+    import torch
+    print("kg small terms", npw, flush=True)
+    nb = 2
+    d = tdx.StatesDims()
+    d.n_k, d.npw_max, d.nb_max = 1, npw, nb
+    st = tdx.States(d, 0)
+    coef = np.zeros((1, nb, npw), dtype=np.complex128)
+    coef[0, 1] = 1.0
+    coef[0, 0] = 2.0 ** -54
+    coef[0, 0, 0] = 1.0
+    mil = np.zeros((1, npw, 3), dtype=np.int32)
+    mil[..., 0] = 1
+    for t, x in ((st.npw, np.array([npw], dtype=np.int32)), (st.nb, np.array([nb], dtype=np.int32)),
+                 (st.miller, mil), (st.eps, np.array([[0.0, 0.5]])), (st.occ, np.array([[1.0, 0.0]])),
+                 (st.coef, coef)):
+        t.copy_(torch.from_numpy(x))
+    st.c.kgrid[:] = [1, 1, 1]
+    st.c.mmax[:] = [1, 1, 1]
+    st.c.bvec[:] = [1.0, 0, 0, 0, 1.0, 0, 0, 0, 1.0]
+    st.c.omega_cell = 1.0
+    tr = tdx.transitions(ctx, st, (0, 0, 0), 1e-3)
+    assert len(tr) == 2
+    om = torch.linspace(0.0, 2.0, 40, dtype=torch.float64)
+    eta = 0.25
+    got = tdx.kg_conductivity(ctx, st, om.cuda(), eta, 1e-3, tr=tr).cpu().numpy()
+    L = np.longdouble
+    p2 = (1 + (npw - 1) * L(2) ** -54) ** 2
+    x = om.numpy().astype(L)
+    dl, df = tr.delta.cpu().numpy().astype(L), tr.df.cpu().numpy().astype(L)
+    z = x[:, None] - dl + 1j * L(eta)
+    ref = 2j * ((df / dl * p2 / 3) / z).sum(1)
+    mag = 2 * (np.abs(df / dl * p2 / 3) / np.abs(z)).sum(1)
+    # half a unit lost per term of the large one's own 32 and per later block,
+    # twice as much of the square; 24 for the weight and its two quotients
+    tol = EPS * (32 + npw / 32 + 24) * mag
+    assert np.all(np.abs(got - ref) <= tol)
