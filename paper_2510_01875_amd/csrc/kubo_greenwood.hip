@@ -68,13 +68,20 @@ constexpr int kKgChunk = 2048;  // transitions per partial
 
 // First transitions of the rows (k, n) of the list, and n after the last row;
 // flag[0] is set if the list is not ordered by k, then n, then m (the rows are
-// then not used).
+// then not used).  A wave that sees the order broken says so once and stops:
+// every lane saying it, on one address, took 930 us for a list of 1.32 million
+// in reverse, and the gaps between the rows of a shuffled one, filled for each
+// of its transitions, 33 ms (7 us either way now, as for an ordered one).
 __global__ void k_kg_rows(const int *tk, const int *tn, const int *tm, int n, int nb_max,
                           long n_rows, int *rows, int *flag) {
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
     const long r = (long)tk[t] * nb_max + tn[t];
     const long before = t > 0 ? (long)tk[t - 1] * nb_max + tn[t - 1] : -1;
-    if (before > r || (before == r && tm[t - 1] >= tm[t])) *flag = 1;
+    if (__any(before > r || (before == r && tm[t - 1] >= tm[t]))) {
+      if ((threadIdx.x & 63) == 0 && !__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
     for (long i = before + 1; i <= r; ++i) rows[i] = t;
     if (t == n - 1)
       for (long i = r + 1; i <= n_rows; ++i) rows[i] = n;
@@ -264,48 +271,78 @@ __global__ void __launch_bounds__(64 * kKgWaves)
   }
 }
 
-// W_t for transitions [0, n): one wavefront per transition, for bases that do
-// not fit in LDS five bands at a time and lists in another order (flag null:
-// always; else only if it is set).
+// W_t for transitions [0, n), a wavefront per U of them, whose loads wait
+// together: for bases that do not fit in LDS five bands at a time (U = 1, flag
+// null, a workgroup per four) and for lists in another order (U = 2, only if the
+// flag is set, by 2048 workgroups, as more would cost the ordered lists the time
+// to start them).  Those of one XCD then take an eighth of the list, so that
+// its L2 holds the orbitals of the k they are at.  1.32 million transitions in
+// reverse: 1730 us, shuffled 2790 (one at a time, the whole list dealt to all in
+// turn: 2040 us in reverse, and 1500 with a workgroup per four).
+template <int U>
 __global__ void __launch_bounds__(256)
     k_kg_weights(const int *flag, const int *tk, const int *tn, const int *tm, const double *delta,
                  const double *df, long long n, const double2 *coef, const int *miller,
                  const int *npw, int npw_max, int nb_max, int N0, int N1, int N2, double3 b0,
                  double3 b1, double3 b2, double *W) {
   if (flag && !*flag) return;
-  const int lane = threadIdx.x & 63;
-  for (long long t = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); t < n; t += 4LL * gridDim.x) {
-    const int k = tk[t];
-    const int r0 = k / (N1 * N2), r1 = (k / N2) % N1, r2 = k % N2;
-    const double kr0 = (2.0 * r0 + 1.0 - N0) / (2.0 * N0), kr1 = (2.0 * r1 + 1.0 - N1) / (2.0 * N1),
-                 kr2 = (2.0 * r2 + 1.0 - N2) / (2.0 * N2);
-    const double2 *cn = coef + ((size_t)k * nb_max + tn[t]) * npw_max;
-    const double2 *cm = coef + ((size_t)k * nb_max + tm[t]) * npw_max;
-    const int *mk = miller + (size_t)k * npw_max * 3;
-    double p[3][2] = {{0, 0}, {0, 0}, {0, 0}};
-    for (int g = lane; g < npw[k]; g += 64) {
-      const double m0 = kr0 + mk[3 * g], m1 = kr1 + mk[3 * g + 1], m2 = kr2 + mk[3 * g + 2];
-      const double gx = m0 * b0.x + m1 * b1.x + m2 * b2.x;
-      const double gy = m0 * b0.y + m1 * b1.y + m2 * b2.y;
-      const double gz = m0 * b0.z + m1 * b1.z + m2 * b2.z;
-      const double2 a = cm[g], b = cn[g];
-      // conj(a) b
-      const double zr = a.x * b.x + a.y * b.y, zi = a.x * b.y - a.y * b.x;
-      p[0][0] += gx * zr; p[0][1] += gx * zi;
-      p[1][0] += gy * zr; p[1][1] += gy * zi;
-      p[2][0] += gz * zr; p[2][1] += gz * zi;
+  const int lane = threadIdx.x & 63, xcds = flag ? 8 : 1, xcd = blockIdx.x % xcds;
+  const long long end = n * (xcd + 1) / xcds, stride = 4LL * U * (gridDim.x / xcds);
+  for (long long t0 = n * xcd / xcds + U * (4LL * (blockIdx.x / xcds) + (threadIdx.x >> 6));
+       t0 < end; t0 += stride) {
+    int np[U], most = 0;
+    double kr[U][3];
+    const double2 *cn[U], *cm[U];
+    const int *mk[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long t = std::min(t0 + u, end - 1);
+      const int k = tk[t];
+      const int r0 = k / (N1 * N2), r1 = (k / N2) % N1, r2 = k % N2;
+      kr[u][0] = (2.0 * r0 + 1.0 - N0) / (2.0 * N0);
+      kr[u][1] = (2.0 * r1 + 1.0 - N1) / (2.0 * N1);
+      kr[u][2] = (2.0 * r2 + 1.0 - N2) / (2.0 * N2);
+      np[u] = npw[k];
+      most = std::max(most, np[u]);
+      cn[u] = coef + ((size_t)k * nb_max + tn[t]) * npw_max;
+      cm[u] = coef + ((size_t)k * nb_max + tm[t]) * npw_max;
+      mk[u] = miller + (size_t)k * npw_max * 3;
+    }
+    double p[U][3][2] = {};
+    for (int g = lane; g < most; g += 64) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = std::min(g, np[u] - 1);
+        const double2 a = cm[u][i], b = cn[u][i];
+        const double m0 = kr[u][0] + mk[u][3 * i], m1 = kr[u][1] + mk[u][3 * i + 1],
+                     m2 = kr[u][2] + mk[u][3 * i + 2];
+        if (g >= np[u]) continue;
+        const double gx = m0 * b0.x + m1 * b1.x + m2 * b2.x;
+        const double gy = m0 * b0.y + m1 * b1.y + m2 * b2.y;
+        const double gz = m0 * b0.z + m1 * b1.z + m2 * b2.z;
+        // conj(a) b
+        const double zr = a.x * b.x + a.y * b.y, zi = a.x * b.y - a.y * b.x;
+        p[u][0][0] += gx * zr; p[u][0][1] += gx * zi;
+        p[u][1][0] += gy * zr; p[u][1][1] += gy * zi;
+        p[u][2][0] += gz * zr; p[u][2][1] += gz * zi;
+      }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        p[a][0] += __shfl_xor(p[a][0], off);
-        p[a][1] += __shfl_xor(p[a][1], off);
-      }
-    if (lane == 0) {
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          p[u][a][0] += __shfl_xor(p[u][a][0], off);
+          p[u][a][1] += __shfl_xor(p[u][a][1], off);
+        }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long t = t0 + u;
+      if (lane > 0 || t >= end) continue;
       double s = 0.0;
 #pragma unroll
-      for (int a = 0; a < 3; ++a) s += p[a][0] * p[a][0] + p[a][1] * p[a][1];
+      for (int a = 0; a < 3; ++a) s += p[u][a][0] * p[u][a][0] + p[u][a][1] * p[u][a][1];
       W[t] = df[t] / delta[t] * (s / 3.0);
     }
   }
@@ -506,11 +543,16 @@ int tdx_kg_conductivity(tdx_ctx *ctx, const tdx_states *st, const tdx_translist 
                        st->kgrid[2], b0, b1, b2, W);
     TDX_HIP(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_kg_weights, dim3((unsigned)(by_band ? std::min<long long>(nb4, 2048) : nb4)),
-                     dim3(256), 0, s, by_band ? flag : nullptr, tl->k, tl->n, tl->m, tl->delta,
-                     tl->df, (long long)n_trans, (const double2 *)st->coef, st->miller, st->npw,
-                     st->npw_max, st->nb_max, st->kgrid[0], st->kgrid[1], st->kgrid[2], b0, b1, b2,
-                     W);
+#define TDX_KGW(U, GRID, FLAG)                                                                    \
+  hipLaunchKernelGGL(k_kg_weights<U>, dim3((unsigned)(GRID)), dim3(256), 0, s, FLAG, tl->k, tl->n, \
+                     tl->m, tl->delta, tl->df, (long long)n_trans, (const double2 *)st->coef,      \
+                     st->miller, st->npw, st->npw_max, st->nb_max, st->kgrid[0], st->kgrid[1],     \
+                     st->kgrid[2], b0, b1, b2, W)
+  if (by_band)
+    TDX_KGW(2, 2048, flag);
+  else
+    TDX_KGW(1, nb4, (const int *)nullptr);
+#undef TDX_KGW
   TDX_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_kg_partial, dim3((n_w + 63) / 64, (unsigned)n_chunks), dim3(256), 0, s, W,
                      tl->delta, (long long)n_trans, omega, n_w, eta, part);

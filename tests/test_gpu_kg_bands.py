@@ -174,3 +174,56 @@ def test_small_terms_of_a_momentum_element_are_kept(tdx, ctx, npw):
     # twice as much of the square; 24 for the weight and its two quotients
     tol = EPS * (32 + npw / 32 + 24) * mag
     assert np.all(np.abs(got - ref) <= tol)
+
+
+def _many_k(tdx, nk, nb, npw, seed, empty=()):
+    """Seeded states on an nk x 1 x 1 grid; the k of `empty` have no transition."""
+    import torch
+    rng = np.random.default_rng(seed)
+    d = tdx.StatesDims()
+    d.n_k, d.npw_max, d.nb_max = nk, max(npw), nb
+    st = tdx.States(d, 0)
+    mil = rng.integers(-4, 5, (nk, max(npw), 3)).astype(np.int32)
+    n = rng.choice(npw, nk).astype(np.int32)
+    coef = rng.standard_normal((nk, nb, max(npw))) + 1j * rng.standard_normal((nk, nb, max(npw)))
+    occ = np.where(np.arange(nb) < (nb + 1) // 2, rng.uniform(0.5, 1.0, (nk, nb)), 0.0)
+    occ[list(empty)] = 0.0
+    eps = np.cumsum(rng.uniform(0.05, 0.2, (nk, nb)), axis=1)
+    for t, x in ((st.npw, n), (st.nb, np.full(nk, nb, dtype=np.int32)), (st.miller, mil),
+                 (st.eps, eps), (st.occ, occ), (st.coef, coef)):
+        t.copy_(torch.from_numpy(x))
+    st.c.kgrid[:] = [nk, 1, 1]
+    st.c.mmax[:] = [4, 4, 4]
+    st.c.bvec[:] = [1.0, 0, 0, 0, 1.1, 0, 0, 0, 0.9]
+    st.c.omega_cell = 37.0
+    return st, n, mil, coef
+
+
+def test_a_shuffled_list_costs_its_weights_only(tdx, ctx):
+    """The gaps between the rows of a list in another order are not filled: it
+    takes about as long as one in which two transitions changed places."""
+    import time
+
+    import torch
+    st, *_ = _many_k(tdx, 125, 160, (60,), 3)
+    tr = tdx.transitions(ctx, st, (0, 0, 0), 1e-3)
+    T = len(tr)
+    print("kg shuffled", T, flush=True)
+    om = torch.linspace(0.0, 2.0, 8, device="cuda", dtype=torch.float64)
+    work = torch.empty(tdx.kg_work_bytes(T, 8), dtype=torch.uint8, device="cuda")
+    us = []
+    for perm in (np.r_[1, 0, 2:T], np.random.default_rng(1).permutation(T)):
+        out = tdx.Transitions(T, 0)
+        idx = torch.from_numpy(perm).cuda()
+        for a in ("k", "n", "m", "delta", "df"):
+            getattr(out, a).copy_(getattr(tr, a)[idx])
+        best = 1e9
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            tdx.kg_conductivity(ctx, st, om, 0.05, 1e-3, tr=out, work=work)
+            torch.cuda.synchronize()
+            best = min(best, time.perf_counter() - t0)
+        us.append(1e6 * best)
+    print(us, flush=True)
+    assert us[1] < 4.0 * us[0]
