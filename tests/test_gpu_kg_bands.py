@@ -199,6 +199,39 @@ def _many_k(tdx, nk, nb, npw, seed, empty=()):
     return st, n, mil, coef
 
 
+@pytest.mark.parametrize("nk,nb", [(150, 23), (701, 7), (90, 41)])
+def test_more_groups_of_bands_than_workgroups(tdx, ctx, nk, nb):
+    """Two workgroups per CU take the groups of five bands in turn: more groups
+    than those, eighths that are uneven, every seventh k without any."""
+    import torch
+    print("kg many k", nk, nb, flush=True)
+    st, n, mil, coef = _many_k(tdx, nk, nb, (8, 13, 20), nk, range(0, nk, 7))
+    tr = tdx.transitions(ctx, st, (0, 0, 0), 1e-3)
+    T = len(tr)
+    k, nn, mm = (x.cpu().numpy()[:T] for x in (tr.k, tr.n, tr.m))
+    delta, df = tr.delta.cpu().numpy()[:T], tr.df.cpu().numpy()[:T]
+    kf = mil + np.stack([(2.0 * np.arange(nk) + 1 - nk) / (2.0 * nk), 0 * np.arange(nk),
+                         0 * np.arange(nk)], -1)[:, None]
+    g = kf * np.array([1.0, 1.1, 0.9])
+    live = np.arange(max(n)) < n[:, None]
+    p = np.einsum("kmg,kga,kng->kanm", coef.conj() * live[:, None], g, coef)
+    a = np.einsum("kmg,kga,kng->kanm", np.abs(coef) * live[:, None], np.abs(g), np.abs(coef))
+    W = df / delta * (np.abs(p) ** 2).sum(1)[k, nn, mm] / 3.0
+    mag = np.abs(df / delta) * (a ** 2).sum(1)[k, nn, mm] / 3.0
+    om, eta = np.linspace(-1.0, 3.0, 160), 0.07
+    # the list's table of rows and groups fits in the space of the partial sums,
+    # and there are more groups than two workgroups on each of 256 CUs
+    groups = nk * -(-nb // 5)
+    assert 4 * (3 + nk * nb + groups) <= 16 * -(-T // 2048) * len(om) and groups * 6 // 7 > 512
+    den = om[:, None] - delta[None, :] + 1j * eta
+    pref = 2.0 / (37.0 * nk)
+    ref = 1j * pref * (W[None, :] / den).sum(axis=1)
+    steps = 2 * (2 * (2 * 20 + 12)) + 40 + 2 * T
+    tol = pref * steps * EPS * (mag[None, :] / np.abs(den)).sum(axis=1)
+    got = tdx.kg_conductivity(ctx, st, torch.as_tensor(om, device="cuda"), eta, 1e-3, tr=tr)
+    assert np.all(np.abs(got.cpu().numpy() - ref) <= tol)
+
+
 def test_a_shuffled_list_costs_its_weights_only(tdx, ctx):
     """The gaps between the rows of a list in another order are not filled: it
     takes about as long as one in which two transitions changed places."""
