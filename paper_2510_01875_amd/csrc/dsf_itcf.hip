@@ -32,45 +32,75 @@ __device__ inline double wave_sum(double x) {
   return x;
 }
 
+// c_j (e^{-tau w_j} + e^{-(beta - tau) w_j}), c the trapezoid's weight.
+__device__ inline double itcf_weight(const double *w, int j, int n, double beta, double t) {
+  const double wj = w[j];
+  double c = 0.0;
+  if (j > 0) c += 0.5 * (wj - w[j - 1]);
+  if (j + 1 < n) c += 0.5 * (w[j + 1] - wj);
+  return c * (exp(-t * wj) + exp(-(beta - t) * wj));
+}
+
 // F_s(tau) = sum_j c_j S_sj (e^{-tau w_j} + e^{-(beta - tau) w_j}) for the rows
-// S_s of n_set spectra: a block forms the kernel's values of one tau in LDS,
-// 1024 frequencies at a time, and its waves take the spectra in turn.  One
-// launch serves a whole filter bank: 86 launches of 4 us each were a third of
-// the attenuation search's 1.07 ms (their host side most of the rest).
+// S_s of n_set spectra.  A row's sum is 256 sums over the frequencies in strides
+// of 256, each in order, then those of 64 by shuffles and the four in order: the
+// same bits from both kernels.
+//
+// One spectrum: a block per tau, a stride per thread.
+__global__ void __launch_bounds__(256)
+    k_itcf_one(const double *S, const double *w, int n, double beta, const double *tau, double *F) {
+  __shared__ double sums[4];
+  const double t = tau[blockIdx.x];
+  double acc = 0.0;
+  for (int j = threadIdx.x; j < n; j += 256) acc = fma(itcf_weight(w, j, n, beta, t), S[j], acc);
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) F[blockIdx.x] = ((sums[0] + sums[1]) + sums[2]) + sums[3];
+}
+
+// Several: a block forms the weights of one tau in LDS, 1024 frequencies at a
+// time, and its waves take the spectra in turn, all 256 strides of one as four
+// per lane.  One launch serves a whole filter bank: 86 launches of 4 us each were
+// a third of the attenuation search's 1.07 ms (their host side most of the rest).
+// A single spectrum of a long grid would leave the sum to one wave here: 100000
+// frequencies, 65 tau: 322 us, 152 in the kernel above.
 constexpr int kItcfSets = 8;      // spectra per block, two per wave
-constexpr int kItcfChunk = 1024;  // kernel values in LDS
+constexpr int kItcfChunk = 1024;  // weights in LDS, a multiple of 256
 __global__ void __launch_bounds__(256)
     k_itcf(const double *S, int n_set, const double *w, int n, double beta, const double *tau,
            int n_tau, double *F) {
   __shared__ double e[kItcfChunk];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int s0 = blockIdx.y * kItcfSets + 2 * wave;
+  const int s0 = blockIdx.y * kItcfSets + wave;  // and four on
   const double t = tau[blockIdx.x];
-  double acc[2] = {0.0, 0.0};
+  double acc[2][4] = {};
   for (int j0 = 0; j0 < n; j0 += kItcfChunk) {
     const int m = min(kItcfChunk, n - j0);
     if (j0 > 0) __syncthreads();
-    for (int i = threadIdx.x; i < m; i += 256) {
-      const int j = j0 + i;
-      const double wj = w[j];
-      double c = 0.0;
-      if (j > 0) c += 0.5 * (wj - w[j - 1]);
-      if (j + 1 < n) c += 0.5 * (w[j + 1] - wj);
-      e[i] = c * (exp(-t * wj) + exp(-(beta - t) * wj));
-    }
+    for (int i = threadIdx.x; i < m; i += 256) e[i] = itcf_weight(w, j0 + i, n, beta, t);
     __syncthreads();
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-      if (s0 + x >= n_set) continue;
-      const double *row = S + (size_t)(s0 + x) * n + j0;
-      for (int i = lane; i < m; i += 64) acc[x] = fma(e[i], row[i], acc[x]);
+      if (s0 + 4 * x >= n_set) continue;
+      const double *row = S + (size_t)(s0 + 4 * x) * n + j0;
+      int i = lane;
+      for (; i + 192 < m; i += 256)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[x][q] = fma(e[i + 64 * q], row[i + 64 * q], acc[x][q]);
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        if (i + 64 * q < m) acc[x][q] = fma(e[i + 64 * q], row[i + 64 * q], acc[x][q]);
     }
   }
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
-    if (s0 + x >= n_set) continue;
-    const double f = wave_sum(acc[x]);
-    if (lane == 0) F[(size_t)(s0 + x) * n_tau + blockIdx.x] = f;
+    if (s0 + 4 * x >= n_set) continue;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[x][q] = wave_sum(acc[x][q]);
+    if (lane == 0)
+      F[(size_t)(s0 + 4 * x) * n_tau + blockIdx.x] =
+          ((acc[x][0] + acc[x][1]) + acc[x][2]) + acc[x][3];
   }
 }
 
@@ -190,6 +220,12 @@ int tdx_itcf_sets(tdx_ctx *ctx, const double *S, int n_set, const double *omega,
               "null argument");
   TDX_REQUIRE(n_w > 0 && n_tau > 0 && n_set >= 0, TDX_ERR_SHAPE, "bad sizes");
   TDX_REQUIRE(std::isfinite(beta) && beta > 0, TDX_ERR_INVALID_ARG, "bad beta");
+  if (n_set == 1) {
+    hipLaunchKernelGGL(k_itcf_one, dim3(n_tau), dim3(256), 0, as_stream(stream), S, omega, n_w,
+                       beta, tau, F);
+    TDX_HIP(hipGetLastError());
+    return TDX_OK;
+  }
   // the grid's second axis holds 65535 blocks
   constexpr int kMost = 65535 * kItcfSets;
   for (int s0 = 0; s0 < n_set; s0 += kMost) {

@@ -36,3 +36,27 @@ def test_rows_equal_single_calls(n_set, n_w, n_tau):
     for i in range(n_set):
         assert torch.equal(F[i], tdx.itcf(ctx, dev(S[i].copy()), dev(om), beta, dev(tau)))
     ctx.close()
+
+
+@pytest.mark.parametrize("n_set,n_w", [(1, 100001), (2, 100001), (6, 20000), (1, 8193), (9, 4097)])
+def test_strides_of_long_grids(n_set, n_w):
+    """Sixty-four large terms and then small ones of 2^-54 of them: 256 strides
+    lose a quarter of these (in one wave's 64, all of them)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2510_01875_amd as tdx
+    print("itcf strides", n_set, n_w, flush=True)
+    ctx = tdx.Context(0)
+    om = torch.arange(n_w, dtype=torch.float64) * 2.0 ** -10
+    tau = torch.zeros(1, dtype=torch.float64)
+    S = torch.full((n_set, n_w), 2.0 ** -54, dtype=torch.float64)
+    S[:, :64] = 1.0
+    # beta so small that each exponential is 1: the weight is twice the step,
+    # half of that at the ends
+    F = tdx.itcf_sets(ctx, S.cuda(), om.cuda(), 1e-30, tau.cuda()).cpu().numpy()[:, 0]
+    ctx.close()
+    ref = (np.longdouble(63.5) + (n_w - 64 - np.longdouble(0.5)) * np.longdouble(2) ** -54) * 2.0 ** -9
+    # 2^-54 lost for a third of the terms at most; eight roundings of the tree
+    tol = (n_w / 3 * 2.0 ** -54 + 8 * 2.0 ** -53 * 64) * 2.0 ** -9
+    assert np.all(np.abs(F - ref) <= tol)
