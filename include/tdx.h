@@ -80,7 +80,10 @@ const char *tdx_last_error(void);
 int tdx_abi_version(void);
 /* Cap on the library-owned workspace (bytes, 0 = no cap).  A call whose
  * workspace would exceed the cap fails with TDX_ERR_ALLOC before it writes
- * any output. */
+ * any output.  Results do not depend on the cap; the density and its adjoint
+ * (tdx_xc_kernel_grid, tdx_kernel_matrix, tdx_density_vjp) take longer under
+ * one, as they then hold one partial density per k instead of up to 16.  A cap
+ * set after use gives back what they held beyond that. */
 int tdx_set_workspace_limit(tdx_ctx *ctx, size_t bytes);
 
 /* ------------------------------------------------------------------ */

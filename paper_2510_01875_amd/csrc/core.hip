@@ -181,6 +181,13 @@ int tdx_set_workspace_limit(tdx_ctx *ctx, size_t bytes) {
   clear_error();
   TDX_REQUIRE(ctx, TDX_ERR_INVALID_ARG, "ctx is null");
   ctx->limit = bytes;
+  // what only contexts without a limit hold (no call in flight uses it: the
+  // density calls, the only ones that do, synchronise)
+  Workspace &w = ctx->ws[WS_DENS_SLICES];
+  if (bytes && w.ptr) {
+    TDX_HIP(hipFree(w.ptr));
+    w = Workspace();
+  }
   return TDX_OK;
 }
 

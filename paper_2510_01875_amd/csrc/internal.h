@@ -60,7 +60,7 @@ struct tdx_ctx {
   int n_cu = 0;
   rocblas_handle blas = nullptr;
   size_t limit = 0;  // 0 = unlimited
-  tdx::Workspace ws[12];
+  tdx::Workspace ws[13];
   tdx_chi0_tune tune[3][64];  // [prec][size class]
   long long slice_len = 0;  // chi0 slice length; 0 = chosen per call to fill the chip
 };
@@ -80,6 +80,7 @@ enum WsSlot {
   WS_ADJ2 = 9,      // adjoint: eigen-adjoint products
   WS_ADJ3 = 10,     // adjoint: reductions
   WS_FXC = 11,      // f_xc(G) grid of the composed kernel-matrix call
+  WS_DENS_SLICES = 12,  // density partials beyond one per k; none under a limit
 };
 
 size_t ws_total(const tdx_ctx *ctx);

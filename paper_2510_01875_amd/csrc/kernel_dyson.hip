@@ -217,21 +217,20 @@ __device__ void make_twiddles(double2 *tw, int N0, int N1, int N2) {
 constexpr int kDensThreads = 512;
 constexpr int kDensPoints = 160 * 1024 / 16 / kDensThreads;  // per thread, of what LDS holds
 
-// Workgroups per k: about four per CU in all, each a share of the bands; one
-// where the workspace is limited (each keeps a partial of its own).
+// Partial sums of a k: about four per CU in all, each a share of the bands.
 inline int dens_slices(const tdx_ctx *ctx, int n_k) {
-  if (ctx->limit) return 1;
   return std::max(1, std::min(16, (4 * ctx->n_cu + n_k - 1) / std::max(n_k, 1)));
 }
 
-// Density partials: dens[k][slice][j] = sum_n f_nk |u_nk(r_j)|^2 over the bands
-// n = slice, slice + slices, ..  Grid (n_k, slices).  FP64 issue is the bound.
-// 64 k of up to 480 plane waves (reach 5) on a 20^3 grid: 4928 us with one
-// workgroup per k, a thread per pencil (its values in scratch memory) and all
-// places summed; 267 us.
+// Density partials: dens[k][y] = sum_n f_nk |u_nk(r_j)|^2 over the bands n = p,
+// p + slices, .. for each p = y, y + gridDim.y, .., these sums added in order.
+// Grid (n_k, slices), or (n_k, 1) where a partial per slice has no room.  FP64
+// issue is the bound.  64 k of up to 480 plane waves (reach 5) on a 20^3 grid:
+// 4928 us with one workgroup per k, a thread per pencil (its values in scratch
+// memory) and all places summed; 267 us.
 __global__ void __launch_bounds__(kDensThreads)
     k_density(const double2 *coef, const double *occ, const int *nb, const int *npw,
-              const int *miller, int nb_max, int npw_max, int N0, int N1, int N2,
+              const int *miller, int nb_max, int npw_max, int N0, int N1, int N2, int slices,
               double *dens) {
   extern __shared__ double2 sm[];
   const int N[3] = {N0, N1, N2}, Nr = N0 * N1 * N2;
@@ -242,40 +241,66 @@ __global__ void __launch_bounds__(kDensThreads)
   int act[3];
   make_twiddles(tw, N0, N1, N2);
   dft_reach(mk, np, N, (int *)box, act);
-  double sum[kDensPoints];
-#pragma unroll
-  for (int i = 0; i < kDensPoints; ++i) sum[i] = 0.0;
-  each_orbital(box, tw, N, act, coef + (size_t)k * nb_max * npw_max, occ + (size_t)k * nb_max, mk,
-               blockIdx.y, gridDim.y, nb[k], np, npw_max, [&](int, double f) {
-#pragma unroll
-                 for (int i = 0; i < kDensPoints; ++i) {
-                   const int j = threadIdx.x + i * kDensThreads;
-                   if (j < Nr) {
-                     const double2 u = box[j];
-                     sum[i] = fma(f, u.x * u.x + u.y * u.y, sum[i]);
-                   }
-                 }
-               });
   double *out = dens + ((size_t)k * gridDim.y + blockIdx.y) * Nr;
+  for (int p = blockIdx.y; p < slices; p += gridDim.y) {
+    double sum[kDensPoints];
 #pragma unroll
-  for (int i = 0; i < kDensPoints; ++i) {
-    const int j = threadIdx.x + i * kDensThreads;
-    if (j < Nr) out[j] = sum[i];
+    for (int i = 0; i < kDensPoints; ++i) sum[i] = 0.0;
+    each_orbital(box, tw, N, act, coef + (size_t)k * nb_max * npw_max, occ + (size_t)k * nb_max, mk,
+                 p, slices, nb[k], np, npw_max, [&](int, double f) {
+#pragma unroll
+                   for (int i = 0; i < kDensPoints; ++i) {
+                     const int j = threadIdx.x + i * kDensThreads;
+                     if (j < Nr) {
+                       const double2 u = box[j];
+                       sum[i] = fma(f, u.x * u.x + u.y * u.y, sum[i]);
+                     }
+                   }
+                 });
+#pragma unroll
+    for (int i = 0; i < kDensPoints; ++i) {
+      const int j = threadIdx.x + i * kDensThreads;
+      if (j < Nr) out[j] = p == (int)blockIdx.y ? sum[i] : out[j] + sum[i];
+    }
   }
 }
 
-// Sum of n partials [n][Nr] at point j = 32 block + (thread & 31), for the
-// first 32 of 256 threads: eight strided sums, then those in order.
-__device__ double sum_partials(const double *dens, int n, int Nr, int j) {
+// Sum of the partials [n_k][per_k][Nr] at point j = 32 block + (thread & 31),
+// for the first 32 of 256 threads: those of a k in order, the k in eight
+// strided sums, then these in order.
+__device__ double sum_partials(const double *dens, int n_k, int per_k, int Nr, int j) {
   __shared__ double part[8][32];
   const int lane = threadIdx.x & 31, row = threadIdx.x >> 5;
   double s = 0.0;
   if (j < Nr)
-    for (int k = row; k < n; k += 8) s += dens[(size_t)k * Nr + j];
+    for (int k = row; k < n_k; k += 8) {
+      const double *of = dens + (size_t)k * per_k * Nr + j;
+      double d = of[0];
+#pragma unroll 4
+      for (int p = 1; p < per_k; ++p) d += of[(size_t)p * Nr];
+      s += d;
+    }
   part[row][lane] = s;
   __syncthreads();
   for (int i = 1; i < 8; ++i) s += part[i][lane];  // row 0 holds its own
   return s;
+}
+
+// Where a call's density partials go: a partial per slice in a workspace of its
+// own, which a workspace limit gives back (only the density calls use it, and
+// they synchronise), or the one per k that `one` holds where there is a limit
+// or no room.  The sums are the same bits either way.
+double *dens_partials(tdx_ctx *ctx, int n_k, int slices, int Nr, double *one, int *per_k) {
+  *per_k = 1;
+  if (ctx->limit || slices == 1) return one;
+  void *w;
+  if (ws_get(ctx, WS_DENS_SLICES, sizeof(double) * (size_t)n_k * slices * Nr, &w) != TDX_OK) {
+    (void)hipGetLastError();
+    clear_error();
+    return one;
+  }
+  *per_k = slices;
+  return (double *)w;
 }
 
 __device__ void pw92(double rs, double *e, double *e1, double *e2) {
@@ -297,9 +322,9 @@ __device__ void pw92(double rs, double *e, double *e1, double *e2) {
 
 // Sum the density partials, scale, apply f_xc(n) pointwise; 32 points a block.
 __global__ void __launch_bounds__(256)
-    k_fxc_real(const double *dens, int parts, int Nr, double scale, double2 *fx) {
+    k_fxc_real(const double *dens, int n_k, int per_k, int Nr, double scale, double2 *fx) {
   const int j = blockIdx.x * 32 + (threadIdx.x & 31);
-  const double s = sum_partials(dens, parts, Nr, j);
+  const double s = sum_partials(dens, n_k, per_k, Nr, j);
   if (threadIdx.x >= 32 || j >= Nr) return;
   const double n = s * scale;
   const double fxv = -(1.0 / 3.0) * cbrt(3.0 / M_PI) * pow(n, -2.0 / 3.0);
@@ -1505,10 +1530,10 @@ __global__ void k_fbar(const double2 *Phi, const double2 *T, int n_g, int Nr, do
 
 // nbar[j] = fbar[j] f_xc'(n(r_j)), n from the density partials; 32 points a block.
 __global__ void __launch_bounds__(256)
-    k_nbar(const double *dens, int parts, int Nr, double scale, const double *fbar,
+    k_nbar(const double *dens, int n_k, int per_k, int Nr, double scale, const double *fbar,
            double *nbar) {
   const int j = blockIdx.x * 32 + (threadIdx.x & 31);
-  const double s = sum_partials(dens, parts, Nr, j);
+  const double s = sum_partials(dens, n_k, per_k, Nr, j);
   if (threadIdx.x >= 32 || j >= Nr) return;
   nbar[j] = fbar[j] * fxc_deriv(s * scale);
 }
@@ -1696,20 +1721,21 @@ int tdx_xc_kernel_grid(tdx_ctx *ctx, const tdx_states *st, const int dens_grid[3
   hipStream_t s = as_stream(stream);
   const int N0 = dens_grid[0], N1 = dens_grid[1], N2 = dens_grid[2];
   void *w;
-  const int slices = dens_slices(ctx, st->n_k), parts = st->n_k * slices;
-  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * (size_t)parts * Nr, &w));
-  double *dens = (double *)w;
+  const int slices = dens_slices(ctx, st->n_k);
+  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * (size_t)st->n_k * Nr, &w));
+  int per_k;
+  double *dens = dens_partials(ctx, st->n_k, slices, Nr, (double *)w, &per_k);
   TDX_HIP(hipFuncSetAttribute((const void *)k_density, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds));
   TDX_HIP(hipFuncSetAttribute((const void *)k_fxc_forward,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(k_density, dim3(st->n_k, slices), dim3(kDensThreads), lds, s, (const double2 *)st->coef,
-                     st->occ, st->nb, st->npw, st->miller, st->nb_max, st->npw_max, N0, N1, N2,
-                     dens);
+  hipLaunchKernelGGL(k_density, dim3(st->n_k, per_k), dim3(kDensThreads), lds, s,
+                     (const double2 *)st->coef, st->occ, st->nb, st->npw, st->miller, st->nb_max,
+                     st->npw_max, N0, N1, N2, slices, dens);
   TDX_HIP(hipGetLastError());
   const double scale = 2.0 / (st->n_k * st->omega_cell);
-  hipLaunchKernelGGL(k_fxc_real, dim3((Nr + 31) / 32), dim3(256), 0, s, dens, parts, Nr, scale,
-                     (double2 *)fxg);
+  hipLaunchKernelGGL(k_fxc_real, dim3((Nr + 31) / 32), dim3(256), 0, s, dens, st->n_k, per_k, Nr,
+                     scale, (double2 *)fxg);
   TDX_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_fxc_forward, dim3(1), dim3(kDensThreads), lds, s, (double2 *)fxg, N0, N1,
                      N2);
@@ -1915,20 +1941,22 @@ int tdx_density_vjp(tdx_ctx *ctx, const tdx_states *st, const int dens_grid[3],
   hipStream_t s = as_stream(stream);
   const int N0 = dens_grid[0], N1 = dens_grid[1], N2 = dens_grid[2];
   void *w;
-  const int slices = dens_slices(ctx, st->n_k), parts = st->n_k * slices;
-  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * ((size_t)parts + 1) * Nr, &w));
-  double *dens = (double *)w, *nbar = dens + (size_t)parts * Nr;
+  const int slices = dens_slices(ctx, st->n_k);
+  TDX_TRY(ws_get(ctx, WS_DENS, sizeof(double) * ((size_t)st->n_k + 1) * Nr, &w));
+  int per_k;
+  double *nbar = (double *)w + (size_t)st->n_k * Nr;
+  double *dens = dens_partials(ctx, st->n_k, slices, Nr, (double *)w, &per_k);
   TDX_HIP(hipFuncSetAttribute((const void *)k_density, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds));
   TDX_HIP(hipFuncSetAttribute((const void *)k_density_vjp,
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(k_density, dim3(st->n_k, slices), dim3(kDensThreads), lds, s, (const double2 *)st->coef,
-                     st->occ, st->nb, st->npw, st->miller, st->nb_max, st->npw_max, N0, N1, N2,
-                     dens);
+  hipLaunchKernelGGL(k_density, dim3(st->n_k, per_k), dim3(kDensThreads), lds, s,
+                     (const double2 *)st->coef, st->occ, st->nb, st->npw, st->miller, st->nb_max,
+                     st->npw_max, N0, N1, N2, slices, dens);
   TDX_HIP(hipGetLastError());
   const double scale = 2.0 / (st->n_k * st->omega_cell);
-  hipLaunchKernelGGL(k_nbar, dim3((Nr + 31) / 32), dim3(256), 0, s, dens, parts, Nr, scale, fxc_bar,
-                     nbar);
+  hipLaunchKernelGGL(k_nbar, dim3((Nr + 31) / 32), dim3(256), 0, s, dens, st->n_k, per_k, Nr,
+                     scale, fxc_bar, nbar);
   TDX_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_density_vjp, dim3(st->n_k, slices), dim3(kDensThreads), lds, s, (const double2 *)st->coef,
                      st->occ, st->nb, st->npw, st->miller, st->nb_max, st->npw_max, N0, N1, N2,

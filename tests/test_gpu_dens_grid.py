@@ -139,3 +139,31 @@ def test_a_limited_workspace_holds_one_partial_per_k(tdx):
     size = float(want.abs().max())
     assert float((got - want).abs().max()) <= (2 * n_k * nb + 2 * 64 + 800) * EPS * size * 4
     small.close()
+
+
+@pytest.mark.parametrize("n_k,nb", [(1, 40), (3, 12), (70, 3)])
+def test_a_limit_changes_neither_results_nor_what_fits(tdx, n_k, nb):
+    """The kernel grid and the adjoint with and without a limit are the same bits,
+    and a limit set after use leaves the room that it leaves a new context."""
+    import torch
+    print("dens limit", n_k, nb, flush=True)
+    grid = (9, 8, 10)
+    Nr = int(np.prod(grid))
+    st, n, _, coef, _ = _system(tdx, (2, 3, 4), 60, nb, n_k, 5 * n_k)
+    fbar = torch.linspace(-1.0, 1.0, Nr, dtype=torch.float64, device="cuda")
+    c = tdx.Context(0)
+    out = []
+    for _ in range(2):
+        ob = torch.zeros(n_k, nb, dtype=torch.float64, device="cuda")
+        cb = torch.zeros(coef.shape, dtype=torch.complex128, device="cuda")
+        f = tdx.xc_kernel_grid(c, st, grid).clone()
+        tdx.density_vjp(c, st, grid, fbar, ob, cb)
+        out.append((f, ob, cb))
+        # the partials and the adjoint's grid (a slot grows by a quarter at least)
+        # and the Dyson solve below
+        c.set_workspace_limit(2 * max(4 * n_k + 4, 5 * n_k) * Nr + 16 * 4 * 20 * 20 + 4 * 4)
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    chi0 = torch.zeros(4, 20, 20, dtype=torch.complex128, device="cuda")
+    tdx.dyson(c, chi0, torch.eye(20, dtype=torch.complex128, device="cuda"), 0)
+    c.close()
