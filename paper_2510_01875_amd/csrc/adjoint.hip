@@ -452,12 +452,16 @@ int vjp_launch(int n_cu, const double2 *P, int ld, long long t_lo, long long n, 
   const size_t red = sizeof(double2) * kWaves * 2 * 256;
   int tt = 1;
   long long best = 0;
+  bool tt_fits = false;
   for (int x = 1; x <= kWaves; x *= 2) {
     if (sizeof(double2) * 16 * x * (ld + 1) > 160 * 1024) break;
     const long long wgs = (n + 16 * x - 1) / (16 * x);
     const int ww = kWaves / x;
     const long long cost = ((wgs + n_cu - 1) / n_cu) * ((n_wt + ww - 1) / ww);
-    if (x == 1 || cost < best) tt = x, best = cost;
+    // a launch holds less than 2^32 threads: lists of 134 million transitions
+    // and more take the tiles that fit
+    const bool fits = 64LL * kWaves * wgs < (1LL << 32);
+    if (x == 1 || (fits && (cost < best || !tt_fits))) tt = x, best = cost, tt_fits = fits;
   }
   const size_t lds = std::max(red, sizeof(double2) * 16 * tt * (ld + 1));
   const long long blocks = (n + 16 * tt - 1) / (16 * tt);

@@ -83,3 +83,35 @@ def test_cotangents_match_the_defining_sums(tdx, ctx, n_g, n_t, n_w, paired):
             assert np.all(got[:, n_g:] == 0.0)
         else:
             assert rho_bar is None
+
+
+def test_more_transitions_than_one_tile_each_launches(tdx, ctx):
+    """2^27 + 5 transitions, all alike: with 16 of them per workgroup of 512
+    threads the launch would hold 2^32 threads."""
+    import torch
+    n_t, n_g, n_w = (1 << 27) + 5, 2, 128
+    print("vjp many transitions", n_t, flush=True)
+    if torch.cuda.mem_get_info()[0] < (48 << 30):
+        pytest.skip("needs 48 GiB")
+    rng = np.random.default_rng(1)
+    u, v = (rng.standard_normal((n_w, n_g)) + 1j * rng.standard_normal((n_w, n_g)) for _ in range(2))
+    om = np.linspace(0.0, 2.0, n_w)
+    dl, df, rho = 0.7, 0.4, np.array([1.0 + 0.5j, -0.25 + 2.0j])
+    tr = tdx.Transitions(n_t, 0, paired=False)
+    tr.delta.fill_(dl)
+    tr.df.fill_(df)
+    P = torch.zeros(n_t, 16, dtype=torch.complex128, device="cuda")
+    P[:, 0], P[:, 1] = complex(rho[0]), complex(rho[1])
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()  # noqa: E731
+    w_bar, _ = tdx.chi0_vjp(ctx, tr, P, n_g, dev(om), ETA, PREF, dev(u), dev(v))
+    del P
+    al, be = u.conj() @ rho, v.conj() @ rho
+    r = 1.0 / (om - dl + 1j * ETA)
+    lam = PREF * al * be.conj()
+    want = np.array([(lam * r).real.sum(), df * (lam * r * r).real.sum(), df * (lam * r * r).imag.sum()])
+    # products of sums of n_g terms, their weights and the sum over frequencies
+    mag = np.abs(PREF) * (np.abs(u) @ np.abs(rho)) * (np.abs(v) @ np.abs(rho)) * np.abs(r)
+    tol = 2 * EPS * (n_w + 40) * np.array([mag.sum(), df * (mag * np.abs(r)).sum(),
+                                           df * (mag * np.abs(r)).sum()])
+    bad = (w_bar - dev(want)).abs() > dev(tol)
+    assert not bool(bad.any())
