@@ -6,6 +6,7 @@
 // are bitwise reproducible.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -270,7 +271,17 @@ __device__ inline void vjp_weight(double w, double dl, double dft, double eta, d
 // and written per 64 frequencies, 2071 us (51 TFLOP/s of the 73 that the MFMA
 // reaches; 57 with the padding); 200 transitions, 300 vectors, 100
 // frequencies: 456 to 122 us; 5000, 300, 300: 1494 to 563 us.
-template <int kTiles, int kWaves>
+//
+// A sum of rhobar in one accumulator holds at most 64 frequencies.  With one wave
+// per SIMD each 16 of them are summed from zero and added; two waves have no
+// registers for that (133 vectors: 2838 us), so that a wave that has more than
+// kVjpRun tiles of frequencies (RUNS) adds the workgroup's sums in global memory
+// after each kVjpRun of them.  60 vectors, 1000 frequencies: error against extended
+// precision 9.8e-16 in one sum, 8.0e-16 so (7.8e-16 with 64 frequencies at a time
+// through global memory); 300, 800: 1.5, 1.2 and 1.3e-15, 3 % slower.
+constexpr int kVjpRun = 4;
+
+template <int kTiles, int kWaves, bool RUNS>
 __global__ void __launch_bounds__(64 * kWaves, kWaves / 4)
     k_chi0_vjp(const double2 *P, int ld, long long t_lo, long long n_trans, int n_g,
                const double *delta, const double *df, int paired, const double *omega, int n_w,
@@ -282,12 +293,6 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves / 4)
   const int col = lane & 15, quad = lane >> 4;
   const int ww = kWaves / tt, tile = wave / ww, share = wave % ww;
   const long long tb = (long long)blockIdx.x * 16 * tt;
-  for (int e = tid; e < 16 * tt * ld; e += 64 * kWaves) {
-    const int r = e / ld, c = e % ld;
-    vjp_lds[r * (ld + 1) + c] =
-        tb + r < n_trans && c < n_g ? P[(size_t)(tb + r) * ld + c] : make_double2(0.0, 0.0);
-  }
-  __syncthreads();
   const long long t = tb + 16 * tile + col;
   const long long tc = t < n_trans ? t : n_trans - 1;
   const double dl = delta[t_lo + tc], dft = df[t_lo + tc];
@@ -295,130 +300,154 @@ __global__ void __launch_bounds__(64 * kWaves, kWaves / 4)
   const int n_wt = (n_w + 15) / 16, n_gt = ld / 16, last = n_g - 1;
   constexpr bool kAhead = kWaves == 4;
   VjpSums sums;
-  f64x4 out[kTiles][2];
+  const int run = RUNS ? kVjpRun * ww : n_wt;
+  int w0 = 0;
+  do {
+    if (w0 > 0) __syncthreads();
+    for (int e = tid; e < 16 * tt * ld; e += 64 * kWaves) {
+      const int r = e / ld, c = e % ld;
+      vjp_lds[r * (ld + 1) + c] =
+          tb + r < n_trans && c < n_g ? P[(size_t)(tb + r) * ld + c] : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+    f64x4 out[kTiles][2];
 #pragma unroll
-  for (int g = 0; g < kTiles; ++g) out[g][0] = out[g][1] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int wt = share; wt < n_wt; wt += ww) {
-    f64x4 ab[4];  // alpha, beta: real and imaginary parts
+    for (int g = 0; g < kTiles; ++g) out[g][0] = out[g][1] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const int w1 = RUNS ? std::min(n_wt, w0 + run) : n_wt;
+    for (int wt = w0 + share; wt < w1; wt += ww) {
+      f64x4 ab[4];  // alpha, beta: real and imaginary parts
 #pragma unroll
-    for (int x = 0; x < 4; ++x) ab[x] = f64x4{0.0, 0.0, 0.0, 0.0};
-    const size_t row = (size_t)std::min(16 * wt + col, n_w - 1) * n_g;
-    // past n_g rho is zero
-    auto load_rows = [&](double2 (&a)[2][4], int g) {
+      for (int x = 0; x < 4; ++x) ab[x] = f64x4{0.0, 0.0, 0.0, 0.0};
+      const size_t row = (size_t)std::min(16 * wt + col, n_w - 1) * n_g;
+      // past n_g rho is zero
+      auto load_rows = [&](double2 (&a)[2][4], int g) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const size_t k = row + std::min(16 * g + 4 * quad + i, last);
-        a[0][i] = u[k];
-        a[1][i] = v[k];
-      }
-    };
-    double2 next[2][4];
-    if (kAhead) load_rows(next, 0);
-    for (int g = 0; g < n_gt; ++g) {
-      double2 a[2][4], b[4];
-      if (!kAhead) load_rows(a, g);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (kAhead) {
-          a[0][i] = next[0][i];
-          a[1][i] = next[1][i];
+        for (int i = 0; i < 4; ++i) {
+          const size_t k = row + std::min(16 * g + 4 * quad + i, last);
+          a[0][i] = u[k];
+          a[1][i] = v[k];
         }
-        b[i] = brow[16 * g + i];
-      }
-      if (kAhead && g + 1 < n_gt) load_rows(next, g + 1);
+      };
+      double2 next[2][4];
+      if (kAhead) load_rows(next, 0);
+      for (int g = 0; g < n_gt; ++g) {
+        double2 a[2][4], b[4];
+        if (!kAhead) load_rows(a, g);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        // conj(a) b
-        ab[0] = mfma64(a[0][i].x, b[i].x, ab[0]);
-        ab[1] = mfma64(a[0][i].x, b[i].y, ab[1]);
-        ab[2] = mfma64(a[1][i].x, b[i].x, ab[2]);
-        ab[3] = mfma64(a[1][i].x, b[i].y, ab[3]);
-        ab[0] = mfma64(a[0][i].y, b[i].y, ab[0]);
-        ab[1] = mfma64(-a[0][i].y, b[i].x, ab[1]);
-        ab[2] = mfma64(a[1][i].y, b[i].y, ab[2]);
-        ab[3] = mfma64(-a[1][i].y, b[i].x, ab[3]);
-      }
-    }
-    // lane holds frequency 16 wt + quad + 4 j, transition t
+        for (int i = 0; i < 4; ++i) {
+          if (kAhead) {
+            a[0][i] = next[0][i];
+            a[1][i] = next[1][i];
+          }
+          b[i] = brow[16 * g + i];
+        }
+        if (kAhead && g + 1 < n_gt) load_rows(next, g + 1);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int wi = 16 * wt + quad + 4 * j;
-      double ar = ab[0][j], ai = ab[1][j], br = ab[2][j], bi = ab[3][j];
-      if (wi < n_w)
-        vjp_weight(omega[wi], dl, dft, eta, pref, paired, ar, ai, br, bi, sums);
-      else
-        ar = ai = br = bi = 0.0;
-      ab[0][j] = ar;
-      ab[1][j] = ai;
-      ab[2][j] = br;
-      ab[3][j] = bi;
-    }
-    if (!rhobar) continue;
-    auto load_cols = [&](double2 (&a)[2][4], int g) {
-      const int gi = 16 * g + col, gc = std::min(gi, last);
+        for (int i = 0; i < 4; ++i) {
+          // conj(a) b
+          ab[0] = mfma64(a[0][i].x, b[i].x, ab[0]);
+          ab[1] = mfma64(a[0][i].x, b[i].y, ab[1]);
+          ab[2] = mfma64(a[1][i].x, b[i].x, ab[2]);
+          ab[3] = mfma64(a[1][i].x, b[i].y, ab[3]);
+          ab[0] = mfma64(a[0][i].y, b[i].y, ab[0]);
+          ab[1] = mfma64(-a[0][i].y, b[i].x, ab[1]);
+          ab[2] = mfma64(a[1][i].y, b[i].y, ab[2]);
+          ab[3] = mfma64(-a[1][i].y, b[i].x, ab[3]);
+        }
+      }
+      // lane holds frequency 16 wt + quad + 4 j, transition t
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const size_t k = (size_t)std::min(16 * wt + quad + 4 * j, n_w - 1) * n_g + gc;
-        a[0][j] = u[k];
-        a[1][j] = v[k];
+        const int wi = 16 * wt + quad + 4 * j;
+        double ar = ab[0][j], ai = ab[1][j], br = ab[2][j], bi = ab[3][j];
+        if (wi < n_w)
+          vjp_weight(omega[wi], dl, dft, eta, pref, paired, ar, ai, br, bi, sums);
+        else
+          ar = ai = br = bi = 0.0;
+        ab[0][j] = ar;
+        ab[1][j] = ai;
+        ab[2][j] = br;
+        ab[3][j] = bi;
       }
-    };
-    if (kAhead) load_cols(next, 0);
-    for_each_of(std::make_integer_sequence<int, kTiles>{}, [&](auto G) {
-      constexpr int g = G;
-      if (g >= n_gt) return;
-      double2 a[2][4];
-      if (!kAhead) load_cols(a, g);
-      if (kAhead) {
+      if (!rhobar) continue;
+      auto load_cols = [&](double2 (&a)[2][4], int g) {
+        const int gi = 16 * g + col, gc = std::min(gi, last);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          a[0][j] = next[0][j];
-          a[1][j] = next[1][j];
+          const size_t k = (size_t)std::min(16 * wt + quad + 4 * j, n_w - 1) * n_g + gc;
+          a[0][j] = u[k];
+          a[1][j] = v[k];
         }
-        if (g + 1 < n_gt) load_cols(next, g + 1);
-      }
+      };
+      if (kAhead) load_cols(next, 0);
+      for_each_of(std::make_integer_sequence<int, kTiles>{}, [&](auto G) {
+        constexpr int g = G;
+        if (g >= n_gt) return;
+        double2 a[2][4];
+        if (!kAhead) load_cols(a, g);
+        if (kAhead) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        out[g][0] = mfma64(ab[0][j], a[0][j].x, out[g][0]);
-        out[g][1] = mfma64(ab[0][j], a[0][j].y, out[g][1]);
-        out[g][0] = mfma64(ab[1][j], a[0][j].y, out[g][0]);
-        out[g][1] = mfma64(-ab[1][j], a[0][j].x, out[g][1]);
-        out[g][0] = mfma64(ab[2][j], a[1][j].x, out[g][0]);
-        out[g][1] = mfma64(ab[2][j], a[1][j].y, out[g][1]);
-        out[g][0] = mfma64(-ab[3][j], a[1][j].y, out[g][0]);
-        out[g][1] = mfma64(ab[3][j], a[1][j].x, out[g][1]);
-      }
-    });
-  }
-  __syncthreads();
-  if (rhobar) {
-    // two tiles of response vectors at a time: [wave][tile][j][lane]
-    double2 *red = vjp_lds;
-    for_each_of(std::make_integer_sequence<int, (kTiles + 1) / 2>{}, [&](auto H) {
-      constexpr int g0 = 2 * H, g1 = std::min(g0 + 1, kTiles - 1);
-      if (g0 >= n_gt) return;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        red[(wave * 8 + j) * 64 + lane] = make_double2(out[g0][0][j], out[g0][1][j]);
-        red[(wave * 8 + 4 + j) * 64 + lane] = make_double2(out[g1][0][j], out[g1][1][j]);
-      }
-      __syncthreads();
-      for (int e = tid; e < tt * 512; e += 64 * kWaves) {
-        const int l = e & 63, j = (e >> 6) & 3, x = (e >> 8) & 1, q = e >> 9;
-        const long long tr = tb + 16 * q + (l >> 4) + 4 * j;
-        const int gi = 16 * (g0 + x) + (l & 15);
-        if (g0 + x >= n_gt || tr >= n_trans) continue;
-        double2 z = make_double2(0.0, 0.0);
-        for (int k = 0; k < ww; ++k) {
-          const double2 y = red[((q * ww + k) * 8 + 4 * x + j) * 64 + l];
-          z.x += y.x;
-          z.y += y.y;
+          for (int j = 0; j < 4; ++j) {
+            a[0][j] = next[0][j];
+            a[1][j] = next[1][j];
+          }
+          if (g + 1 < n_gt) load_cols(next, g + 1);
         }
-        rhobar[(size_t)tr * ld + gi] = gi < n_g ? z : make_double2(0.0, 0.0);
-      }
-      __syncthreads();
-    });
-  }
+        f64x4 re = kAhead ? f64x4{0.0, 0.0, 0.0, 0.0} : out[g][0];
+        f64x4 im = kAhead ? f64x4{0.0, 0.0, 0.0, 0.0} : out[g][1];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          re = mfma64(ab[0][j], a[0][j].x, re);
+          im = mfma64(ab[0][j], a[0][j].y, im);
+          re = mfma64(ab[1][j], a[0][j].y, re);
+          im = mfma64(-ab[1][j], a[0][j].x, im);
+          re = mfma64(ab[2][j], a[1][j].x, re);
+          im = mfma64(ab[2][j], a[1][j].y, im);
+          re = mfma64(-ab[3][j], a[1][j].y, re);
+          im = mfma64(ab[3][j], a[1][j].x, im);
+        }
+        out[g][0] = kAhead ? out[g][0] + re : re;
+        out[g][1] = kAhead ? out[g][1] + im : im;
+      });
+    }
+    __syncthreads();
+    if (rhobar) {
+      // two tiles of response vectors at a time: [wave][tile][j][lane]
+      double2 *red = vjp_lds;
+      for_each_of(std::make_integer_sequence<int, (kTiles + 1) / 2>{}, [&](auto H) {
+        constexpr int g0 = 2 * H, g1 = std::min(g0 + 1, kTiles - 1);
+        if (g0 >= n_gt) return;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          red[(wave * 8 + j) * 64 + lane] = make_double2(out[g0][0][j], out[g0][1][j]);
+          red[(wave * 8 + 4 + j) * 64 + lane] = make_double2(out[g1][0][j], out[g1][1][j]);
+        }
+        __syncthreads();
+        for (int e = tid; e < tt * 512; e += 64 * kWaves) {
+          const int l = e & 63, j = (e >> 6) & 3, x = (e >> 8) & 1, q = e >> 9;
+          const long long tr = tb + 16 * q + (l >> 4) + 4 * j;
+          const int gi = 16 * (g0 + x) + (l & 15);
+          if (g0 + x >= n_gt || tr >= n_trans) continue;
+          double2 z = make_double2(0.0, 0.0);
+          for (int k = 0; k < ww; ++k) {
+            const double2 y = red[((q * ww + k) * 8 + 4 * x + j) * 64 + l];
+            z.x += y.x;
+            z.y += y.y;
+          }
+          double2 *o = rhobar + (size_t)tr * ld + gi;
+          if (gi >= n_g) {
+            z = make_double2(0.0, 0.0);
+          } else if (RUNS && w0 > 0) {
+            z.x += o->x;
+            z.y += o->y;
+          }
+          *o = z;
+        }
+        __syncthreads();
+      });
+    }
+    w0 += run;
+  } while (RUNS && w0 < n_wt);
   // lanes of one column hold disjoint frequencies of the same transition
   double *ws = (double *)vjp_lds;  // [wave][3][16]
   sums.sf += __shfl_xor(sums.sf, 16);
@@ -466,11 +495,20 @@ int vjp_launch(int n_cu, const double2 *P, int ld, long long t_lo, long long n, 
   const size_t lds = std::max(red, sizeof(double2) * 16 * tt * (ld + 1));
   const long long blocks = (n + 16 * tt - 1) / (16 * tt);
   TDX_REQUIRE(blocks <= 0x7fffffffLL, TDX_ERR_SHAPE, "too many transitions");
-  TDX_HIP(hipFuncSetAttribute((const void *)k_chi0_vjp<kTiles, kWaves>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((k_chi0_vjp<kTiles, kWaves>), dim3((unsigned)blocks), dim3(64 * kWaves), lds,
-                     s, P, ld, t_lo, n, n_g, tl->delta, tl->df, (int)tl->paired, omega, n_w, eta,
-                     pref, u, v, tt, wbar, rhobar);
+  // (one wave per SIMD, four per workgroup, needs no runs)
+  auto go = [&](auto runs) -> int {
+    constexpr bool kRuns = decltype(runs)::value && kWaves == 8;
+    TDX_HIP(hipFuncSetAttribute((const void *)k_chi0_vjp<kTiles, kWaves, kRuns>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL((k_chi0_vjp<kTiles, kWaves, kRuns>), dim3((unsigned)blocks),
+                       dim3(64 * kWaves), lds, s, P, ld, t_lo, n, n_g, tl->delta, tl->df,
+                       (int)tl->paired, omega, n_w, eta, pref, u, v, tt, wbar, rhobar);
+    return TDX_OK;
+  };
+  if (rhobar && n_wt > kVjpRun * (kWaves / tt))
+    TDX_TRY(go(std::true_type{}));
+  else
+    TDX_TRY(go(std::false_type{}));
   TDX_HIP(hipGetLastError());
   return TDX_OK;
 }

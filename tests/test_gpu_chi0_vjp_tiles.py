@@ -115,3 +115,32 @@ def test_more_transitions_than_one_tile_each_launches(tdx, ctx):
                                            df * (mag * np.abs(r)).sum()])
     bad = (w_bar - dev(want)).abs() > dev(tol)
     assert not bool(bad.any())
+
+
+@pytest.mark.parametrize("n_g", [20, 60, 133, 190, 250, 300])
+def test_no_sum_of_rhobar_is_longer_than_64_frequencies(tdx, ctx, n_g):
+    """The first frequency gives 1 of rhobar, each other 2^-54 of it: those of the
+    first one's sum are lost, the others' sums kept."""
+    import torch
+    n_t, n_w = 40, 4000
+    print("vjp sum length", n_g, flush=True)
+    tr = tdx.Transitions(n_t, 0, paired=False)
+    tr.delta.fill_(0.7)
+    tr.df.fill_(0.5)
+    ld = (n_g + 15) // 16 * 16
+    P = torch.zeros(n_t, ld, dtype=torch.complex128, device="cuda")
+    P[:, 0] = 1.0
+    u = torch.zeros(n_w, n_g, dtype=torch.complex128, device="cuda")
+    v = torch.zeros_like(u)
+    u[:, 0], u[0, 0], v[:, 0] = 2.0 ** -54, 1.0, 1.0
+    om = torch.full((n_w,), 0.25, dtype=torch.float64, device="cuda")
+    _, rho_bar = tdx.chi0_vjp(ctx, tr, P, n_g, om, ETA, PREF, u, v, want_rho=True)
+    # alpha = u, beta = v = 1: rhobar_0 = sum_w 2 pref Re(w_t) u
+    x = np.longdouble(0.25) - np.longdouble(0.7)
+    r = np.longdouble(0.5) * x / (x * x + np.longdouble(ETA) ** 2)
+    ref = 2 * np.longdouble(PREF) * r * (1 + (n_w - 1) * np.longdouble(2) ** -54)
+    got = rho_bar.cpu().numpy()[:, 0].real
+    # half a unit for each of the 63, one per later sum of 64 and per wave, 16 for
+    # the weight and its products
+    tol = EPS * (32 + n_w / 64 + 8 + 16) * abs(ref)
+    assert np.all(np.abs(got - ref) <= tol)
