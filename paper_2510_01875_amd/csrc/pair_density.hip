@@ -334,9 +334,12 @@ __host__ __device__ inline size_t pd_front_bytes(int npw_max, int nb_max) {
 }
 // The form above runs where the fixed sides and an unpadded box fit (and the
 // lookup tables of the other form, whose space it uses, hold two ints per k and
-// four).
-inline bool pd_shared_fits(int npw_max, int nb_max, long box) {
-  return box >= 6 && npw_max < 65535 &&
+// four), and a transition is worth the tables: with one tile of response vectors
+// and up to 96 plane waves the other form is faster on most lists (61 plane
+// waves, N_G 15, 2.6e4 transitions on 216 k: 53 us against 64; 81: 73 against
+// 94; but 107, 4.7e4: 86 against 100, 2.4e4: 97 against 67).
+inline bool pd_shared_fits(int npw_max, int nb_max, long box, int n_gt) {
+  return box >= 6 && npw_max < 65535 && n_gt * npw_max > 96 &&
          pd_front_bytes(npw_max, nb_max) + sizeof(short) * box <= kPdLds;
 }
 
@@ -345,12 +348,17 @@ inline bool pd_shared_fits(int npw_max, int nb_max, long box) {
 // chunk left 39 % of the wavefronts' time idle, since an XCD deals workgroups
 // to its shader engines in turn whatever their load, and half of the k-points
 // of a paired list hold none.  A chunk is a tile per wavefront, fewer where
-// the list is short, and more where a tile is short against the tables that are
-// built for each (about 15 us; 16 n_gt npw cycles per tile).  About two thirds
-// of a list's tiles belong to one of the two launches.
+// the list is short and its tiles long, and more where a tile is short against
+// the tables that are built for each (about 15 us; 16 n_gt npw cycles per tile).
+// About two thirds of a list's tiles belong to one of the two launches.  A list
+// of short rows has up to three times the tiles that are taken for it, and below
+// 600 n_gt npw the tables then cost more than the CUs that larger chunks leave
+// idle (61 plane waves, N_G 55, 5202 transitions on 216 k: 171 us with one tile,
+// 77 with eight; 155 and 70 at N_G 129, 52 plane waves).
 inline int pd_chunk(long long n_trans, int n_gt, int npw_max, int n_cu) {
   const double tiles = n_trans / 24.0;
-  if (tiles < 8.0 * n_cu) return std::max(1, (int)std::ceil(tiles / n_cu));
+  if (tiles < 8.0 * n_cu)
+    return n_gt * npw_max <= 600 ? kPdWaves : std::max(1, (int)std::ceil(tiles / n_cu));
   const int least = (2800 + n_gt * npw_max - 1) / (n_gt * npw_max);
   return 8 * std::min({8, least, std::max(1, (int)(tiles / (32.0 * n_cu) + 0.5))});
 }
@@ -715,7 +723,7 @@ int pd_enqueue(int n_cu, const tdx_states *st, const int qj[3], const tdx_transl
   hipLaunchKernelGGL(k_kq_map, dim3((nk + 255) / 256), dim3(256), 0, s, st->kgrid[0],
                      st->kgrid[1], st->kgrid[2], qj[0], qj[1], qj[2], w.kp, w.gs);
   TDX_HIP(hipGetLastError());
-  const bool shared = pd_shared_fits(st->npw_max, nb_max, box);
+  const bool shared = pd_shared_fits(st->npw_max, nb_max, box, ld_of(n_g) / 16);
   if (!shared) {
     hipLaunchKernelGGL(k_fill<int>, dim3(1024), dim3(256), 0, s, w.lut, (long long)nk * box, -1);
     TDX_HIP(hipGetLastError());
