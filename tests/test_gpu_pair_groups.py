@@ -29,12 +29,15 @@ def ctx(tdx):
 
 def _system(tdx, npw, nb, seed):
     """States on a 2 x 1 x 1 grid: random bases, coefficients and occupations."""
+    half = 4  # of the cube the plane waves come from: the smallest that holds them
+    while (2 * half + 1) ** 3 < npw + 3:
+        half += 1
     import torch
     rng = np.random.default_rng(seed)
     d = tdx.StatesDims()
     d.n_k, d.npw_max, d.nb_max = 2, npw + 3, nb
     st = tdx.States(d, 0)
-    ax = np.arange(-4, 5)
+    ax = np.arange(-half, half + 1)
     cube = np.stack(np.meshgrid(ax, ax, ax, indexing="ij"), -1).reshape(-1, 3)
     n = [npw, npw + 3]
     mil = np.zeros((2, npw + 3, 3), dtype=np.int32)
@@ -50,7 +53,7 @@ def _system(tdx, npw, nb, seed):
                  (st.miller, mil), (st.eps, eps), (st.occ, occ), (st.coef, coef)):
         t.copy_(torch.from_numpy(x))
     st.c.kgrid[:] = [2, 1, 1]
-    st.c.mmax[:] = [4, 4, 4]
+    st.c.mmax[:] = [half] * 3
     return st, n, mil, coef
 
 
@@ -104,3 +107,15 @@ def test_pair_densities_match_the_defining_sum(tdx, ctx, npw, nb, n_g, reach, pa
     assert np.all(np.abs(part - ref[b0:b1]) <= tol[b0:b1])
     p32 = tdx.pair_density_view(tdx.pair_density(ctx, st, qj, tr, gb, "fp32"), T, n_g, "fp32")
     assert torch.equal(p32, whole[:, :n_g].to(torch.complex64))
+
+
+# one group per workgroup, which runs where the shared form's fixed sides and box
+# do not fit: plane waves on either side of that line, then one wavefront with
+# the Miller indices in LDS, eight with them, eight without; and either side of
+# 96 plane waves at one tile of response vectors
+@pytest.mark.parametrize("paired", [False, True])
+@pytest.mark.parametrize("npw,nb,n_g,reach",
+                         [(1214, 5, 17, 3), (1215, 5, 17, 3), (1400, 7, 33, 4), (3000, 6, 17, 3),
+                          (6350, 5, 16, 3), (93, 30, 16, 3), (94, 30, 16, 3)])
+def test_larger_bases_match_the_defining_sum(tdx, ctx, npw, nb, n_g, reach, paired):
+    test_pair_densities_match_the_defining_sum(tdx, ctx, npw, nb, n_g, reach, paired)
