@@ -234,7 +234,8 @@ int launch_fp(const void *P, int ld, const double *delta, const double *df, int 
 
 
 // ------------------------------------------------- all columns in one tile
-// Bases of 17 to 29 and of 33 to 144 vectors.  The rows (w, G) of w_t(w) rho_t(G) are one list
+// Bases of 17 to 29 and of 33 to 144 vectors, on lists long enough for them
+// (rows_pay).  The rows (w, G) of w_t(w) rho_t(G) are one list
 // of n_w n_g, dealt to the waves in tiles of 16 whatever frequencies these
 // hold, against all columns G': no row is padding, one set of rho rows in LDS
 // (contiguous in memory) serves rows and columns, and a tile of A is formed
@@ -472,16 +473,37 @@ void chi0_fp32_shape(int v, int *wblock, int *cols, int *chunk) {
   *chunk = V.chunk;
 }
 
-// The launch of a basis of 17 to 144 vectors (but 30 to 32) does not depend on
-// the variant, which still sets the slices (and so the order of the sums).
+// Whether the tiles that hold all columns come out ahead of the variant's.  They
+// do at 4, 6 and 7 column blocks.  Those of 2, 3, 5 and 9 spill around the run of
+// a list, and at 2, 8 and 9 a workgroup's share is larger than the variant's, so
+// that a list of few slices leaves CUs idle: steps pay that back, by the list's
+// length or by that times the frequencies.
+// Either side of the lines, all-column tiles over the variant's, mean over the
+// bases: 2 columns 1.18 (80 frequencies, 700 transitions) and 0.90 (130, 1000);
+// 3: 1.04 (20, 700) and 0.93 (40, 1000); 5: 1.07 (80, 100) and 0.95 (20, 700);
+// 8: 1.04 (20, 100) and 0.93 (20, 300); 9: 1.13 (20, 100) and 0.82 (20, 300).
+// 30 to 32 vectors have hardly any padding to save (N_G 32, 700 frequencies,
+// 2000 transitions: 240 us, 231 in the tiles of the variant).
+bool rows_pay(int n_g, int n_w, long long n_trans) {
+  const long long work = n_trans * n_w;
+  switch ((n_g + 15) / 16) {
+    case 2: return n_g <= 29 && (n_trans >= 5000 || work >= 100000);
+    case 3: return n_trans >= 5000 || work >= 40000;
+    case 5: return n_trans >= 1000 || work >= 13000;
+    case 8: return n_trans >= 700 || work >= 4000;
+    case 9: return n_trans >= 300;
+  }
+  return true;
+}
+
+// The launch of a basis of 17 to 144 vectors does not depend on the variant
+// where rows_pay; the variant still sets the slices (and so the order of the
+// sums).
 int chi0_fp32_launch(int v, const void *P, int ld, const double *delta, const double *df,
                      int paired, long long n_trans, long long slice_len, int slices,
                      const double *omega, int n_w, double eta, int n_g, double2 *part,
                      hipStream_t s) {
-  // 30 to 32 vectors: hardly any padding to save, and the six row tiles of two
-  // column blocks spill (N_G 32, 700 frequencies, 2000 transitions: 240 us,
-  // 231 in the tiles of the variant; 29 and less come out ahead)
-  switch (ld == 32 && n_g > 29 ? 0 : ld / 16) {
+  switch (rows_pay(n_g, n_w, n_trans) ? ld / 16 : 0) {
 #define TDX_ROWS(N, R)                                                                         \
   case N:                                                                                      \
     return launch_rows<R, N>(P, delta, df, paired, n_trans, slice_len, slices, omega, n_w, eta, \

@@ -87,3 +87,52 @@ def test_a_value_that_is_not_finite_stays_in_its_row_and_column(tdx, ctx, n_g, n
                    .cpu().numpy().reshape(n_w, n_g, n_g))
     assert np.array_equal(out[0][:, :-1, :-1], out[1][:, :-1, :-1])
     assert not np.isfinite(out[1][:, -1, -1]).any()
+
+
+# lists on which the all-column tiles run, and, in several chunks, slices and
+# tiles, those on which the general tiles do
+@pytest.mark.parametrize("paired", [False, True])
+@pytest.mark.parametrize("n_g,n_w,n_t",
+                         [(17, 1, 5001), (29, 60, 5000), (31, 60, 5000), (33, 5, 5003),
+                          (48, 11, 8200), (80, 5, 1040), (113, 5, 731), (128, 2, 705),
+                          (129, 3, 331), (144, 4, 8200), (16, 40, 300), (29, 60, 1666),
+                          (29, 60, 1667), (30, 60, 8200), (32, 40, 300), (48, 40, 999),
+                          (48, 40, 1000), (80, 13, 999), (80, 13, 1000), (128, 10, 399),
+                          (128, 10, 400), (144, 4, 299), (144, 4, 300), (145, 20, 100)])
+def test_chi0_of_other_lists_matches_the_defining_sum(tdx, ctx, n_g, n_w, n_t, paired):
+    test_chi0_matches_the_defining_sum(tdx, ctx, n_g, n_w, n_t, paired)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+@pytest.mark.parametrize("n_g,n_t", [(20, 5003), (48, 8005), (80, 1001), (128, 805), (144, 333)])
+def test_a_value_that_is_not_finite_stays_in_place_in_longer_lists(tdx, ctx, n_g, n_t, bad):
+    test_a_value_that_is_not_finite_stays_in_its_row_and_column(tdx, ctx, n_g, n_t, bad)
+
+
+@pytest.mark.parametrize("n_w", [20, 80])
+def test_a_short_list_of_29_vectors_takes_no_longer_than_one_of_30(tdx, ctx, n_w):
+    import time
+
+    import torch
+    n_t, us = 300, []
+    rng = np.random.default_rng(n_w)
+    tr = tdx.Transitions(n_t, 0, paired=True)
+    tr.delta.copy_(torch.from_numpy(rng.uniform(0.05, 1.5, n_t)))
+    tr.df.copy_(torch.from_numpy(rng.uniform(0.1, 1.0, n_t)))
+    om = torch.linspace(0.0, 2.0, n_w, device="cuda", dtype=torch.float64)
+    P = torch.ones((n_t, 32), dtype=torch.complex64, device="cuda")
+    for n_g in (29, 30):
+        P[:, n_g:] = 0
+        out = torch.empty(n_w * n_g * n_g, dtype=torch.complex128, device="cuda")
+        best = 1e9
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(20):
+                tdx.chi0(ctx, tr, P, n_g, "fp32", om, ETA, PREF, out=out)
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t0) / 20)
+        us.append(1e6 * best)
+        print("chi0 fp32 short", n_w, n_g, us, flush=True)
+        P[:, :] = 1
+    assert us[0] < 1.12 * us[1]
