@@ -384,7 +384,8 @@ int tdx_chi0_bf16x3_slicing(int n_cu, int variant, int64_t n_trans, int n_g, int
 int tdx_autotune_chi0(tdx_ctx *ctx, const tdx_chi0_item *probe, int prec, int64_t max_trans,
                       int *best_variant, int *best_slice_log2, double *best_ms);
 /* Tuning cache as JSON text keyed by the gfx arch, one entry per precision
- * and size class. */
+ * and size class.  Loading passes over the entries whose variants number other
+ * tiles than this library's (FP64 ones of earlier caches). */
 int tdx_tune_save(tdx_ctx *ctx, const char *path);
 int tdx_tune_load(tdx_ctx *ctx, const char *path);
 

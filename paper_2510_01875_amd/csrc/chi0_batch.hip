@@ -95,6 +95,10 @@ int variant_count(int prec) {
                                  : chi0_fp32_variant_count();
 }
 
+// The set of tiles that a precision's variants number, counted up when a number
+// comes to mean another tile (FP64: tiles of pairs in place of columns).
+int tile_set(int prec) { return prec == TDX_PREC_FP64 ? 2 : 1; }
+
 const char *prec_name(int prec) {
   return prec == TDX_PREC_FP64 ? "fp64" : prec == TDX_PREC_FP32 ? "fp32" : "bf16x3";
 }
@@ -661,8 +665,8 @@ int tdx_tune_save(tdx_ctx *ctx, const char *path) {
       if (t.variant < 0) continue;
       std::fprintf(f,
                    "%s  {\"prec\": \"%s\", \"blocks\": %d, \"variant\": %d, \"slice_log2\": %d, "
-                   "\"ms\": %.4f}",
-                   first ? "" : ",\n", prec_name(p), b, t.variant, t.slice_log2, t.ms);
+                   "\"ms\": %.4f, \"tiles\": %d}",
+                   first ? "" : ",\n", prec_name(p), b, t.variant, t.slice_log2, t.ms, tile_set(p));
       first = false;
     }
   std::fprintf(f, "\n]}\n");
@@ -683,18 +687,21 @@ int tdx_tune_load(tdx_ctx *ctx, const char *path) {
     int b, v, sl;
     double ms;
     char pn[16] = "bf16x3";
+    int tiles = 1;
     // entries name their precision; entries without one (older caches)
-    // are split-BF16
+    // are split-BF16, and those without a tile set are of the first
     const bool with_prec =
         std::sscanf(line, " {\"prec\": \"%15[a-z0-9]\", \"blocks\": %d, \"variant\": %d, "
-                          "\"slice_log2\": %d, \"ms\": %lf}", pn, &b, &v, &sl, &ms) == 5;
+                          "\"slice_log2\": %d, \"ms\": %lf, \"tiles\": %d}", pn, &b, &v, &sl, &ms,
+                    &tiles) >= 5;
     if (arch_ok && (with_prec || std::sscanf(line, " {\"blocks\": %d, \"variant\": %d, "
                                                   "\"slice_log2\": %d, \"ms\": %lf}",
                                              &b, &v, &sl, &ms) == 4)) {
       int p = -1;
       for (int q = TDX_PREC_FP64; q <= TDX_PREC_BF16X3; ++q)
         if (std::strcmp(pn, prec_name(q)) == 0) p = q;
-      if (p >= 0 && b >= 0 && b < 64 && v >= 0 && v < variant_count(p) && sl >= 10 && sl <= 30) {
+      // a variant of another set of tiles says nothing about this one's
+      if (p >= 0 && tiles == tile_set(p) && b >= 0 && b < 64 && v >= 0 && v < variant_count(p) && sl >= 10 && sl <= 30) {
         ctx->tune[p][b] = tdx_chi0_tune{v, sl, ms};
         ++loaded;
       }

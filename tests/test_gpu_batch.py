@@ -235,3 +235,34 @@ def test_fp_variants_tune_and_match_oracle(tdx, ctx, prec, tol):
     c2.close()
     tdx.chi0_set_config(ctx, n_g, -1, 20, "bf16x3")
     tdx.chi0_set_config(ctx, n_g, -1, 20, prec)
+
+
+def test_a_tuning_cache_of_other_tiles_is_passed_over(tdx, tmp_path):
+    """Entries without a tile set are of the first, which FP32 and split-BF16
+    still number and FP64 no longer does."""
+    _say("cache of other tiles")
+    line = '  {{"prec": "{}", "blocks": 9, "variant": {}, "slice_log2": 19, "ms": 1.5{}}},\n'
+    ctx = tdx.Context(0)
+    default = {p: tdx.chi0_get_config(ctx, 133, p) for p in ("fp64", "fp32", "bf16x3")}
+    old = {p: (default[p][0] + 1) % tdx.chi0_variants(p) for p in default}
+    path = str(tmp_path / "old.json")
+    with open(path, "w") as f:
+        f.write('{"arch": "gfx950", "entries": [\n')
+        f.writelines(line.format(p, v, "") for p, v in old.items())
+        f.write(line.format("fp64", old["fp64"], ', "tiles": 1'))
+        f.write(line.format("fp32", 0, ', "tiles": 9'))
+        f.write("]}\n")
+    tdx.tune_load(ctx, path)
+    assert tdx.chi0_get_config(ctx, 133, "fp64") == default["fp64"]
+    assert tdx.chi0_get_config(ctx, 133, "fp32") == (old["fp32"], 19)
+    assert tdx.chi0_get_config(ctx, 133, "bf16x3") == (old["bf16x3"], 19)
+    # what is saved now is loaded whole
+    for p in default:
+        tdx.chi0_set_config(ctx, 133, old[p], 20, p)
+    path = str(tmp_path / "new.json")
+    tdx.tune_save(ctx, path)
+    ctx.close()
+    ctx = tdx.Context(0)
+    tdx.tune_load(ctx, path)
+    assert all(tdx.chi0_get_config(ctx, 133, p) == (old[p], 20) for p in default)
+    ctx.close()
