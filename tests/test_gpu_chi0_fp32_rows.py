@@ -103,6 +103,19 @@ def test_chi0_of_other_lists_matches_the_defining_sum(tdx, ctx, n_g, n_w, n_t, p
     test_chi0_matches_the_defining_sum(tdx, ctx, n_g, n_w, n_t, paired)
 
 
+# several chunks, columns that end inside a tile of each variant
+@pytest.mark.parametrize("variant", range(5))
+@pytest.mark.parametrize("n_g,n_w,n_t", [(16, 33, 300), (32, 20, 200), (48, 17, 130),
+                                         (80, 5, 99), (145, 9, 100), (180, 3, 65)])
+def test_every_variant_of_the_general_tiles_matches_the_defining_sum(tdx, n_g, n_w, n_t, variant):
+    assert tdx.chi0_variants("fp32") == 5
+    c = tdx.Context(0)
+    tdx.chi0_set_config(c, n_g, variant, 20, "fp32")
+    assert tdx.chi0_get_config(c, n_g, "fp32")[0] == variant
+    test_chi0_matches_the_defining_sum(tdx, c, n_g, n_w, n_t, True)
+    c.close()
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 @pytest.mark.parametrize("n_g,n_t", [(20, 5003), (48, 8005), (80, 1001), (128, 805), (144, 333)])
 def test_a_value_that_is_not_finite_stays_in_place_in_longer_lists(tdx, ctx, n_g, n_t, bad):
