@@ -341,14 +341,17 @@ int tdx_chi0_batched(tdx_ctx *ctx, const tdx_chi0_item *items, int n_items, int 
                      tdx_stream stream);
 
 /* Number of tile variants of a precision (frequencies per wave x G' per
- * workgroup x chunk, and for split-BF16 buffering and waves per workgroup). */
+ * workgroup x chunk, for split-BF16 also buffering and waves per workgroup; for
+ * FP64 waves of 16 pairs of vectors x blocks of 16 frequencies). */
 int tdx_chi0_variants(int prec, int *count);
 /* Tile variant (-1 = default: for split-BF16 the 8-wave 2 x 9 tile with three
  * LDS buffers, for FP32 variant 0, for FP64 variant 0 or 3 by the number of
  * pairs of basis vectors) and slice length 2^slice_log2
  * (default 2^20; split-BF16 only, the FP32 and FP64 kernels choose their
  * slices to fill the chip) used for bases of n_g vectors (size classes of
- * 16), per precision. */
+ * 16), per precision.  FP32 bases of 17 to 29 and 33 to 144 vectors run other
+ * tiles on all but short lists, with the same results; there the variant sets
+ * the slices only, so tuning it at such a size ranks little but noise. */
 int tdx_chi0_set_config(tdx_ctx *ctx, int prec, int n_g, int variant, int slice_log2);
 int tdx_chi0_get_config(tdx_ctx *ctx, int prec, int n_g, int *variant, int *slice_log2);
 /* Slice length of every later chi0 contraction on this context (all
@@ -540,7 +543,7 @@ int tdx_dielectric(tdx_ctx *ctx, const double *S, const double *omega, int n_w, 
  * its own filtered value (the smoother's diagonal; its sum is the filter's
  * effective number of parameters).  windows, degrees: host [n_filt]; each
  * window odd, above its degree and at most n_w; degrees 0..8, else
- * INVALID_ARG.  Synchronises (the host lists are copied on the stream). */
+ * INVALID_ARG.  Synchronises. */
 int tdx_sg_filter(tdx_ctx *ctx, const double *S, int n_w, const int *windows,
                   const int *degrees, int n_filt, double *Sp, double *hdiag, tdx_stream stream);
 

@@ -2,9 +2,9 @@
 // (for a time-reversal-paired list each kept t carries its partner too, with
 // the weight df_t [1/(w - delta_t + i eta) - 1/(w + delta_t + i eta)]).
 //
-// The entry point and the slice reduction.  The contraction kernels: FP32 and
-// FP64 in chi0_fp.hip, split-BF16 in chi0_bf16x3.hip (with its batches in
-// chi0_batch.hip).  The transition axis is cut into slices whose FP64
+// The entry point and the slice reduction.  The contraction kernels: FP32
+// in chi0_fp.hip, FP64 in chi0_fp64.hip (with its slice reduction), split-BF16
+// in chi0_bf16x3.hip (with its batches in chi0_batch.hip).  The transition axis is cut into slices whose FP64
 // partials are summed here in a fixed order (no atomics: bitwise
 // reproducible).
 #include <algorithm>
